@@ -334,11 +334,14 @@ int policy_asymre_fwd_bwd(const float* logp, const int32_t* seq_of_token, const 
  * fp32 [T]; dhidden device fp32 [T, d] (overwritten); dW device fp32 [V, d]
  * (overwritten, or accumulated into when accumulate_dW != 0).
  * ws device: the tokens are processed in chunks of Tc tokens, with Tc the
- * largest multiple of 256 (at most T rounded up to 256) whose
- * rbp_workspace_bytes(RBP_OP_LOGPROB_BWD, Tc, d, V) fits in ws_bytes.  With
- * Vp = V rounded up to 256 it holds dz^T (bf16 [Vp, Tc]) and a split-K
- * partial of dhidden (fp32 [Tc, d]): 5.2 GB for Tc = 16384 at d = 3584,
- * V = 152064.
+ * largest multiple of 256 (at most T rounded up to 256) whose dz^T (bf16
+ * [Vp, Tc], Vp = V rounded up to 256) and split-K partial of dhidden (fp32
+ * [Tc, d]) fit in ws_bytes: 5.2 GB for Tc = 16384 at d = 3584, V = 152064.
+ * rbp_workspace_bytes(RBP_OP_LOGPROB_BWD, Tc, d, V) adds up to 64 MB for
+ * further partials of dhidden where a small chunk leaves compute units idle;
+ * a workspace of its size is cut into chunks of exactly Tc.  Any bytes beyond
+ * the chunk's least are used for them, so results may differ in rounding
+ * between workspaces of different sizes.
  * Errors: RBP_EINVAL; RBP_EUNSUPPORTED (d % 8 != 0); RBP_EWORKSPACE (not even
  * a 256-token chunk fits).
  */
@@ -399,12 +402,13 @@ typedef struct rbp_exec {
  * fp32 [T] (overwritten; may be NULL; 0 for masked tokens); dhidden, dW,
  * accumulate_dW as in policy_logprob_bwd.
  * ws device: tokens are processed in chunks of Tc tokens, with Tc the largest
- * multiple of 256 (at most T rounded up to 256, at most 2^21) whose
- * rbp_workspace_bytes(RBP_OP_FUSED, Tc, d, V) fits in ws_bytes: with
- * Vp = V rounded up to 256, bf16 [Vp, Tc], fp32 [3 Vp / 128, Tc] partial
- * sums, five fp32 / int32 [Tc] arrays, bf16 [Tc, d] (scaled hidden states),
- * fp32 [Tc, d] and the loss pass's sums -- 5.6 GB for Tc = 16384 at
- * d = 3584, V = 152064.
+ * multiple of 256 (at most T rounded up to 256, at most 2^21) for which these
+ * fit in ws_bytes: with Vp = V rounded up to 256, bf16 [Vp, Tc], fp32
+ * [3 Vp / 128, Tc] partial sums, five fp32 / int32 [Tc] arrays, bf16 [Tc, d]
+ * (scaled hidden states), fp32 [Tc, d] and the loss pass's sums -- 5.6 GB for
+ * Tc = 16384 at d = 3584, V = 152064.  As for policy_logprob_bwd,
+ * rbp_workspace_bytes(RBP_OP_FUSED, Tc, d, V) may add up to 64 MB for partial
+ * sums of dhidden at small chunks.
  * Errors: RBP_EINVAL (null pointers, T < 0, d < 1, V < 1, B < 1,
  *         n_seq_total < 1, eps < 0); RBP_EUNSUPPORTED (d % 8 != 0);
  *         RBP_EWORKSPACE (not even a 256-token chunk fits); RBP_EHIP (a

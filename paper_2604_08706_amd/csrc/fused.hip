@@ -396,19 +396,21 @@ __global__ void __launch_bounds__(256) token_scale_kernel(
   }
 }
 
-// Workspace: Q^T [Vp][Tc] bf16, partials M, S, E [Vp / 128][Tc] fp32, the
-// per-token target logit, reference R, chosen reference and scale [Tc] fp32,
-// the list of re-referenced tokens [Tc] and its count, H' [Tc][d] bf16, the
-// second dhidden K half [Tc][d] fp32, the loss pass's partial sums.
+// Workspace: Q^T [Vp][Tc] bf16, the per-token target logit, reference R,
+// chosen reference and scale [Tc] fp32, the list of re-referenced tokens [Tc]
+// and its count, the loss pass's partial sums, H' [Tc][d] bf16, partials M,
+// S, E [Vp / 128][Tc] fp32 and [Tc][d] fp32 of scratch.  The partials are
+// scratch too once the fix-up has read them (dW's partial sums), and so is H'
+// once dW has (dhidden's).
 struct FusedWs {
   uint16_t* Qt;
-  float *pM, *pS, *pE;
   float *zy, *R, *ref, *cs;
   int32_t *listed, *n_listed;
-  uint16_t* Hp;
-  float* dh_half;
   void* loss;
   size_t loss_bytes;
+  uint16_t* Hp;
+  float *pM, *pS, *pE;
+  size_t hp_at, pm_at;  // byte offsets of Hp and pM
   size_t bytes;
 };
 
@@ -417,19 +419,21 @@ FusedWs carve_fused(void* base, int64_t Tc, int32_t d, int32_t V) {
   const int64_t Vp = round256(V);
   FusedWs w;
   w.Qt = c.take<uint16_t>((size_t)Vp * (size_t)Tc);
-  w.pM = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
-  w.pS = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
-  w.pE = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
   w.zy = c.take<float>((size_t)Tc);
   w.R = c.take<float>((size_t)Tc);
   w.ref = c.take<float>((size_t)Tc);
   w.cs = c.take<float>((size_t)Tc);
   w.listed = c.take<int32_t>((size_t)Tc);
   w.n_listed = c.take<int32_t>(1);
-  w.Hp = c.take<uint16_t>((size_t)Tc * (size_t)d);
-  w.dh_half = c.take<float>((size_t)Tc * (size_t)d);
   w.loss_bytes = rbp::loss_ws(Tc);
   w.loss = c.take<uint8_t>(w.loss_bytes);
+  w.hp_at = rbp::align_up(c.used, 256);
+  w.Hp = c.take<uint16_t>((size_t)Tc * (size_t)d);
+  w.pm_at = rbp::align_up(c.used, 256);
+  w.pM = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
+  w.pS = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
+  w.pE = c.take<float>((size_t)(Vp / 128) * (size_t)Tc);
+  c.take<float>((size_t)Tc * (size_t)d);
   w.bytes = rbp::align_up(c.used, 256);
   return w;
 }
@@ -437,7 +441,11 @@ FusedWs carve_fused(void* base, int64_t Tc, int32_t d, int32_t V) {
 }  // namespace
 
 size_t rbp::fused_ws(int64_t Tc, int32_t d, int32_t V) {
-  return carve_fused(nullptr, round256(Tc < 1 ? 1 : Tc), d < 1 ? 1 : d, V < 1 ? 1 : V).bytes;
+  const int64_t T256 = round256(Tc < 1 ? 1 : Tc);
+  const int32_t dd = d < 1 ? 1 : d, VV = V < 1 ? 1 : V;
+  const FusedWs w = carve_fused(nullptr, T256, dd, VV);
+  return w.bytes + dhidden_extra(T256, dd, VV, w.bytes - w.hp_at, w.bytes,
+                                 carve_fused(nullptr, T256 + 256, dd, VV).bytes);
 }
 
 namespace {
@@ -474,8 +482,8 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
               RBP_EINVAL, "policy_fused_fwd_bwd: null per-token pointer");
   hipStream_t s = rbp::as_stream(stream);
   if (T == 0) {
-    rbp::launch_grad_products(nullptr, W, nullptr, 0, 0, d, V, nullptr, nullptr, dW,
-                              accumulate_dW, s);
+    rbp::launch_grad_products(nullptr, W, nullptr, 0, 0, d, V, nullptr, dW, accumulate_dW, s,
+                              nullptr, 0);
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     return RBP_OK;
   }
@@ -484,17 +492,17 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
   int64_t Tc = 0;
   if (ws) {
     int64_t lo = 256, hi = round256(T) < (int64_t(1) << 21) ? round256(T) : (int64_t(1) << 21);
-    if (rbp::fused_ws(lo, d, V) <= ws_bytes) {
+    if (carve_fused(nullptr, lo, d, V).bytes <= ws_bytes) {
       while (lo < hi) {
         const int64_t mid = (lo + hi + 256) / 512 * 256;
-        if (rbp::fused_ws(mid, d, V) <= ws_bytes) lo = mid; else hi = mid - 256;
+        if (carve_fused(nullptr, mid, d, V).bytes <= ws_bytes) lo = mid; else hi = mid - 256;
       }
       Tc = lo;
     }
   }
   RBP_REQUIRE(Tc >= 256, RBP_EWORKSPACE,
               "policy_fused_fwd_bwd: workspace of %zu bytes holds no 256-token chunk (needs %zu)",
-              ws_bytes, rbp::fused_ws(256, d, V));
+              ws_bytes, carve_fused(nullptr, 256, d, V).bytes);
   const FusedWs w = carve_fused(ws, Tc, d, V);
   const int64_t Vp = round256(V), tiles_v = Vp / 256;
   const int n_cu = device_cus();
@@ -541,12 +549,13 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_SCALE);
     const int acc = (accumulate_dW || t0 > 0) ? 1 : 0;
-    // the dhidden K half is free until dhidden runs
-    rbp::launch_dweight(w.Hp, w.Qt, Tc, Tn, d, V, dW, acc, 0, tiles_v, s, w.dh_half,
-                        Tc * (int64_t)d);
+    rbp::launch_dweight(w.Hp, w.Qt, Tc, Tn, d, V, dW, acc, 0, tiles_v, s, w.pM,
+                        (int64_t)((ws_bytes - w.pm_at) / sizeof(float)));
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_DW);
-    rbp::launch_dhidden(W, w.Qt, Tc, Tn, d, V, dhidden + t0 * d, w.dh_half, s, w.cs);
+    rbp::launch_dhidden(W, w.Qt, Tc, Tn, d, V, dhidden + t0 * d, s,
+                        reinterpret_cast<float*>(w.Hp),
+                        (int64_t)((ws_bytes - w.hp_at) / sizeof(float)), w.cs);
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_DHIDDEN);
   }

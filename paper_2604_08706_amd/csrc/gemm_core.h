@@ -88,18 +88,20 @@ struct Grid {
 // enough waves keep loads in flight to feed a 256 x 256 tile.
 using Grid8 = Grid<2, 4>;
 
-// Block id -> (tile_m, tile_n).  The dispatcher hands block b to XCD b % 8, so
-// blocks are first renumbered XCD by XCD (each XCD gets a contiguous range of
-// tiles), then rastered in groups of `group_m` M-tiles per N-tile: the ~32
-// blocks an XCD runs at once form a compact group_m x (32 / group_m) patch
-// whose operand rows are shared through that XCD's L2.
-__device__ __forceinline__ void map_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n,
-                                         int32_t group_m, int32_t& tm, int32_t& tn) {
-  const uint32_t nblk = (uint32_t)tiles_m * (uint32_t)tiles_n;
-  const uint32_t xcd = (uint32_t)bid & 7u, local = (uint32_t)bid >> 3;
+// Block id -> position in XCD-contiguous order.  The dispatcher hands block b
+// to XCD b % 8; renumbering the nblk blocks XCD by XCD gives each XCD a
+// contiguous range of positions.
+__host__ __device__ __forceinline__ uint32_t xcd_order(uint32_t bid, uint32_t nblk) {
+  const uint32_t xcd = bid & 7u, local = bid >> 3;
   const uint32_t per = nblk >> 3, rem = nblk & 7u;
-  const uint32_t L = xcd < rem ? xcd * (per + 1) + local
-                               : rem * (per + 1) + (xcd - rem) * per + local;
+  return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+}
+
+// Position -> (tile_m, tile_n): groups of `group_m` M-tiles per N-tile, so
+// that the ~32 blocks an XCD runs at once form a compact group_m x
+// (32 / group_m) patch whose operand rows are shared through that XCD's L2.
+__device__ __forceinline__ void raster_tile(uint32_t L, int32_t tiles_m, int32_t tiles_n,
+                                            int32_t group_m, int32_t& tm, int32_t& tn) {
   const uint32_t group_size = (uint32_t)group_m * (uint32_t)tiles_n;
   const uint32_t g = L / group_size;
   const uint32_t first_m = g * (uint32_t)group_m;
@@ -109,6 +111,13 @@ __device__ __forceinline__ void map_tile(int32_t bid, int32_t tiles_m, int32_t t
   const uint32_t in = L - g * group_size;
   tm = (int32_t)(first_m + in % gm);
   tn = (int32_t)(in / gm);
+}
+
+// Block id -> (tile_m, tile_n) of a launch over every tile.
+__device__ __forceinline__ void map_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n,
+                                         int32_t group_m, int32_t& tm, int32_t& tn) {
+  raster_tile(xcd_order((uint32_t)bid, (uint32_t)tiles_m * (uint32_t)tiles_n), tiles_m, tiles_n,
+              group_m, tm, tn);
 }
 
 }  // namespace gemm

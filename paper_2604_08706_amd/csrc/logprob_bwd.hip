@@ -16,6 +16,7 @@
 // atomics are used, so results are bitwise reproducible.
 
 #include "logits_epilogue.h"
+#include "pieces.h"
 #include "rbp_internal.h"
 
 namespace {
@@ -25,6 +26,10 @@ using rbp::gemm::kLdsBytes;
 using rbp::gemm::Tile;
 using rbp::gemm::tile_stream;
 using rbp::gemm::map_tile;
+using rbp::gemm::raster_tile;
+using rbp::gemm::xcd_order;
+using rbp::gemm::Pieces;
+using rbp::gemm::plan_pieces;
 using rbp::gemm::Operand;
 using rbp::gemm::kKMajor;
 using rbp::gemm::kMNMajor;
@@ -110,159 +115,116 @@ __global__ void __launch_bounds__(256) target_dz_kernel(
 
 // Backward step 2: dH[t][m] = c_t sum_v W[v][m] dz[t][v], with A = W and
 // B = dz^T both read MN-major (m / t contiguous, k = vocabulary); c_t = 1,
-// or cs[t] for the single pass.  The launch covers n_vid tiles from virtual
-// tile vid_base on, over the whole vocabulary, or (split_steps > 0) each in
-// two K halves of split_steps steps: virtual block 2 i + h is half h of tile
-// vid_base + i; half 0 writes dH, half 1 its part[i] block ([t][m], 256 x
-// 256 fp32), added by part_add_dh_kernel -- or, with part_full, its rows of
-// part laid out like dH ([Tn][d]), added by add_f32_kernel.
+// or cs[t] for the single pass.
+//
+// Stores one finished tile, rows scaled by c_t, into `out` laid out like dH.
+__device__ __forceinline__ void store_dh(const Tile& tile, const f32x16 (&acc)[GL::MI][GL::NI],
+                                         int64_t Tn, int32_t d, const float* __restrict__ cs,
+                                         float* __restrict__ out) {
+#pragma unroll
+  for (int ni = 0; ni < GL::NI; ++ni) {
+    const int64_t t = tile.n0 + GL::col(ni);
+    if (t >= Tn) continue;
+    const float c = cs != nullptr ? cs[t] : 1.0f;  // per-token scale of the single pass
+#pragma unroll
+    for (int mi = 0; mi < GL::MI; ++mi)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const int64_t m = tile.m0 + GL::row(mi, rg * 4);
+        if (m < d)
+          *reinterpret_cast<float4*>(out + t * d + m) =
+              make_float4(c * acc[mi][ni][rg * 4 + 0], c * acc[mi][ni][rg * 4 + 1],
+                          c * acc[mi][ni][rg * 4 + 2], c * acc[mi][ni][rg * 4 + 3]);
+      }
+  }
+}
+
+// Whole rounds: the first n_vid tiles in raster order, the whole vocabulary
+// per tile.
 RBP_LOGITS_KERNEL void dhidden_kernel(const uint16_t* __restrict__ W,
                                       const uint16_t* __restrict__ Gt, int64_t ldGt, int64_t Tn,
                                       int32_t d, int32_t V, const float* __restrict__ cs,
                                       float* __restrict__ dH, int64_t tiles_m, int64_t tiles_n,
-                                      int32_t vid_base, int32_t n_vid, int32_t split_steps,
-                                      float* __restrict__ part, int part_full) {
+                                      int32_t n_vid) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
   const int64_t T256 = (Tn + 255) / 256 * 256;
   const Operand A{W, d, d, V};          // (m = hidden unit, k = vocab): W[v][m]
   const Operand B{Gt, ldGt, T256, V};   // (n = token, k = vocab): Gt[v][t]
   auto tile_of = [&](int32_t vid) {
     int32_t tm, tn;
-    const int32_t half = split_steps > 0 ? (vid & 1) : 0;
-    const int32_t tv = vid_base + (split_steps > 0 ? vid >> 1 : vid);
-    map_tile(tv, (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
-    // both halves span split_steps steps (uniform step count); columns past
-    // V read as zero
-    const int32_t kb = half * split_steps * 64;
-    return Tile{tm * 256, tn * 256, kb, split_steps > 0 ? kb + split_steps * 64 : V};
+    raster_tile(xcd_order((uint32_t)vid, (uint32_t)n_vid), (int32_t)tiles_m, (int32_t)tiles_n,
+                kGroupGrad, tm, tn);
+    return Tile{tm * 256, tn * 256, 0, V};
   };
   auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) {
-    const Tile tile = tile_of(vid);
-    const bool to_part = split_steps > 0 && (vid & 1);
-    float* blk = part + (int64_t)(vid >> 1) * 65536;
-#pragma unroll
-    for (int ni = 0; ni < GL::NI; ++ni) {
-      const int64_t t = tile.n0 + GL::col(ni);
-      if (t >= Tn) continue;
-      const float c = cs != nullptr ? cs[t] : 1.0f;  // per-token scale of the single pass
-#pragma unroll
-      for (int mi = 0; mi < GL::MI; ++mi)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int64_t m = tile.m0 + GL::row(mi, rg * 4);
-          const float4 val = make_float4(c * acc[mi][ni][rg * 4 + 0], c * acc[mi][ni][rg * 4 + 1],
-                                         c * acc[mi][ni][rg * 4 + 2], c * acc[mi][ni][rg * 4 + 3]);
-          if (to_part && !part_full)
-            *reinterpret_cast<float4*>(blk + GL::col(ni) * 256 + GL::row(mi, rg * 4)) = val;
-          else if (m < d)
-            *reinterpret_cast<float4*>((to_part ? part : dH) + t * d + m) = val;
-        }
-    }
+    store_dh(tile_of(vid), acc, Tn, d, cs, dH);
   };
   tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, n_vid, smem, tile_of, epi);
 }
 
-// The last round of a dhidden launch when it is more than half full: its r
-// tiles (virtual tiles vid_base .. vid_base + r - 1) are cut into s pieces
-// of `steps` K steps each and run by one round of P = gridDim.x workgroups,
-// with s - 1 = ceil(r / (P - r)).  Workgroup c < r runs pieces 0 .. s - 2 of
-// tile c back to back, its accumulators carried from piece to piece, and
-// writes dH; workgroup r + e runs the last piece of tiles e, e + (P - r),
-// e + 2 (P - r), ... below r and writes each into part[i] (256 x 256 fp32,
-// [t][m]), which part_add_dh_kernel adds afterwards.  No workgroup runs more
-// than s - 1 pieces, so the round takes (s - 1) / s of a whole-vocabulary
-// tile instead of leaving P - r compute units idle for all of it.  Virtual
-// block vid = c + j P (j < s - 1) is workgroup c's j-th piece; the s r
-// pieces are exactly the blocks below s r.
+// The last round of a dhidden launch: its r tiles (raster positions base ..
+// base + r - 1), fewer than there are compute units, cut along the vocabulary
+// so that every unit has work (Pieces, below).  A workgroup's accumulators
+// are carried from piece to piece of a tile; a tile's first share goes to dH
+// and the others to their slots of `part`, arrays laid out like dH that
+// part_add_dh_kernel adds in order.
 RBP_LOGITS_KERNEL void dhidden_pieces_kernel(const uint16_t* __restrict__ W,
                                              const uint16_t* __restrict__ Gt, int64_t ldGt,
                                              int64_t Tn, int32_t d, int32_t V,
                                              const float* __restrict__ cs,
                                              float* __restrict__ dH, int64_t tiles_m,
-                                             int64_t tiles_n, int32_t vid_base, int32_t r,
-                                             int32_t s, int32_t steps,
-                                             float* __restrict__ part) {
+                                             int64_t tiles_n, int32_t base, Pieces pc,
+                                             float* __restrict__ part, int64_t slot_floats) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
   const int64_t T256 = (Tn + 255) / 256 * 256;
   const Operand A{W, d, d, V};          // (m = hidden unit, k = vocab): W[v][m]
   const Operand B{Gt, ldGt, T256, V};   // (n = token, k = vocab): Gt[v][t]
-  const int32_t P = (int32_t)gridDim.x;
-  // tile i (of the round) and piece j of virtual block vid
-  auto piece = [&](int32_t vid, int32_t& i, int32_t& j) {
-    const int32_t c = vid % P, jj = vid / P;
-    if (c < r) {
-      i = c;
-      j = jj;
-    } else {
-      i = jj * (P - r) + (c - r);
-      j = s - 1;
-    }
-  };
   auto tile_of = [&](int32_t vid) {
-    int32_t i, j, tm, tn;
-    piece(vid, i, j);
-    map_tile(vid_base + i, (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
-    // every piece spans `steps` steps; columns past V read as zero
-    const int32_t kb = j * steps * 64;
-    return Tile{tm * 256, tn * 256, kb, kb + steps * 64};
+    const Pieces::At a = pc.at(vid, (int32_t)gridDim.x);
+    int32_t tm, tn;
+    raster_tile((uint32_t)(base + a.tile), (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm,
+                tn);
+    // every piece spans `steps` steps; rows past V read as zero
+    const int32_t kb = a.piece * pc.steps * 64;
+    return Tile{tm * 256, tn * 256, kb, kb + pc.steps * 64};
   };
   auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) -> bool {
-    int32_t i, j;
-    piece(vid, i, j);
-    if (j < s - 2) return false;  // the tile's next piece follows on this workgroup
-    // dhidden_kernel's stores: c_t-scaled, the last piece into its block
-    const Tile tile = tile_of(vid);
-    const bool to_part = j == s - 1;
-    float* blk = part + (int64_t)i * 65536;
-#pragma unroll
-    for (int ni = 0; ni < GL::NI; ++ni) {
-      const int64_t t = tile.n0 + GL::col(ni);
-      if (t >= Tn) continue;
-      const float c = cs != nullptr ? cs[t] : 1.0f;
-#pragma unroll
-      for (int mi = 0; mi < GL::MI; ++mi)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int64_t m = tile.m0 + GL::row(mi, rg * 4);
-          const float4 val = make_float4(c * acc[mi][ni][rg * 4 + 0], c * acc[mi][ni][rg * 4 + 1],
-                                         c * acc[mi][ni][rg * 4 + 2], c * acc[mi][ni][rg * 4 + 3]);
-          if (to_part)
-            *reinterpret_cast<float4*>(blk + GL::col(ni) * 256 + GL::row(mi, rg * 4)) = val;
-          else if (m < d)
-            *reinterpret_cast<float4*>(dH + t * d + m) = val;
-        }
-    }
+    const Pieces::At a = pc.at(vid, (int32_t)gridDim.x);
+    if (!a.flush) return false;  // the tile's next piece follows on this workgroup
+    if (a.piece < pc.p)
+      store_dh(tile_of(vid), acc, Tn, d, cs, a.slot == 0 ? dH : part + (a.slot - 1) * slot_floats);
     return true;
   };
-  tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, s * r, smem, tile_of, epi);
+  tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, pc.q * (int32_t)gridDim.x, smem, tile_of,
+                                               epi);
 }
 
-// dH += part[i] over the tiles vid_base + i of a split dhidden launch; one
-// block per (tile, 16 tokens).
+// dH += its tiles' slots of `part`, in slot order; one block per (tile, 4
+// tokens), 16 bytes per lane.
 __global__ void __launch_bounds__(256) part_add_dh_kernel(float* __restrict__ dH,
                                                           const float* __restrict__ part,
-                                                          int32_t vid_base, int64_t tiles_m,
+                                                          int64_t slot_floats, int32_t base,
+                                                          Pieces pc, int64_t tiles_m,
                                                           int64_t tiles_n, int32_t d,
                                                           int64_t Tn) {
   const int32_t i = (int32_t)blockIdx.x;
   int32_t tm, tn;
-  map_tile(vid_base + i, (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
-  const int32_t tl = (int32_t)blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int64_t t = (int64_t)tn * 256 + tl;
-  if (t >= Tn) return;
-  const float* src = part + (int64_t)i * 65536 + (int64_t)tl * 256;
-  for (int32_t ml = (threadIdx.x & 15) * 4; ml < 256; ml += 64) {
-    const int32_t m = tm * 256 + ml;
-    if (m >= d) break;  // d % 8 == 0: a float4 never straddles the edge
-    float4* dst = reinterpret_cast<float4*>(dH + t * d + m);
-    const float4 p = *reinterpret_cast<const float4*>(src + ml);
-    float4 o = *dst;
+  raster_tile((uint32_t)(base + i), (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
+  const int64_t t = (int64_t)tn * 256 + blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int32_t m = tm * 256 + (threadIdx.x & 63) * 4;
+  if (t >= Tn || m >= d) return;  // d % 8 == 0: a float4 never straddles the edge
+  float4* dst = reinterpret_cast<float4*>(dH + t * d + m);
+  float4 o = *dst;
+  const int32_t n = pc.slots_of(i);
+#pragma unroll 4
+  for (int32_t k = 0; k < n; ++k) {
+    const float4 p = *reinterpret_cast<const float4*>(part + k * slot_floats + t * d + m);
     o.x += p.x;
     o.y += p.y;
     o.z += p.z;
     o.w += p.w;
-    *dst = o;
   }
+  *dst = o;
 }
 
 // Backward step 3: dW[v][m] (+)= sum_t H[t][m] dz[t][v], with A = H read
@@ -395,21 +357,6 @@ __global__ void __launch_bounds__(256) part_add_kernel(float* __restrict__ dW,
   }
 }
 
-// a[i] += b[i] (n % 4 == 0), fixed order per element.
-__global__ void __launch_bounds__(256) add_f32_kernel(float* __restrict__ a,
-                                                      const float* __restrict__ b, int64_t n4) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4;
-       i += (int64_t)gridDim.x * 256) {
-    float4 x = reinterpret_cast<float4*>(a)[i];
-    const float4 y = reinterpret_cast<const float4*>(b)[i];
-    x.x += y.x;
-    x.y += y.y;
-    x.z += y.z;
-    x.w += y.w;
-    reinterpret_cast<float4*>(a)[i] = x;
-  }
-}
-
 __global__ void __launch_bounds__(256) fill_zero_kernel(float* __restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
     p[i] = 0.0f;
@@ -417,11 +364,12 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(float* __restrict__ p, i
 
 
 
-// Backward workspace carving: dz^T [Vp][T256] bf16, then the second dhidden
-// K half [T256][d] fp32.
+// Backward workspace carving: dz^T [Vp][T256] bf16, then scratch for partial
+// sums, [T256][d] fp32 at least.
 struct BwdWs {
   uint16_t* Gt;
-  float* dh_half;
+  float* scratch;
+  size_t scratch_at;  // byte offset of scratch
   size_t bytes;
 };
 BwdWs carve_bwd(void* base, int64_t Tc, int32_t d, int32_t V) {
@@ -429,14 +377,19 @@ BwdWs carve_bwd(void* base, int64_t Tc, int32_t d, int32_t V) {
   const int64_t T256 = round256(Tc < 1 ? 1 : Tc), Vp = round256(V);
   BwdWs w;
   w.Gt = c.take<uint16_t>((size_t)Vp * (size_t)T256);
-  w.dh_half = c.take<float>((size_t)T256 * (size_t)d);
+  w.scratch = c.take<float>((size_t)T256 * (size_t)d);
+  w.scratch_at = c.used - sizeof(float) * (size_t)T256 * (size_t)d;
   w.bytes = rbp::align_up(c.used, 256);
   return w;
 }
 }  // namespace
 
 size_t rbp::logprob_bwd_ws(int64_t Tc, int32_t d, int32_t V) {
-  return carve_bwd(nullptr, Tc, d < 1 ? 1 : d, V).bytes;
+  const int64_t T256 = round256(Tc < 1 ? 1 : Tc);
+  const int32_t dd = d < 1 ? 1 : d;
+  const BwdWs w = carve_bwd(nullptr, T256, dd, V);
+  return w.bytes + dhidden_extra(T256, dd, V, w.bytes - w.scratch_at, w.bytes,
+                                 carve_bwd(nullptr, T256 + 256, dd, V).bytes);
 }
 
 void rbp::launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, int64_t Tn,
@@ -466,68 +419,47 @@ void rbp::launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, i
 }
 
 void rbp::launch_dhidden(const uint16_t* W, const uint16_t* Gt, int64_t ldGt, int64_t Tn,
-                         int32_t d, int32_t V, float* dhidden_c, float* dh_half, hipStream_t s,
-                         const float* cs) {
-  const int n_cu = device_cus();
+                         int32_t d, int32_t V, float* dhidden_c, hipStream_t s, float* scratch,
+                         int64_t scratch_floats, const float* cs) {
   const int64_t tiles_d = rbp::ceil_div(d, 256), tiles_t = rbp::ceil_div(Tn, 256);
   const int64_t tiles = tiles_d * tiles_t;
-  const int64_t G = rbp::gemm::stream_grid(int64_t(1) << 30, n_cu);  // one round
-  const int64_t nk = rbp::ceil_div(V, 64);
-  const int32_t half_steps = (int32_t)((nk + 1) / 2);
-  // The whole vocabulary per tile; when the tiles fill at most half a round,
-  // all of them in two K halves (the second halves into dh_half, laid out
-  // like dhidden, then summed); otherwise a last round filled to at most
-  // half goes to a second launch as two K halves per tile (dh_half holds one
-  // 256 x 256 block per tile).
-  if (nk >= 8 && 2 * tiles <= G) {
-    hipLaunchKernelGGL(dhidden_kernel, dim3(rbp::gemm::stream_grid(2 * tiles, n_cu)),
-                       dim3(GL::kThreads), 0, s, W, Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d,
-                       tiles_t, 0, (int32_t)(2 * tiles), half_steps, dh_half, 1);
-    const int64_t n4 = Tn * d / 4;
-    int64_t blocks = rbp::ceil_div(n4, 256);
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(add_f32_kernel, dim3(blocks), dim3(256), 0, s, dhidden_c, dh_half, n4);
-    return;
-  }
+  const int64_t G = rbp::gemm::stream_grid(int64_t(1) << 30, device_cus());  // one round
+  const int64_t slot_floats = Tn * d;
   const int64_t r = tiles % G;
-  const bool fits = r * 65536 <= ldGt * (int64_t)d;  // one scratch block per tile of the round
-  const int64_t rem = (nk >= 8 && tiles > G && r > 0 && 2 * r <= G && fits) ? r : 0;
-  // A last round more than half full: its tiles cut into pieces of the K
-  // range, s - 1 = ceil(r / (G - r)) pieces per workgroup
-  // (dhidden_pieces_kernel), when a piece keeps at least 8 steps and the
-  // last piece is not empty.
-  int64_t pieces = 0, piece_steps = 0;
-  if (2 * r > G && fits) {
-    const int64_t ps = 1 + rbp::ceil_div(r, G - r), st = rbp::ceil_div(nk, ps);
-    if (ps <= 16 && st >= 8 && (ps - 1) * st < nk) {
-      pieces = ps;
-      piece_steps = st;
-    }
-  }
-  const int64_t n_main = tiles - (rem > 0 ? rem : (pieces > 0 ? r : 0));
+  const Pieces pc = plan_pieces(r, rbp::ceil_div(V, 64), G, scratch_floats / slot_floats);
+  const int64_t n_main = pc.p > 1 ? tiles - r : tiles;
   if (n_main > 0)
-    hipLaunchKernelGGL(dhidden_kernel, dim3(rbp::gemm::stream_grid(n_main, n_cu)),
+    hipLaunchKernelGGL(dhidden_kernel, dim3(rbp::gemm::stream_grid(n_main, device_cus())),
                        dim3(GL::kThreads), 0, s, W, Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d,
-                       tiles_t, 0, (int32_t)n_main, 0, (float*)nullptr, 0);
-  if (rem > 0) {
-    hipLaunchKernelGGL(dhidden_kernel, dim3(rbp::gemm::stream_grid(2 * rem, n_cu)),
+                       tiles_t, (int32_t)n_main);
+  if (pc.p > 1) {
+    hipLaunchKernelGGL(dhidden_pieces_kernel, dim3((unsigned)pc.workgroups()),
                        dim3(GL::kThreads), 0, s, W, Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d,
-                       tiles_t, (int32_t)n_main, (int32_t)(2 * rem), half_steps, dh_half, 0);
-    hipLaunchKernelGGL(part_add_dh_kernel, dim3((unsigned)rem, 16), dim3(256), 0, s, dhidden_c,
-                       dh_half, (int32_t)n_main, tiles_d, tiles_t, d, Tn);
-  } else if (pieces > 0) {
-    // grid G exactly: workgroup c's pieces are the virtual blocks c + j G
-    hipLaunchKernelGGL(dhidden_pieces_kernel, dim3((unsigned)G), dim3(GL::kThreads), 0, s, W,
-                       Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d, tiles_t, (int32_t)n_main,
-                       (int32_t)r, (int32_t)pieces, (int32_t)piece_steps, dh_half);
-    hipLaunchKernelGGL(part_add_dh_kernel, dim3((unsigned)r, 16), dim3(256), 0, s, dhidden_c,
-                       dh_half, (int32_t)n_main, tiles_d, tiles_t, d, Tn);
+                       tiles_t, (int32_t)n_main, pc, scratch, slot_floats);
+    hipLaunchKernelGGL(part_add_dh_kernel, dim3((unsigned)r, 64), dim3(256), 0, s, dhidden_c,
+                       scratch, slot_floats, (int32_t)n_main, pc, tiles_d, tiles_t, d, Tn);
   }
+}
+
+size_t rbp::dhidden_extra(int64_t T256, int32_t d, int32_t V, size_t free_bytes, size_t base,
+                          size_t next) {
+  // sized for the 256 compute units of an MI355X, 64 MiB of partial sums at
+  // most (one 256 x 256 block per unit)
+  constexpr int64_t kUnits = 256;
+  const int64_t slot = T256 * (int64_t)d * 4;
+  const int64_t tiles = rbp::ceil_div(d, 256) * (T256 / 256);
+  const Pieces pc = plan_pieces(tiles % kUnits, rbp::ceil_div(V, 64), kUnits,
+                                (kUnits << 18) / slot);
+  const size_t want = (size_t)(pc.slots() * slot);
+  if (want <= free_bytes) return 0;
+  const size_t extra = align_up(want - free_bytes, 256);
+  return base + extra < next ? extra : next - base - 256;
 }
 
 void rbp::launch_grad_products(const uint16_t* Hc, const uint16_t* W, const uint16_t* Gt,
                                int64_t ldGt, int64_t Tn, int32_t d, int32_t V, float* dhidden_c,
-                               float* dh_half, float* dW, int accumulate, hipStream_t s) {
+                               float* dW, int accumulate, hipStream_t s, float* scratch,
+                               int64_t scratch_floats) {
   if (Tn == 0) {
     if (!accumulate) {
       const int64_t n = (int64_t)V * d;
@@ -537,10 +469,10 @@ void rbp::launch_grad_products(const uint16_t* Hc, const uint16_t* W, const uint
     }
     return;
   }
-  launch_dhidden(W, Gt, ldGt, Tn, d, V, dhidden_c, dh_half, s);
-  // dh_half is free again once dhidden's sum has read it
-  launch_dweight(Hc, Gt, ldGt, Tn, d, V, dW, accumulate, 0, round256(V) / 256, s, dh_half,
-                 ldGt * (int64_t)d);
+  launch_dhidden(W, Gt, ldGt, Tn, d, V, dhidden_c, s, scratch, scratch_floats);
+  // the scratch is free again once dhidden's sum has read it
+  launch_dweight(Hc, Gt, ldGt, Tn, d, V, dW, accumulate, 0, round256(V) / 256, s, scratch,
+                 scratch_floats);
 }
 
 extern "C" int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
@@ -557,8 +489,8 @@ extern "C" int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
               "policy_logprob_bwd: null pointer");
   hipStream_t s = rbp::as_stream(stream);
   if (T == 0) {
-    rbp::launch_grad_products(nullptr, W, nullptr, 0, 0, d, V, nullptr, nullptr, dW,
-                              accumulate_dW, s);
+    rbp::launch_grad_products(nullptr, W, nullptr, 0, 0, d, V, nullptr, dW, accumulate_dW, s,
+                              nullptr, 0);
     RBP_CHECK_LAUNCH("policy_logprob_bwd");
     return RBP_OK;
   }
@@ -568,17 +500,17 @@ extern "C" int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
     // chunks of at most 2^21 tokens keep every per-tile byte range of dz^T
     // (256 rows x Tc x 2 bytes) inside a 32-bit buffer offset
     int64_t lo = 256, hi = round256(T) < (int64_t(1) << 21) ? round256(T) : (int64_t(1) << 21);
-    if (rbp::logprob_bwd_ws(lo, d, V) <= ws_bytes) {
+    if (carve_bwd(nullptr, lo, d, V).bytes <= ws_bytes) {
       while (lo < hi) {  // largest multiple of 256 in [lo, hi] that fits
         const int64_t mid = (lo + hi + 256) / 512 * 256;
-        if (rbp::logprob_bwd_ws(mid, d, V) <= ws_bytes) lo = mid; else hi = mid - 256;
+        if (carve_bwd(nullptr, mid, d, V).bytes <= ws_bytes) lo = mid; else hi = mid - 256;
       }
       Tc = lo;
     }
   }
   RBP_REQUIRE(Tc >= 256, RBP_EWORKSPACE,
               "policy_logprob_bwd: workspace of %zu bytes holds no 256-token chunk (needs %zu)",
-              ws_bytes, rbp::logprob_bwd_ws(256, d, V));
+              ws_bytes, carve_bwd(nullptr, 256, d, V).bytes);
   const BwdWs w = carve_bwd(ws, Tc, d, V);
   const int64_t tiles_v = round256(V) / 256;
   const int n_cu = device_cus();
@@ -593,8 +525,9 @@ extern "C" int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
     hipLaunchKernelGGL(target_dz_kernel, dim3(rbp::ceil_div(Tn, 4)), dim3(256), 0, s, Hc, W,
                        tokens + t0, seq_of_token ? seq_of_token + t0 : nullptr, lse + t0,
                        dlogp + t0, Tn, d, V, w.Gt, Tc);
-    rbp::launch_grad_products(Hc, W, w.Gt, Tc, Tn, d, V, dhidden + t0 * d, w.dh_half, dW,
-                              (accumulate_dW || t0 > 0) ? 1 : 0, s);
+    rbp::launch_grad_products(Hc, W, w.Gt, Tc, Tn, d, V, dhidden + t0 * d, dW,
+                              (accumulate_dW || t0 > 0) ? 1 : 0, s, w.scratch,
+                              (int64_t)((ws_bytes - w.scratch_at) / sizeof(float)));
   }
   RBP_CHECK_LAUNCH("policy_logprob_bwd");
   return RBP_OK;

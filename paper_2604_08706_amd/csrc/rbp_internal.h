@@ -44,21 +44,29 @@ size_t note_use_ws(int64_t capacity);
 
 // The two products of the log-prob backward for one chunk of Tn tokens, from
 // dz^T (bf16 [round256(V)][ldGt], columns Tn..round256(Tn) zero):
-// dhidden_c [Tn][d] overwritten (dh_half: fp32 [ldGt][d] scratch), dW [V][d]
-// overwritten or accumulated.  Tn = 0 only zeroes dW (unless accumulating).
+// dhidden_c [Tn][d] overwritten, dW [V][d] overwritten or accumulated.
+// scratch (fp32, scratch_floats) holds the partial sums of last rounds cut
+// along K.  Tn = 0 only zeroes dW (unless accumulating).
 void launch_grad_products(const uint16_t* Hc, const uint16_t* W, const uint16_t* Gt,
                           int64_t ldGt, int64_t Tn, int32_t d, int32_t V, float* dhidden_c,
-                          float* dh_half, float* dW, int accumulate, hipStream_t s);
+                          float* dW, int accumulate, hipStream_t s, float* scratch,
+                          int64_t scratch_floats);
 // Its two parts: dW rows of the vocabulary tiles [tn_begin, tn_end) (256 rows
-// each), and dhidden (with its split-K sum; row t scaled by cs[t] when cs is
-// given).
-// scratch (fp32, scratch_floats) may hold partial sums of dW's last round.
+// each), and dhidden (row t scaled by cs[t] when cs is given).
 void launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, int64_t Tn, int32_t d,
                     int32_t V, float* dW, int accumulate, int64_t tn_begin, int64_t tn_end,
                     hipStream_t s, float* scratch = nullptr, int64_t scratch_floats = 0);
 void launch_dhidden(const uint16_t* W, const uint16_t* Gt, int64_t ldGt, int64_t Tn, int32_t d,
-                    int32_t V, float* dhidden_c, float* dh_half, hipStream_t s,
-                    const float* cs = nullptr);
+                    int32_t V, float* dhidden_c, hipStream_t s, float* scratch,
+                    int64_t scratch_floats, const float* cs = nullptr);
+
+// Workspace bytes to ask for beyond `base`, the least a chunk of T256 tokens
+// (a multiple of 256) runs with and whose last `free_bytes` are scratch by
+// the time dhidden runs: what its cut of a partly filled round can use.
+// Always less than one more 256-token granule (`next` = the base of T256 +
+// 256 tokens), so the chunk that fits a workspace of this size stays T256.
+size_t dhidden_extra(int64_t T256, int32_t d, int32_t V, size_t free_bytes, size_t base,
+                     size_t next);
 
 }  // namespace rbp
 
