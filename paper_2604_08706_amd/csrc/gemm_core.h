@@ -76,6 +76,18 @@ struct Grid {
   static __device__ __forceinline__ int col(int ni) {
     return wn() * (256 / WN) + ni * 32 + (threadIdx.x & 31);
   }
+  // the same of tile (mi, ni) with the operands swapped (gemm_dma.h, kOutN):
+  // lane l holds m = l % 32 and, as accumulator r, n = 8 (r / 4) + 4 (l / 32) +
+  // r % 4, so that 32 lanes cover 128 contiguous bytes of an fp32 row of m.
+  // Split into a wave-uniform and a per-lane part.
+  static __device__ __forceinline__ int out_m(int mi) {
+    return __builtin_amdgcn_readfirstlane(wm()) * (256 / WM) + mi * 32;
+  }
+  static __device__ __forceinline__ int out_n(int ni, int r) {
+    return __builtin_amdgcn_readfirstlane(wn()) * (256 / WN) + ni * 32 + (r >> 2) * 8 + (r & 3);
+  }
+  static __device__ __forceinline__ int lane_m() { return threadIdx.x & 31; }
+  static __device__ __forceinline__ int lane_n() { return ((threadIdx.x & 63) >> 5) * 4; }
   // column of tile ni when B is loaded with paired rows (gemm_dma.h,
   // kKPaired): lane l of tiles 0 and 1 holds columns 2 (l % 32) and
   // 2 (l % 32) + 1 of the wave's 64
@@ -95,6 +107,14 @@ __host__ __device__ __forceinline__ uint32_t xcd_order(uint32_t bid, uint32_t nb
   const uint32_t xcd = bid & 7u, local = bid >> 3;
   const uint32_t per = nblk >> 3, rem = nblk & 7u;
   return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+}
+
+// The block that xcd_order puts at position L.
+__host__ __device__ __forceinline__ uint32_t xcd_block(uint32_t L, uint32_t nblk) {
+  const uint32_t per = nblk >> 3, rem = nblk & 7u;
+  if (L < rem * (per + 1)) return (L % (per + 1)) * 8u + L / (per + 1);
+  const uint32_t k = L - rem * (per + 1);  // per > 0 here
+  return (k % per) * 8u + rem + k / per;
 }
 
 // Position -> (tile_m, tile_n): groups of `group_m` M-tiles per N-tile, so

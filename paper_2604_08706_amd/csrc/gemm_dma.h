@@ -85,20 +85,32 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <class G>
+// One MFMA of the tile (mi, ni).  kOut names the direction in which a lane
+// owns consecutive outputs: kOutM -- runs of four m of one n (Grid::row, col);
+// kOutN -- runs of four n of one m (Grid::out_m, out_n), the operands swapped.
+constexpr int kOutM = 0, kOutN = 1;
+template <int kOut>
+__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  if constexpr (kOut == kOutM)
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
+}
+
+template <class G, int kOut>
 __device__ __forceinline__ void mfma_tiles(const bf16x8 (&a)[G::MI], const bf16x8 (&b)[G::NI],
                                            f32x16 (&acc)[G::MI][G::NI]) {
 #pragma unroll
   for (int mi = 0; mi < G::MI; ++mi)
 #pragma unroll
     for (int ni = 0; ni < G::NI; ++ni)
-      acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+      acc[mi][ni] = mfma32<kOut>(a[mi], b[ni], acc[mi][ni]);
 }
 
 // MFMAs of one K slice with `nload` loads spread evenly between them: a
 // burst of loads would stall this wave's MFMA issue while the CU's address
 // unit accepts them.  load(l) issues load l (or nothing).
-template <class G, class LoadFn>
+template <class G, int kOut, class LoadFn>
 __device__ __forceinline__ void mfma_tiles_interleaved(const bf16x8 (&a)[G::MI],
                                                        const bf16x8 (&b)[G::NI],
                                                        f32x16 (&acc)[G::MI][G::NI], int nload,
@@ -108,7 +120,7 @@ __device__ __forceinline__ void mfma_tiles_interleaved(const bf16x8 (&a)[G::MI],
 #pragma unroll
   for (int q = 0; q < M; ++q) {
     const int mi = q / G::NI, ni = q % G::NI;
-    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+    acc[mi][ni] = mfma32<kOut>(a[mi], b[ni], acc[mi][ni]);
     if ((q + 1) % every == 0 && (q + 1) / every <= nload) {
       RBP_FENCE();
       load((q + 1) / every - 1);
@@ -344,6 +356,7 @@ struct SideLoad<G, kMNMajor> {
 // output tile); one that returns void always starts the next block from
 // zero.  kLA / kLB select the layouts of A / B (kKMajor, kMNMajor,
 // kKPaired); K-major needs k_extent % 8 == 0, MN-major mn_extent % 8 == 0.
+// kOut chooses which outputs a lane holds (mfma32 above).
 // kDeep names the operand with three buffers (1: A, 2: B); smem holds
 // kLdsBytes: the deep operand's buffers, then the other's two.
 //
@@ -365,7 +378,7 @@ struct SideLoad<G, kMNMajor> {
 //   of it is a buffer) and may contain barriers.
 // The load cursor runs two steps ahead of the MFMAs and recomputes its view
 // whenever it enters a new tile.
-template <class G, int kLA, int kLB, int kDeep, class TileFn, class EpiFn>
+template <class G, int kLA, int kLB, int kDeep, int kOut = kOutM, class TileFn, class EpiFn>
 __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, int32_t n_vid,
                                             uint8_t* smem, TileFn&& tile_of, EpiFn&& epi) {
   static_assert(kDeep == 1 || kDeep == 2, "deep operand: 1 = A, 2 = B");
@@ -451,7 +464,7 @@ __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, 
     const uint32_t na = kDeep == 1 ? d1 : (o0 ^ 1u), nb = kDeep == 2 ? d1 : (o0 ^ 1u);
     read(ca, cb, 1, a1, b1);
     RBP_FENCE();
-    mfma_tiles_interleaved<G>(a0, b0, acc, L, [&](int l) {
+    mfma_tiles_interleaved<G, kOut>(a0, b0, acc, L, [&](int l) {
       if constexpr (kDeep == 1)
         issue_a(d2, l);
       else
@@ -460,11 +473,11 @@ __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, 
     RBP_FENCE();
     read(ca, cb, 2, a0, b0);
     RBP_FENCE();
-    mfma_tiles<G>(a1, b1, acc);
+    mfma_tiles<G, kOut>(a1, b1, acc);
     RBP_FENCE();
     read(ca, cb, 3, a1, b1);
     RBP_FENCE();
-    mfma_tiles<G>(a0, b0, acc);
+    mfma_tiles<G, kOut>(a0, b0, acc);
     RBP_FENCE();
     // step g + 1 landed (only the deep operand's step g + 2 loads are
     // outstanding); this wave's reads of step g done
@@ -473,7 +486,7 @@ __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, 
     // unconditional (after the last step it reads a stale buffer)
     read(na, nb, 0, a0, b0);
     RBP_FENCE();
-    mfma_tiles_interleaved<G>(a1, b1, acc, L, [&](int l) {
+    mfma_tiles_interleaved<G, kOut>(a1, b1, acc, L, [&](int l) {
       if constexpr (kDeep == 1)
         issue_b(o0, l);
       else

@@ -26,14 +26,19 @@ using rbp::gemm::kLdsBytes;
 using rbp::gemm::Tile;
 using rbp::gemm::tile_stream;
 using rbp::gemm::map_tile;
-using rbp::gemm::raster_tile;
-using rbp::gemm::xcd_order;
+using rbp::gemm::xcd_block;
 using rbp::gemm::Pieces;
 using rbp::gemm::plan_pieces;
 using rbp::gemm::Operand;
 using rbp::gemm::kKMajor;
 using rbp::gemm::kMNMajor;
 using rbp::gemm::kKPaired;
+using rbp::gemm::kOutN;
+
+// Rows of a dW tile read, then stored back, at a time (4 values per lane each).
+constexpr int kDwRows = 8;
+// Longest dW row whose 256-row tile a 32-bit buffer offset spans.
+constexpr int32_t kMaxBufferD = 2000000;
 
 // Backward step 1: recompute the tile and write dz = dlogp (onehot - p) as
 // bf16, vocabulary-major (Gt[v][t], the layout both later products read).
@@ -139,8 +144,8 @@ __device__ __forceinline__ void store_dh(const Tile& tile, const f32x16 (&acc)[G
   }
 }
 
-// Whole rounds: the first n_vid tiles in raster order, the whole vocabulary
-// per tile.
+// Whole rounds: blocks 0 .. n_vid - 1 of the launch over every tile, the whole
+// vocabulary per tile.
 RBP_LOGITS_KERNEL void dhidden_kernel(const uint16_t* __restrict__ W,
                                       const uint16_t* __restrict__ Gt, int64_t ldGt, int64_t Tn,
                                       int32_t d, int32_t V, const float* __restrict__ cs,
@@ -152,8 +157,7 @@ RBP_LOGITS_KERNEL void dhidden_kernel(const uint16_t* __restrict__ W,
   const Operand B{Gt, ldGt, T256, V};   // (n = token, k = vocab): Gt[v][t]
   auto tile_of = [&](int32_t vid) {
     int32_t tm, tn;
-    raster_tile(xcd_order((uint32_t)vid, (uint32_t)n_vid), (int32_t)tiles_m, (int32_t)tiles_n,
-                kGroupGrad, tm, tn);
+    map_tile(vid, (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
     return Tile{tm * 256, tn * 256, 0, V};
   };
   auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) {
@@ -162,8 +166,17 @@ RBP_LOGITS_KERNEL void dhidden_kernel(const uint16_t* __restrict__ W,
   tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, n_vid, smem, tile_of, epi);
 }
 
-// The last round of a dhidden launch: its r tiles (raster positions base ..
-// base + r - 1), fewer than there are compute units, cut along the vocabulary
+// Tile i of the r tiles of a last round, blocks base .. base + r - 1 of the
+// launch over every tile: XCD by XCD, so that neighbouring i are neighbours.
+__device__ __forceinline__ void last_round_tile(int32_t i, int32_t r, int32_t base,
+                                                int64_t tiles_m, int64_t tiles_n, int32_t& tm,
+                                                int32_t& tn) {
+  map_tile(base + (int32_t)xcd_block((uint32_t)i, (uint32_t)r), (int32_t)tiles_m,
+           (int32_t)tiles_n, kGroupGrad, tm, tn);
+}
+
+// The last round of a dhidden launch: its r tiles (blocks base .. base + r - 1
+// of the launch over every tile), fewer than there are compute units, cut along the vocabulary
 // so that every unit has work (Pieces, below).  A workgroup's accumulators
 // are carried from piece to piece of a tile; a tile's first share goes to dH
 // and the others to their slots of `part`, arrays laid out like dH that
@@ -182,8 +195,7 @@ RBP_LOGITS_KERNEL void dhidden_pieces_kernel(const uint16_t* __restrict__ W,
   auto tile_of = [&](int32_t vid) {
     const Pieces::At a = pc.at(vid, (int32_t)gridDim.x);
     int32_t tm, tn;
-    raster_tile((uint32_t)(base + a.tile), (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm,
-                tn);
+    last_round_tile(a.tile, pc.r, base, tiles_m, tiles_n, tm, tn);
     // every piece spans `steps` steps; rows past V read as zero
     const int32_t kb = a.piece * pc.steps * 64;
     return Tile{tm * 256, tn * 256, kb, kb + pc.steps * 64};
@@ -209,7 +221,7 @@ __global__ void __launch_bounds__(256) part_add_dh_kernel(float* __restrict__ dH
                                                           int64_t Tn) {
   const int32_t i = (int32_t)blockIdx.x;
   int32_t tm, tn;
-  raster_tile((uint32_t)(base + i), (int32_t)tiles_m, (int32_t)tiles_n, kGroupGrad, tm, tn);
+  last_round_tile(i, pc.r, base, tiles_m, tiles_n, tm, tn);
   const int64_t t = (int64_t)tn * 256 + blockIdx.y * 4 + (threadIdx.x >> 6);
   const int32_t m = tm * 256 + (threadIdx.x & 63) * 4;
   if (t >= Tn || m >= d) return;  // d % 8 == 0: a float4 never straddles the edge
@@ -225,6 +237,67 @@ __global__ void __launch_bounds__(256) part_add_dh_kernel(float* __restrict__ dH
     o.w += p.w;
   }
   *dst = o;
+}
+
+// Stores one finished dW tile, adding the previous values when `accumulate`.
+//
+// A lane holds one column m (kOutN), so 32 lanes cover one 128-byte line of a
+// row and an instruction two whole lines.  With runs of four m per lane
+// (16-byte accesses, 32 rows of 32 bytes each) the address unit took every
+// line four times, and a tile's read-modify-write of 512 KB cost about 30 us
+// beside its K loop (1.5 us a step): dW at d = 3584, V = 152064 took 2.05 ms
+// for 1301 tokens, 1.66 ms this way, and 14.50 / 14.45 ms for 16384; without
+// accumulation into d = 1536, V = 151936, 4096 tokens 1.12 -> 0.96 ms.
+//
+// Rows go through a buffer resource over the tile: one offset per lane and
+// 32-column block, columns past d pointing beyond the range (loads read 0,
+// stores are dropped), and the row as the scalar offset -- or, in the last
+// vocabulary tile (kTail), inside the lane's offset, which the range check
+// then covers, so that rows past V are dropped too.
+template <bool kTail>
+__device__ __forceinline__ void dw_rows(const f32x16 (&acc)[GL::MI][GL::NI],
+                                        float* __restrict__ dW, const Tile& tile, int32_t d,
+                                        int32_t V, int accumulate) {
+  const int64_t rows = kTail ? V - tile.n0 : 256;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      uniform_ptr(dW + (int64_t)tile.n0 * d + tile.m0), 0,
+      (int)(((rows - 1) * d + (d - tile.m0)) * 4), 0x00020000);
+  uint32_t at[GL::MI];
+#pragma unroll
+  for (int mi = 0; mi < GL::MI; ++mi) {
+    const int m = GL::out_m(mi) + GL::lane_m();
+    at[mi] = tile.m0 + m < d ? (uint32_t)(GL::lane_n() * d + m) * 4u : rbp::gemm::kOutOfRange;
+  }
+#pragma unroll
+  for (int ni = 0; ni < GL::NI; ++ni)
+#pragma unroll
+    for (int rb = 0; rb < 16; rb += kDwRows) {
+      // the previous values of kDwRows rows are loaded before any of them is
+      // stored back, so the tile waits for memory four times (8 rows; 4 rows
+      // time the same)
+      float o[kDwRows][GL::MI];
+#pragma unroll
+      for (int k = 0; k < kDwRows; ++k) {
+        const int row = GL::out_n(ni, rb + k) * d * 4;
+#pragma unroll
+        for (int mi = 0; mi < GL::MI; ++mi)
+          o[k][mi] = !accumulate ? 0.0f
+                                 : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                       rsrc, kTail ? at[mi] + row : at[mi], kTail ? 0 : row, 0));
+      }
+#pragma unroll
+      for (int k = 0; k < kDwRows; ++k) {
+        const int row = GL::out_n(ni, rb + k) * d * 4;
+#pragma unroll
+        for (int mi = 0; mi < GL::MI; ++mi)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mi][ni][rb + k] + o[k][mi]),
+                                                rsrc, kTail ? at[mi] + row : at[mi],
+                                                kTail ? 0 : row, 0);
+      }
+      // keeps the next rows' loads below these stores (the compiler would
+      // otherwise hoist them all)
+      asm volatile("" ::: "memory");
+    }
 }
 
 // Backward step 3: dW[v][m] (+)= sum_t H[t][m] dz[t][v], with A = H read
@@ -263,69 +336,36 @@ RBP_LOGITS_KERNEL void dweight_kernel(const uint16_t* __restrict__ Hc,
 #pragma unroll
       for (int ni = 0; ni < GL::NI; ++ni)
 #pragma unroll
-        for (int mi = 0; mi < GL::MI; ++mi)
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int rg = 0; rg < 4; ++rg)
-            *reinterpret_cast<float4*>(blk + GL::col(ni) * 256 + GL::row(mi, rg * 4)) =
-                make_float4(acc[mi][ni][rg * 4 + 0], acc[mi][ni][rg * 4 + 1],
-                            acc[mi][ni][rg * 4 + 2], acc[mi][ni][rg * 4 + 3]);
+          for (int mi = 0; mi < GL::MI; ++mi)
+            blk[(GL::out_n(ni, r) + GL::lane_n()) * 256 + GL::out_m(mi) + GL::lane_m()] =
+                acc[mi][ni][r];
       return;
     }
-    if (accumulate && tile.n0 + 256 <= V && tile.m0 + 256 <= d) {
-      // interior tile: the previous values are loaded kDwBatch float4 at a
-      // time before any of them is stored back, so the tile waits for memory
-      // a few times rather than once per float4 (batches of 4 and 16 time
-      // the same)
-      constexpr int kDwBatch = 8;
+    if (d <= kMaxBufferD) {
+      if (tile.n0 + 256 <= V)
+        dw_rows<false>(acc, dW, tile, d, V, accumulate);
+      else
+        dw_rows<true>(acc, dW, tile, d, V, accumulate);
+      return;
+    }
 #pragma unroll
-      for (int ni = 0; ni < GL::NI; ++ni) {
-        float* row = dW + (int64_t)(tile.n0 + GL::col(ni)) * d + tile.m0;
+    for (int ni = 0; ni < GL::NI; ++ni)
 #pragma unroll
-        for (int mh = 0; mh < GL::MI; mh += kDwBatch / 4) {
-          float4 o[kDwBatch];
+      for (int r = 0; r < 16; ++r) {
+        const int64_t v = tile.n0 + GL::out_n(ni, r) + GL::lane_n();
+        if (v >= V) continue;
 #pragma unroll
-          for (int k = 0; k < kDwBatch; ++k)
-            o[k] = *reinterpret_cast<const float4*>(row + GL::row(mh + k / 4, (k % 4) * 4));
-#pragma unroll
-          for (int k = 0; k < kDwBatch; ++k) {
-            const int mi = mh + k / 4, rg = k % 4;
-            *reinterpret_cast<float4*>(row + GL::row(mi, rg * 4)) =
-                make_float4(acc[mi][ni][rg * 4 + 0] + o[k].x, acc[mi][ni][rg * 4 + 1] + o[k].y,
-                            acc[mi][ni][rg * 4 + 2] + o[k].z, acc[mi][ni][rg * 4 + 3] + o[k].w);
-          }
-          // keeps the next batch's loads below these stores (the compiler
-          // would otherwise hoist them all and hold 16 float4 at once)
-          asm volatile("" ::: "memory");
+        for (int mi = 0; mi < GL::MI; ++mi) {
+          const int64_t m = tile.m0 + GL::out_m(mi) + GL::lane_m();
+          if (m >= d) continue;
+          float* dst = dW + v * d + m;
+          *dst = accumulate ? acc[mi][ni][r] + *dst : acc[mi][ni][r];
         }
       }
-      return;
-    }
-#pragma unroll
-    for (int ni = 0; ni < GL::NI; ++ni) {
-      const int64_t v = tile.n0 + GL::col(ni);
-      if (v >= V) continue;
-#pragma unroll
-      for (int mi = 0; mi < GL::MI; ++mi)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int64_t m = tile.m0 + GL::row(mi, rg * 4);
-          if (m < d) {
-            float4* dst = reinterpret_cast<float4*>(dW + v * d + m);
-            float4 val = make_float4(acc[mi][ni][rg * 4 + 0], acc[mi][ni][rg * 4 + 1],
-                                     acc[mi][ni][rg * 4 + 2], acc[mi][ni][rg * 4 + 3]);
-            if (accumulate) {
-              const float4 o = *dst;
-              val.x += o.x;
-              val.y += o.y;
-              val.z += o.z;
-              val.w += o.w;
-            }
-            *dst = val;
-          }
-        }
-    }
   };
-  tile_stream<GL, kMNMajor, kKMajor, kDeepDw>(A, B, n_vid, smem, tile_of, epi);
+  tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, n_vid, smem, tile_of, epi);
 }
 
 // dW += part[i] over the tiles vid_base + i (i < n_tiles) of a split

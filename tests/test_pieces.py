@@ -59,6 +59,11 @@ static void check(int r, int nk, int G, int max_slots) {
   }
 }
 int main() {
+  for (uint32_t n = 1; n <= 700; ++n)  // xcd_block undoes xcd_order
+    for (uint32_t b = 0; b < n; ++b) {
+      const uint32_t L = rbp::gemm::xcd_order(b, n);
+      if (L >= n || rbp::gemm::xcd_block(L, n) != b) return printf("xcd n=%u b=%u\n", n, b), 1;
+    }
   const int nks[] = {1, 7, 8, 15, 16, 17, 47, 63, 64, 100, 594, 2374, 2376};
   const int slots[] = {0, 1, 2, 3, 5, 17, 300};
   for (int G : {8, 104, 256, 304})
