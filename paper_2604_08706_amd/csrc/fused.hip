@@ -272,47 +272,58 @@ __device__ __forceinline__ void merge_partial(float& m, float& s, float& e, floa
   }
 }
 
-// Step 2: 64 tokens per block of 16 waves.  Wave q merges the partials
-// i = q, q + 16, ... of the block's tokens (coalesced: consecutive lanes read
-// consecutive tokens), the 16 results are combined in a fixed order by the
-// first wave, which writes lse, logp (from the step-0 target logit), the
-// entropy and the token's reference, and lists the tokens that cannot keep
-// R_t (order-free: the fix-up treats each listed token on its own).
-constexpr int kMergeTokens = 64;
-constexpr int kMergeWaves = 16;
-
+// Step 2: kTok tokens per block of 16 waves, 1024 / kTok lanes per token
+// (merge_tokens).  Lane group q merges the token's partials i = q, q + Q, ...
+// (coalesced: consecutive lanes read consecutive tokens), a wave's groups are
+// combined by shuffles and the 16 waves' results in a fixed order; the first
+// lanes write lse, logp (from the step-0 target logit), the entropy and the
+// token's reference, and list the tokens that cannot keep R_t (order-free: the
+// fix-up treats each listed token on its own).
+template <int kTok>
 __global__ void __launch_bounds__(64 * kMergeWaves) fused_merge_kernel(
     const float* __restrict__ pM, const float* __restrict__ pS, const float* __restrict__ pE,
     int64_t ldp, int32_t n_half, const float* __restrict__ zy, const float* __restrict__ R,
     const int32_t* __restrict__ seq, int64_t Tn, float* __restrict__ logp,
     float* __restrict__ lse, float* __restrict__ ent, float* __restrict__ ref,
     int32_t* __restrict__ listed, int32_t* __restrict__ n_listed) {
-  __shared__ float sm[kMergeWaves][kMergeTokens], ss[kMergeWaves][kMergeTokens],
-      se[kMergeWaves][kMergeTokens];
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * kMergeTokens + c;
+  __shared__ float sm[kMergeWaves][kTok], ss[kMergeWaves][kTok], se[kMergeWaves][kTok];
+  constexpr int kGroups = 64 / kTok, Q = kMergeWaves * kGroups;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = lane % kTok, q = wave * kGroups + lane / kTok;
+  const int64_t t = (int64_t)blockIdx.x * kTok + c;
   float m = -INFINITY, s = 0.0f, e = 0.0f;
   if (t < Tn) {
     int32_t i = q;
-    // two partials per iteration: their loads are issued together
+    // four partials per iteration: their loads are issued together
     // pE is read only when the entropy is wanted (the tile pass wrote it)
-    for (; i + kMergeWaves < n_half; i += 2 * kMergeWaves) {
-      const int64_t o0 = (int64_t)i * ldp + t, o1 = o0 + (int64_t)kMergeWaves * ldp;
-      const float M0 = pM[o0], S0 = pS[o0], E0 = ent ? pE[o0] : 0.0f;
-      const float M1 = pM[o1], S1 = pS[o1], E1 = ent ? pE[o1] : 0.0f;
-      merge_partial(m, s, e, M0, S0, E0);
-      merge_partial(m, s, e, M1, S1, E1);
+    for (; i + 3 * Q < n_half; i += 4 * Q) {
+      float M[4], S[4], E[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t o = (int64_t)(i + k * Q) * ldp + t;
+        M[k] = pM[o];
+        S[k] = pS[o];
+        E[k] = ent ? pE[o] : 0.0f;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) merge_partial(m, s, e, M[k], S[k], E[k]);
     }
-    if (i < n_half) {
+    for (; i < n_half; i += Q) {
       const int64_t o = (int64_t)i * ldp + t;
       merge_partial(m, s, e, pM[o], pS[o], ent ? pE[o] : 0.0f);
     }
   }
-  sm[q][c] = m;
-  ss[q][c] = s;
-  se[q][c] = e;
+#pragma unroll
+  for (int off = kTok; off < 64; off <<= 1)
+    merge_partial(m, s, e, __shfl_down(m, off, 64), __shfl_down(s, off, 64),
+                  __shfl_down(e, off, 64));
+  if (lane < kTok) {
+    sm[wave][c] = m;
+    ss[wave][c] = s;
+    se[wave][c] = e;
+  }
   __syncthreads();
-  if (threadIdx.x >= kMergeTokens || t >= Tn) return;
+  if (threadIdx.x >= kTok || t >= Tn) return;
   float M = -INFINITY, S = 0.0f, E = 0.0f;
 #pragma unroll
   for (int k = 0; k < kMergeWaves; ++k) merge_partial(M, S, E, sm[k][c], ss[k][c], se[k][c]);
@@ -530,10 +541,13 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
                        w.Qt, Tc, tiles_v, tiles_t);
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_LOGITS);
-    hipLaunchKernelGGL(fused_merge_kernel, dim3(rbp::ceil_div(Tn, kMergeTokens)),
-                       dim3(64 * kMergeWaves), 0, s, w.pM, w.pS, w.pE, Tc, (int32_t)(Vp / 128),
-                       w.zy, w.R, sq, Tn, logp + t0, lse + t0, entropy ? entropy + t0 : nullptr,
-                       w.ref, w.listed, w.n_listed);
+    merge_tokens(Tn, Vp / 128 > 2 * kMergeWaves, [&](auto tok) {
+      constexpr int kTok = decltype(tok)::value;
+      hipLaunchKernelGGL(fused_merge_kernel<kTok>, dim3(rbp::ceil_div(Tn, kTok)),
+                         dim3(64 * kMergeWaves), 0, s, w.pM, w.pS, w.pE, Tc, (int32_t)(Vp / 128),
+                         w.zy, w.R, sq, Tn, logp + t0, lse + t0, entropy ? entropy + t0 : nullptr,
+                         w.ref, w.listed, w.n_listed);
+    });
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_MERGE);
     const int st = policy_loss_fwd_bwd(logp + t0, old_logp + t0, sq, adv, seq_len, Tn, B,

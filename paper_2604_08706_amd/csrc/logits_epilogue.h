@@ -6,6 +6,7 @@
 #pragma once
 
 #include <cmath>
+#include <type_traits>
 
 #include "gemm_core.h"
 #include "gemm_dma.h"
@@ -179,6 +180,30 @@ __device__ __forceinline__ void dz_rows(const f32x16 (&acc)[GL::MI][GL::NI], con
     __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(g[0], g[1]), rGt, off,
                                           (int)(GL::row_off(mi, r) * ldGt * 2), kStreamStore);
   }
+}
+
+// The merge of a token's partials over the vocabulary's half tiles
+// (lse_merge_kernel, fused_merge_kernel) runs blocks of 16 waves on kTok
+// tokens, 1024 / kTok lanes on each token's chain of loads.  At 16384 tokens
+// and more 64 per block fill the chip and read whole lines (49 us against 57
+// with 32, 84 with 16, at V = 152064: 5 TB/s); with fewer tokens the chain
+// bounds it, and shorter chains on more blocks win: 8192 tokens 33 us with 32
+// against 37 / 49 with 64 / 16, 1301 tokens 22 with 16 against 29 with 64,
+// and the forward call of 37 tokens at d = 896 76 us with 8 against 95 (its
+// target dot products are spread over the blocks too).  `chain`: false where a
+// few partials per token and no dot products leave nothing to shorten, and
+// more blocks only cost their launch (256 tokens, V = 1024: +1 us).
+constexpr int kMergeWaves = 16;
+template <class Launch>
+inline void merge_tokens(int64_t T, bool chain, Launch&& launch) {
+  if (T >= 12288 || !chain)
+    launch(std::integral_constant<int, 64>{});
+  else if (T >= 6144)
+    launch(std::integral_constant<int, 32>{});
+  else if (T >= 1024)
+    launch(std::integral_constant<int, 16>{});
+  else
+    launch(std::integral_constant<int, 8>{});
 }
 
 inline int64_t round256(int64_t x) { return (x + 255) / 256 * 256; }

@@ -74,41 +74,49 @@ __device__ __forceinline__ void merge_ms(float& m, float& s, float Mi, float Si)
   }
 }
 
-// 64 tokens per block of 16 waves.  Wave q merges the partials q, q + 16, ...
-// of the block's tokens (consecutive lanes read consecutive tokens), the 16
-// results are combined in a fixed order, then each wave forms the target
-// logits of 4 tokens with one dot product each.
-constexpr int kMergeTokens = 64;
-constexpr int kMergeWaves = 16;
-
+// kTok tokens per block of 16 waves, 1024 / kTok lanes per token (merge_tokens,
+// logits_epilogue.h): lane group q merges the token's partials q, q + Q, ...
+// (consecutive lanes read consecutive tokens), a wave's groups are combined by
+// shuffles and the 16 waves' results in a fixed order; then each wave forms the
+// target logits of its share of the tokens, one dot product each.
+template <int kTok>
 __global__ void __launch_bounds__(64 * kMergeWaves) lse_merge_kernel(
     const float2* __restrict__ part, int64_t ld_part, int32_t n_half,
     const uint16_t* __restrict__ H, const uint16_t* __restrict__ W,
     const int32_t* __restrict__ tokens, const int32_t* __restrict__ seq, int64_t T, int32_t d,
     int32_t V, float* __restrict__ logp, float* __restrict__ lse) {
-  __shared__ float sm[kMergeWaves][kMergeTokens], ss[kMergeWaves][kMergeTokens];
-  __shared__ float sl[kMergeTokens];
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int64_t t0 = (int64_t)blockIdx.x * kMergeTokens;
+  __shared__ float sm[kMergeWaves][kTok], ss[kMergeWaves][kTok];
+  __shared__ float sl[kTok];
+  constexpr int kGroups = 64 / kTok, Q = kMergeWaves * kGroups;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = lane % kTok, q = wave * kGroups + lane / kTok;
+  const int64_t t0 = (int64_t)blockIdx.x * kTok;
   const int64_t t = t0 + c;
   float m = -INFINITY, s = 0.0f;
   if (t < T) {
+    const float2* p = part + t;
     int32_t i = q;
-    for (; i + kMergeWaves < n_half; i += 2 * kMergeWaves) {
-      const float2 a = part[(int64_t)i * ld_part + t];
-      const float2 b = part[(int64_t)(i + kMergeWaves) * ld_part + t];
-      merge_ms(m, s, a.x, a.y);
-      merge_ms(m, s, b.x, b.y);
+    for (; i + 3 * Q < n_half; i += 4 * Q) {  // four partials' loads in flight
+      float2 a[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] = p[(int64_t)(i + k * Q) * ld_part];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) merge_ms(m, s, a[k].x, a[k].y);
     }
-    if (i < n_half) {
-      const float2 a = part[(int64_t)i * ld_part + t];
+    for (; i < n_half; i += Q) {
+      const float2 a = p[(int64_t)i * ld_part];
       merge_ms(m, s, a.x, a.y);
     }
   }
-  sm[q][c] = m;
-  ss[q][c] = s;
+#pragma unroll
+  for (int off = kTok; off < 64; off <<= 1)
+    merge_ms(m, s, __shfl_down(m, off, 64), __shfl_down(s, off, 64));
+  if (lane < kTok) {
+    sm[wave][c] = m;
+    ss[wave][c] = s;
+  }
   __syncthreads();
-  if (threadIdx.x < kMergeTokens) {
+  if (threadIdx.x < kTok) {
     float M = -INFINITY, S = 0.0f;
 #pragma unroll
     for (int k = 0; k < kMergeWaves; ++k) merge_ms(M, S, sm[k][c], ss[k][c]);
@@ -118,10 +126,7 @@ __global__ void __launch_bounds__(64 * kMergeWaves) lse_merge_kernel(
     if (t < T) lse[t] = valid ? l : 0.0f;
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 0; k < kMergeTokens / kMergeWaves; ++k) {
-    const int cc = q * (kMergeTokens / kMergeWaves) + k;
+  for (int cc = wave; cc < kTok; cc += kMergeWaves) {
     const int64_t tt = t0 + cc;
     if (tt >= T) break;
     if (seq != nullptr && seq[tt] < 0) {
@@ -163,9 +168,12 @@ extern "C" int policy_logprob_fwd(const uint16_t* hidden, const uint16_t* W,
   const int64_t grid = rbp::gemm::stream_grid(tiles_m * tiles_n, device_cus());
   hipLaunchKernelGGL(logits_lse_partial_kernel, dim3(grid), dim3(GL::kThreads), 0, s, W,
                      hidden, T, d, V, tiles_m, tiles_n, part, ld_part);
-  hipLaunchKernelGGL(lse_merge_kernel, dim3(rbp::ceil_div(T, kMergeTokens)),
-                     dim3(64 * kMergeWaves), 0, s, part, ld_part, (int32_t)(tiles_m * 2), hidden,
-                     W, tokens, seq_of_token, T, d, V, logp, lse);
+  merge_tokens(T, true, [&](auto tok) {
+    constexpr int kTok = decltype(tok)::value;
+    hipLaunchKernelGGL(lse_merge_kernel<kTok>, dim3(rbp::ceil_div(T, kTok)),
+                       dim3(64 * kMergeWaves), 0, s, part, ld_part, (int32_t)(tiles_m * 2),
+                       hidden, W, tokens, seq_of_token, T, d, V, logp, lse);
+  });
   RBP_CHECK_LAUNCH("policy_logprob_fwd");
   return RBP_OK;
 }
