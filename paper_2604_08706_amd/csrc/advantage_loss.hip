@@ -21,33 +21,26 @@ constexpr int kLossThreads = 256;
 constexpr int kLossMaxBlocks = 1024;
 constexpr int kNumSums = 5;  // -sum w*l, sum rho, n clipped, n valid, sum l
 
-constexpr int kAdvGroups = 256;   // groups per block, one thread each
-constexpr int kAdvStage = 4096;   // records a block stages through LDS
+constexpr int kAdvGroups = 256;  // groups per block, one thread each
 
-// Block b takes groups [256 b, 256 b + 256), whose records form one
-// contiguous range.  When that range fits the stage, it is read into LDS and
-// the advantages written back with coalesced accesses (a thread per group
-// reading its own records from HBM makes a wave's loads 4 G bytes apart);
-// longer ranges take the direct path.  Same arithmetic either way.
+// Block b takes groups [256 b, 256 b + 256).  The advantages are staged too
+// and written back with coalesced accesses.
 __global__ void __launch_bounds__(kAdvGroups) group_advantage_kernel(
     const float* __restrict__ reward, const int32_t* __restrict__ group_off,
     int32_t n_groups, int32_t ddof, float eps, float* __restrict__ adv) {
-  __shared__ float r_s[kAdvStage], a_s[kAdvStage];
+  __shared__ float r_s[rbp::kAdvStage], a_s[rbp::kAdvStage];
   const int32_t g0 = blockIdx.x * kAdvGroups;
   const int32_t g1 = g0 + kAdvGroups < n_groups ? g0 + kAdvGroups : n_groups;
-  const int32_t g = g0 + threadIdx.x;
   const int32_t lo = group_off[g0], n = group_off[g1] - lo;
-  if (n > kAdvStage) {
-    if (g < g1)
-      rbp::group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps,
-                           [&](int32_t i, float a) { adv[i] = a; });
-    return;
-  }
-  for (int32_t k = threadIdx.x; k < n; k += kAdvGroups) r_s[k] = reward[lo + k];
-  __syncthreads();
-  if (g < g1)
-    rbp::group_advantage(r_s, group_off[g] - lo, group_off[g + 1] - lo, ddof, eps,
-                         [&](int32_t i, float a) { a_s[i] = a; });
+  const bool staged = n <= rbp::kAdvStage;
+  rbp::block_advantages(reward, group_off, g0, n_groups, ddof, eps, r_s,
+                        [&](int32_t i, float a) {
+                          if (staged)
+                            a_s[i - lo] = a;
+                          else
+                            adv[i] = a;
+                        });
+  if (!staged) return;
   __syncthreads();
   for (int32_t k = threadIdx.x; k < n; k += kAdvGroups) adv[lo + k] = a_s[k];
 }

@@ -27,67 +27,112 @@ __device__ __forceinline__ int64_t ring_row(int64_t base, int64_t i, int64_t cap
   return r >= cap ? r - cap : r;
 }
 
-// One thread per new group: advantages straight into the ring rows.
-__global__ void __launch_bounds__(64) push_advantage_kernel(
-    const float* __restrict__ reward, const int32_t* __restrict__ group_off, int32_t n_groups,
-    int32_t ddof, float eps, int64_t base, int64_t cap, float* __restrict__ adv) {
-  const int32_t g = blockIdx.x * 64 + threadIdx.x;
-  if (g >= n_groups) return;
-  rbp::group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps,
-                       [&](int32_t i, float a) { adv[ring_row(base, i, cap)] = a; });
-}
+constexpr int kHistMaxBins = 4096;
+constexpr int kPushThreads = 256;
+constexpr int kPushLoads = 8;  // tokens a thread has in flight
+constexpr int kPushTokens = kPushLoads * kPushThreads;
 
-// One thread per new record: the per-record fields of its row.
-__global__ void __launch_bounds__(256) push_rows_kernel(
-    int32_t n_new, int64_t base, int64_t cap, int64_t slot_tokens,
-    const int32_t* __restrict__ length, const float* __restrict__ reward, int32_t version,
-    int64_t* __restrict__ r_off, int32_t* __restrict__ r_len, float* __restrict__ r_reward,
-    int32_t* __restrict__ r_version, int32_t* __restrict__ r_uses,
-    int64_t* __restrict__ r_last) {
-  const int32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_new) return;
-  const int64_t r = ring_row(base, i, cap);
-  const int32_t len = length[i];
-  r_off[r] = r * slot_tokens;
-  r_len[r] = (int64_t)len < slot_tokens ? len : (int32_t)slot_tokens;
-  r_reward[r] = reward[i];
-  r_version[r] = version;
-  if (r_uses != nullptr) r_uses[r] = 0;
-  if (r_last != nullptr) r_last[r] = -1;
-}
+struct PushRing {
+  int64_t base, cap, slot_tokens;  // base: the first new record's row
+  int64_t* off;
+  int32_t* len;
+  float *reward, *advantage;
+  int32_t *version, *uses;
+  int64_t* last;
+  int32_t* tokens;
+  float* old_logp;
+  int64_t* hist;
+  int32_t n_bins;
+  int64_t first_evict;  // new records from here on overwrite a live one
+};
 
-// Block row i copies record i's tokens and behaviour log-probs into its row's
-// arena stretch (at most slot_tokens of them).
-__global__ void __launch_bounds__(256) push_copy_kernel(
-    int64_t base, int64_t cap, int64_t slot_tokens, const int32_t* __restrict__ length,
-    const int64_t* __restrict__ src_off, const int32_t* __restrict__ tokens,
-    const float* __restrict__ old_logp, int32_t* __restrict__ arena_tokens,
-    float* __restrict__ arena_old) {
-  const int32_t i = blockIdx.x;
-  const int64_t r = ring_row(base, i, cap);
-  int64_t n = length[i];
-  if (n > slot_tokens) n = slot_tokens;
-  const int64_t src = src_off[i], dst = r * slot_tokens;
-  for (int64_t p = (int64_t)blockIdx.y * 256 + threadIdx.x; p < n;
-       p += (int64_t)gridDim.y * 256) {
-    arena_tokens[dst + p] = tokens[src + p];
-    arena_old[dst + p] = old_logp[src + p];
+// One launch for a whole push (four launches of 2 to 7 us, each waiting for
+// the one before, took 29.5 us for 1024 records of about 900 tokens; bound by
+// launches and load latency, the bytes are worth 3 us).  Its parts are
+// independent of each other; the ones with the longest chains come first:
+//   group_blocks blocks: the advantages of 256 groups each, straight into the
+//     ring rows;
+//   field_blocks blocks: the fields of 256 records each, after the evicted
+//     records' use counts -- their replay ratios (Sec. 3.2) -- are counted in
+//     LDS and added to the histogram bin by bin (an atomic per record on a
+//     dozen hot bins took longer than the copy);
+//   the others: one column per record, the rows of the grid splitting long
+//     ones, copy tokens and behaviour log-probs into the records' arena
+//     stretches (at most slot_tokens of them).
+__global__ void __launch_bounds__(kPushThreads) push_kernel(
+    PushRing ring, int32_t n_new, int32_t group_blocks, int32_t field_blocks, int32_t n_groups,
+    const int32_t* __restrict__ group_off, const int32_t* __restrict__ length,
+    const int64_t* __restrict__ src_off, const float* __restrict__ reward, int32_t version,
+    const int32_t* __restrict__ tokens, const float* __restrict__ old_logp, int32_t ddof,
+    float eps) {
+  __shared__ union {
+    float r[rbp::kAdvStage];
+    uint32_t h[kHistMaxBins];
+  } lds;
+  int32_t b = (int32_t)blockIdx.x;
+  if (b < group_blocks) {
+    if (blockIdx.y == 0)
+      rbp::block_advantages(reward, group_off, b * kPushThreads, n_groups, ddof, eps, lds.r,
+                            [&](int32_t k, float a) {
+                              ring.advantage[ring_row(ring.base, k, ring.cap)] = a;
+                            });
+    return;
   }
-}
-
-// Replay ratio of the records a push evicts (Sec. 3.2): new record i >= first
-// overwrites a row that still holds a live record; its final use count goes
-// to the histogram before push_rows_kernel resets it.
-__global__ void __launch_bounds__(256) push_evict_kernel(int32_t n_new, int64_t first,
-                                                         int64_t base, int64_t cap,
-                                                         const int32_t* __restrict__ uses,
-                                                         int32_t n_bins,
-                                                         int64_t* __restrict__ hist) {
-  const int64_t i = first + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_new) return;
-  int32_t u = uses[ring_row(base, i, cap)];
-  u = u < 0 ? 0 : (u > n_bins - 1 ? n_bins - 1 : u);
-  atomicAdd(reinterpret_cast<unsigned long long*>(hist + u), 1ull);
+  b -= group_blocks;
+  if (b < field_blocks) {
+    if (blockIdx.y != 0) return;
+    const int32_t i = b * kPushThreads + (int32_t)threadIdx.x;
+    const int64_t r = ring_row(ring.base, i, ring.cap);
+    if (ring.hist != nullptr && ring.first_evict < n_new) {
+      for (int32_t k = threadIdx.x; k < ring.n_bins; k += kPushThreads) lds.h[k] = 0u;
+      __syncthreads();
+      if (i < n_new && i >= ring.first_evict) {
+        const int32_t u = ring.uses[r];
+        atomicAdd(&lds.h[u < 0 ? 0 : (u > ring.n_bins - 1 ? ring.n_bins - 1 : u)], 1u);
+      }
+      __syncthreads();
+      for (int32_t k = threadIdx.x; k < ring.n_bins; k += kPushThreads)
+        if (lds.h[k] != 0u)
+          atomicAdd(reinterpret_cast<unsigned long long*>(ring.hist + k),
+                    (unsigned long long)lds.h[k]);
+    }
+    if (i >= n_new) return;
+    const int32_t len = length[i];
+    ring.off[r] = r * ring.slot_tokens;
+    ring.len[r] = (int64_t)len < ring.slot_tokens ? len : (int32_t)ring.slot_tokens;
+    ring.reward[r] = reward[i];
+    ring.version[r] = version;
+    if (ring.uses != nullptr) ring.uses[r] = 0;
+    if (ring.last != nullptr) ring.last[r] = -1;
+    return;
+  }
+  b -= field_blocks;
+  const int32_t rec_blocks = (int32_t)gridDim.x - group_blocks - field_blocks;
+  for (int64_t i = b; i < n_new; i += rec_blocks) {
+    const int64_t r = ring_row(ring.base, i, ring.cap);
+    const int32_t len = length[i];
+    const int64_t n = (int64_t)len < ring.slot_tokens ? len : ring.slot_tokens;
+    const int64_t src = src_off[i], dst = r * ring.slot_tokens;
+    for (int64_t p0 = (int64_t)blockIdx.y * kPushTokens; p0 < n;
+         p0 += (int64_t)gridDim.y * kPushTokens) {
+      int32_t tk[kPushLoads];
+      float ol[kPushLoads];
+#pragma unroll
+      for (int k = 0; k < kPushLoads; ++k) {  // all loads in flight before the first store
+        const int64_t p = p0 + k * kPushThreads + threadIdx.x;
+        tk[k] = p < n ? tokens[src + p] : 0;
+        ol[k] = p < n ? old_logp[src + p] : 0.0f;
+      }
+#pragma unroll
+      for (int k = 0; k < kPushLoads; ++k) {
+        const int64_t p = p0 + k * kPushThreads + threadIdx.x;
+        if (p < n) {
+          ring.tokens[dst + p] = tk[k];
+          ring.old_logp[dst + p] = ol[k];
+        }
+      }
+    }
+  }
 }
 
 // ---- usage bookkeeping ------------------------------------------------------
@@ -142,9 +187,50 @@ __global__ void __launch_bounds__(256) use_update_kernel(const int32_t* __restri
   }
 }
 
-// ---- statistics ------------------------------------------------------------
+// Up to kUseThreads draws: one block, with the drawn rows in a hash table in
+// LDS (twice as many places as draws, so a probe ends) instead of the table of
+// first draws: one launch in place of the four above, each of which waits for
+// the one before.  Which place a row gets depends on the order of the
+// insertions, its first draw and its number of draws do not.
+constexpr int kUseThreads = 1024;
+constexpr int kUsePlaces = 2 * kUseThreads;
 
-constexpr int kHistMaxBins = 4096;
+__global__ void __launch_bounds__(kUseThreads) use_small_kernel(
+    const int32_t* __restrict__ idx, int32_t n, int64_t head, int64_t cap, int64_t step,
+    int32_t* __restrict__ uses, int64_t* __restrict__ last, int32_t* __restrict__ since) {
+  __shared__ int32_t key[kUsePlaces], first[kUsePlaces], draws[kUsePlaces];
+  const int32_t j = (int32_t)threadIdx.x;
+  for (int32_t k = j; k < kUsePlaces; k += kUseThreads) {
+    key[k] = -1;  // slots are not negative
+    first[k] = INT32_MAX;
+    draws[k] = 0;
+  }
+  const int32_t slot = j < n ? idx[j] : 0;
+  const int64_t r = ring_row(head, slot, cap);
+  const int64_t l = j < n ? last[r] : 0;
+  const int32_t u = j < n ? uses[r] : 0;
+  __syncthreads();
+  int32_t at = (int32_t)(((uint32_t)slot * 2654435761u) >> 21);  // 11 bits: kUsePlaces
+  if (j < n) {
+    for (int32_t probe = 0; probe < kUsePlaces; ++probe) {
+      const int32_t was = atomicCAS(&key[at], -1, slot);
+      if (was == -1 || was == slot) break;
+      at = (at + 1) & (kUsePlaces - 1);
+    }
+    atomicMin(&first[at], j);
+    atomicAdd(&draws[at], 1);
+  }
+  __syncthreads();
+  if (j >= n) return;
+  const bool is_first = first[at] == j;
+  if (since != nullptr) since[j] = !is_first ? 0 : (l < 0 ? -1 : (int32_t)(step - l));
+  if (is_first) {
+    uses[r] = u + draws[at];
+    last[r] = step;
+  }
+}
+
+// ---- statistics ------------------------------------------------------------
 
 // Block histogram in LDS, then one integer atomic per non-empty bin.
 __global__ void __launch_bounds__(256) hist_kernel(const int32_t* __restrict__ values, int64_t n,
@@ -200,23 +286,35 @@ extern "C" int rb_push(rb_ring* ring, int32_t n_new, int32_t n_groups, const int
   // the first free row: just past the newest record
   int64_t base = ring->head + ring->n_live;
   if (base >= cap) base -= cap;
-  // new records from index cap - n_live on overwrite live ones
-  const int64_t first_evict = cap - ring->n_live;
-  if (ring->replay_hist != nullptr && first_evict < n_new)
-    hipLaunchKernelGGL(push_evict_kernel, dim3(rbp::ceil_div(n_new - first_evict, 256)),
-                       dim3(256), 0, s, n_new, first_evict, base, cap, ring->use_count,
-                       ring->replay_bins, ring->replay_hist);
-  hipLaunchKernelGGL(push_rows_kernel, dim3(rbp::ceil_div(n_new, 256)), dim3(256), 0, s, n_new,
-                     base, cap, ring->slot_tokens, length, reward, version, ring->arena_off,
-                     ring->length, ring->reward, ring->version, ring->use_count,
-                     ring->last_step);
-  hipLaunchKernelGGL(push_advantage_kernel, dim3(rbp::ceil_div(n_groups, 64)), dim3(64), 0, s,
-                     reward, group_off, n_groups, ddof, eps, base, cap, ring->advantage);
-  int64_t by = rbp::ceil_div(ring->slot_tokens, 256);
-  if (by > 16) by = 16;
-  hipLaunchKernelGGL(push_copy_kernel, dim3(n_new, by), dim3(256), 0, s, base, cap,
-                     ring->slot_tokens, length, src_off, tokens, old_logp, ring->arena_tokens,
-                     ring->arena_old_logp);
+  const PushRing pr{base,
+                    cap,
+                    ring->slot_tokens,
+                    ring->arena_off,
+                    ring->length,
+                    ring->reward,
+                    ring->advantage,
+                    ring->version,
+                    ring->use_count,
+                    ring->last_step,
+                    ring->arena_tokens,
+                    ring->arena_old_logp,
+                    ring->replay_hist,
+                    ring->replay_bins,
+                    cap - ring->n_live};
+  // rows of the grid for long records, while there are too few records for
+  // two blocks per compute unit
+  int64_t by = rbp::ceil_div(ring->slot_tokens, kPushTokens);
+  if (by > 512 / n_new) by = 512 / n_new < 1 ? 1 : 512 / n_new;
+  // a launch holds 2^32 threads, 2^24 blocks: at most 2^21 blocks of records
+  // beside the (at most 2^23) blocks of groups and of fields, which lie below
+  // 2^24 together unless both counts are near 2^31
+  const int32_t rec_blocks = n_new < (1 << 21) ? n_new : (1 << 21);
+  const int32_t group_blocks = (int32_t)rbp::ceil_div(n_groups, kPushThreads);
+  const int32_t field_blocks = (int32_t)rbp::ceil_div(n_new, kPushThreads);
+  hipLaunchKernelGGL(push_kernel,
+                     dim3((unsigned)(rec_blocks + group_blocks + field_blocks), (unsigned)by),
+                     dim3(kPushThreads), 0, s, pr, n_new, group_blocks, field_blocks, n_groups,
+                     group_off, length, src_off, reward, version, tokens, old_logp, ddof, eps);
   RBP_CHECK_LAUNCH("rb_push");
   // FIFO bookkeeping (host integers): records past the capacity evict the oldest
   const int64_t total = ring->n_live + n_new;
@@ -240,6 +338,12 @@ extern "C" int rb_note_use(const int32_t* idx, int64_t n_draw, int64_t head, int
   RBP_REQUIRE(ws && ws_bytes >= need, RBP_EWORKSPACE,
               "rb_note_use: workspace needs %zu bytes, got %zu", need, ws_bytes);
   hipStream_t s = rbp::as_stream(stream);
+  if (n_draw <= kUseThreads) {
+    hipLaunchKernelGGL(use_small_kernel, dim3(1), dim3(kUseThreads), 0, s, idx, (int32_t)n_draw,
+                       head, capacity, step, use_count, last_step, since);
+    RBP_CHECK_LAUNCH("rb_note_use");
+    return RBP_OK;
+  }
   int32_t* first = static_cast<int32_t*>(ws);
   int64_t blocks = rbp::ceil_div(n_draw, 256);
   if (blocks > 4096) blocks = 4096;

@@ -46,4 +46,31 @@ __device__ __forceinline__ void group_advantage(const float* __restrict__ reward
   for (int32_t i = lo; i < hi; ++i) out(i, (float)(((double)reward[i] - mean) / denom));
 }
 
+// Records of a block's groups that fit its stage in LDS.
+constexpr int kAdvStage = 4096;
+
+// The groups [g0, g0 + blockDim.x) below n_groups, one thread each.  Their
+// records form one contiguous range; when it fits the stage `r_s`, it is read
+// with coalesced accesses (a thread per group reading its own records makes a
+// wave's loads 4 G bytes apart), longer ranges are read directly.  Same
+// arithmetic either way.  out(i, A_i) receives record i's value.
+template <class Out>
+__device__ __forceinline__ void block_advantages(const float* __restrict__ reward,
+                                                 const int32_t* __restrict__ group_off,
+                                                 int32_t g0, int32_t n_groups, int32_t ddof,
+                                                 float eps, float (&r_s)[kAdvStage], Out out) {
+  const int32_t g1 = g0 + (int32_t)blockDim.x < n_groups ? g0 + (int32_t)blockDim.x : n_groups;
+  const int32_t g = g0 + (int32_t)threadIdx.x;
+  const int32_t lo = group_off[g0], n = group_off[g1] - lo;
+  if (n > kAdvStage) {
+    if (g < g1) group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps, out);
+    return;
+  }
+  for (int32_t k = threadIdx.x; k < n; k += blockDim.x) r_s[k] = reward[lo + k];
+  __syncthreads();
+  if (g < g1)
+    group_advantage(r_s, group_off[g] - lo, group_off[g + 1] - lo, ddof, eps,
+                    [&](int32_t i, float a) { out(lo + i, a); });
+}
+
 }  // namespace rbp
