@@ -7,18 +7,24 @@
 // App. D.4).  The positive-prioritised mixture is an addition (see header).
 //
 // Device pipeline (one stream):
-//   [mix/retain only] pos_count -> pos_scan -> pos_compact : ascending list of
-//       positive slots (slot = FIFO position, 0 = oldest) in the workspace;
-//   [without replacement] slot_key -> select_top -> select_cand ->
-//       select_rest -> sel_count -> sel_scan -> sel_compact : an MSD radix
+//   [mix/retain only] pos_mask : one bit per slot, set for positives, and
+//       their number per granule of 1024 slots;
+//   [without replacement] slot_key -> select_cand -> select_rest : an MSD radix
 //       select (8-bit digits) finds the n_draw-th smallest 64-bit slot key K
 //       exactly -- the top digit from per-block histograms of every key, the
-//       seven lower ones by one block over the keys that share the top digit
-//       -- then the slots with a key below K (and the first ties in slot
-//       order) are listed ascending;
-//   draw     : one thread per draw; Philox4x64-10 block -> slot; per-draw
-//              outputs; scan of lengths -> cu_seqlens, n_tokens (one block
-//              up to 1024 draws, else draw_rows -> draw_scan -> draw_cu);
+//       seven lower ones by every block over the keys that share the top
+//       digit -- and marks the slots with a key below K and those equal to K,
+//       again one bit per slot with the numbers per granule;
+//   the k-th marked slot (slot = FIFO position, 0 = oldest) is then found by
+//   rank (ranks.h): no list of slots is written or read back.
+//   up to 1024 draws, as far as it pays (launch rules below), one launch:
+//   sample_packed / sample_padded : every block draws what it copies --
+//       Philox4x64-10 block -> slot -> record -- and, packed, scans all the
+//       lengths; the first block writes the per-draw outputs;
+//   otherwise
+//   draw     : one thread per draw, per-draw outputs; scan of lengths ->
+//              cu_seqlens, n_tokens (one block up to 1024 draws, else
+//              draw_rows -> draw_scan -> draw_cu);
 //   gather   : one block column per draw (packed: the part of its sequence
 //              inside the window; padded: its l_max row); coalesced copies
 //              from the token arena.
@@ -27,12 +33,22 @@
 #include <atomic>
 #include <mutex>
 
+#include "ranks.h"
 #include "rbp_internal.h"
 
 namespace {
 
-constexpr int kSlotsPerBlock = 1024;  // compaction granule
-constexpr int kCountThreads = 256;    // 4 slots per thread
+using rbp::ranks::kGranule;
+using rbp::ranks::kWords;
+using rbp::ranks::View;
+
+constexpr int kMaskThreads = 256;
+constexpr int kLdsGranules = 2048;     // granules whose offsets a block scans itself
+constexpr int kFuseThreads = 256;      // sample_packed / sample_padded
+constexpr int kFuseDraws = 512;        // draws that sample_packed redoes in every block
+constexpr int kFusePositions = 4;      // window positions per thread, at most
+constexpr int kRowVecs = 4;            // 16-byte groups of a padded row per thread
+constexpr int kRowSingles = 8;         // or positions, where rows are not aligned to them
 constexpr int kDrawThreads = 1024;  // single-block draw pass, up to this many draws
 constexpr int kRowThreads = 256;    // draws per block beyond that
 constexpr int kMaxRowBlocks = (1 << 20) / kRowThreads;
@@ -90,25 +106,85 @@ __device__ int64_t block_exclusive_scan(int64_t v, int64_t* total, int64_t* lds_
   return wave_base + incl - v;
 }
 
-__global__ void __launch_bounds__(kCountThreads) pos_count_kernel(
-    const float* __restrict__ reward, int64_t head, int64_t cap, int64_t n_range,
-    int32_t* __restrict__ counts) {
-  __shared__ int64_t lds[kCountThreads / 64];
-  const int64_t s0 = (int64_t)blockIdx.x * kSlotsPerBlock + threadIdx.x * 4;
-  int64_t c = 0;
+// ---- ranks of marked slots (ranks.h) -----------------------------------------
+
+// Where a launch finds the marks: masks and counts per granule, and, for
+// tables of more than kLdsGranules granules, their scanned offsets and total.
+struct Ranks {
+  const uint64_t *mark, *tie;  // [nb * kWords]; tie may be null
+  const int64_t* counts;       // [nb]
+  const int64_t* offsets;      // [nb], or null: scanned by each block
+  const int64_t* total;        // with offsets
+  const int64_t* need;         // ties to take, in slot order (with tie)
+  int32_t nb;
+};
+
+// Offsets of the granules (scanned into `off_s` unless they are given) and the
+// number of ranks.
+template <int NT>
+__device__ View view_ranks(const Ranks& r, int64_t (&off_s)[kLdsGranules], int64_t* lds_waves) {
+  View v{r.mark, r.tie, r.offsets, r.nb, r.tie != nullptr ? *r.need : 0, 0};
+  if (r.offsets != nullptr) {
+    v.n = rbp::ranks::below(*r.total, v.need);
+    return v;
+  }
+  constexpr int kPer = kLdsGranules / NT;
+  const int32_t per = (r.nb + NT - 1) / NT;  // <= kPer
+  const int32_t lo = (int32_t)threadIdx.x * per;
+  int64_t c[kPer], sum = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t s = s0 + i;
-    if (s < n_range && reward[phys_row(s, head, cap)] > 0.0f) ++c;
+  for (int k = 0; k < kPer; ++k) {
+    c[k] = k < per && lo + k < r.nb ? r.counts[lo + k] : 0;
+    sum += c[k];
   }
   int64_t total;
-  block_exclusive_scan<kCountThreads>(c, &total, lds);
-  if (threadIdx.x == 0) counts[blockIdx.x] = (int32_t)total;
+  int64_t at = block_exclusive_scan<NT>(sum, &total, lds_waves);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (k < per && lo + k < r.nb) off_s[lo + k] = at;
+    at += c[k];
+  }
+  __syncthreads();
+  v.off = off_s;
+  v.n = rbp::ranks::below(total, v.need);
+  return v;
 }
 
-__global__ void __launch_bounds__(1024) pos_scan_kernel(const int32_t* __restrict__ counts,
-                                                        int32_t* __restrict__ offsets,
-                                                        int64_t nb, int64_t* __restrict__ meta) {
+// Positives of granule b among the slots [0, n_range).
+__global__ void __launch_bounds__(kMaskThreads) pos_mask_kernel(
+    const float* __restrict__ reward, int64_t head, int64_t cap, int64_t n_range,
+    uint64_t* __restrict__ mark, int64_t* __restrict__ counts) {
+  __shared__ int32_t part[kMaskThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int kPer = kGranule / kMaskThreads;  // words per wave
+  const int64_t w0 = (int64_t)blockIdx.x * kWords + wave * kPer;
+  float x[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t s = (w0 + k) * 64 + lane;
+    x[k] = s < n_range ? reward[phys_row(s, head, cap)] : 0.0f;
+  }
+  int32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const uint64_t m = __ballot(x[k] > 0.0f);
+    if (lane == 0) mark[w0 + k] = m;
+    c += __popcll(m);
+  }
+  if (lane == 0) part[wave] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t n = 0;
+    for (int w = 0; w < kMaskThreads / 64; ++w) n += part[w];
+    counts[blockIdx.x] = n;
+  }
+}
+
+// Offsets and total of the counts, for tables of more than kLdsGranules
+// granules.
+__global__ void __launch_bounds__(1024) rank_scan_kernel(const int64_t* __restrict__ counts,
+                                                         int64_t* __restrict__ offsets, int64_t nb,
+                                                         int64_t* __restrict__ total_out) {
   __shared__ int64_t lds[1024 / 64];
   int64_t carry = 0;
   for (int64_t base = 0; base < nb; base += 1024) {
@@ -116,37 +192,16 @@ __global__ void __launch_bounds__(1024) pos_scan_kernel(const int32_t* __restric
     const int64_t v = i < nb ? counts[i] : 0;
     int64_t total;
     const int64_t ex = block_exclusive_scan<1024>(v, &total, lds);
-    if (i < nb) offsets[i] = (int32_t)(carry + ex);
+    if (i < nb) offsets[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) meta[0] = carry;
-}
-
-__global__ void __launch_bounds__(kCountThreads) pos_compact_kernel(
-    const float* __restrict__ reward, int64_t head, int64_t cap, int64_t n_range,
-    const int32_t* __restrict__ offsets, int32_t* __restrict__ pos_list) {
-  __shared__ int64_t lds[kCountThreads / 64];
-  const int64_t s0 = (int64_t)blockIdx.x * kSlotsPerBlock + threadIdx.x * 4;
-  bool f[4];
-  int64_t c = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t s = s0 + i;
-    f[i] = s < n_range && reward[phys_row(s, head, cap)] > 0.0f;
-    c += f[i];
-  }
-  int64_t total;
-  int64_t at = offsets[blockIdx.x] + block_exclusive_scan<kCountThreads>(c, &total, lds);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (f[i]) pos_list[at++] = (int32_t)(s0 + i);
+  if (threadIdx.x == 0) *total_out = carry;
 }
 
 // ---- selection without replacement -----------------------------------------
 
 constexpr int kKeyBlocks = 256;   // key kernel blocks (at most): key segments; a power of 2
 constexpr int kKeyThreads = 1024;
-constexpr int kTopThreads = 1024;
 constexpr int kRestThreads = 1024;
 constexpr int kRestRegKeys = 16;  // candidates per thread held in registers
 
@@ -194,41 +249,41 @@ __device__ __forceinline__ bool holds_need(int64_t excl, int64_t count, int64_t 
   return excl < need && need <= excl + count;
 }
 
-// One block: sums the per-segment top-digit histograms (four threads per
-// bin) and picks the top digit.
-__global__ void __launch_bounds__(kTopThreads) select_top_kernel(
-    const uint32_t* __restrict__ top_hist, int32_t n_seg, int64_t n_draw,
-    SelState* __restrict__ st) {
-  __shared__ uint32_t part[kTopThreads / 256][256];
-  __shared__ int64_t lds[kTopThreads / 64];
+// Every block sums the per-segment top-digit histograms (four threads per
+// bin) and picks the top digit; the first one keeps it.  Block b then lists
+// the keys of segment b whose top digit is the selected one at the start of
+// the segment's stretch of `cand` (order free: only their digit histograms
+// are taken), and their number in cand_cnt[b].  One LDS atomic per wave, no
+// global ones.
+__global__ void __launch_bounds__(kKeyThreads) select_cand_kernel(
+    const uint64_t* __restrict__ keys, int64_t n, const uint32_t* __restrict__ top_hist,
+    int64_t n_draw, SelState* __restrict__ st, uint64_t* __restrict__ cand,
+    uint32_t* __restrict__ cand_cnt) {
+  __shared__ uint32_t part[kKeyThreads / 256][256];
+  __shared__ int64_t lds[kKeyThreads / 64];
+  __shared__ uint32_t cnt, s_top;
+  const int32_t n_seg = (int32_t)gridDim.x;
   const int bin = threadIdx.x & 255, q = threadIdx.x >> 8;
   uint32_t c = 0u;
 #pragma unroll 8
-  for (int32_t b = q; b < n_seg; b += kTopThreads / 256) c += top_hist[b * 256 + bin];
+  for (int32_t b = q; b < n_seg; b += kKeyThreads / 256) c += top_hist[b * 256 + bin];
   part[q][bin] = c;
+  if (threadIdx.x == 0) cnt = 0u;
   __syncthreads();
   int64_t v = 0;
   if (threadIdx.x < 256)
-    for (int i = 0; i < kTopThreads / 256; ++i) v += part[i][bin];
+    for (int i = 0; i < kKeyThreads / 256; ++i) v += part[i][bin];
   int64_t total;
-  const int64_t excl = block_exclusive_scan<kTopThreads>(v, &total, lds);
+  const int64_t excl = block_exclusive_scan<kKeyThreads>(v, &total, lds);
   if (threadIdx.x < 256 && holds_need(excl, v, n_draw)) {
-    st->prefix = (uint64_t)bin << 56;
-    st->need = n_draw - excl;
+    s_top = (uint32_t)bin;
+    if (blockIdx.x == 0) {
+      st->prefix = (uint64_t)bin << 56;
+      st->need = n_draw - excl;
+    }
   }
-}
-
-// Block b lists the keys of segment b whose top digit is the selected one at
-// the start of the segment's stretch of `cand` (order free: only their digit
-// histograms are taken), and their number in cand_cnt[b].  One LDS atomic per
-// wave, no global ones.
-__global__ void __launch_bounds__(kKeyThreads) select_cand_kernel(
-    const uint64_t* __restrict__ keys, int64_t n, const SelState* __restrict__ st,
-    uint64_t* __restrict__ cand, uint32_t* __restrict__ cand_cnt) {
-  __shared__ uint32_t cnt;
-  if (threadIdx.x == 0) cnt = 0u;
   __syncthreads();
-  const uint64_t top = st->prefix >> 56;
+  const uint64_t top = s_top;
   const int lane = threadIdx.x & 63;
   const int64_t per = seg_len(n, gridDim.x);
   const int64_t lo = (int64_t)blockIdx.x * per;
@@ -248,16 +303,16 @@ __global__ void __launch_bounds__(kKeyThreads) select_cand_kernel(
   if (threadIdx.x == 0) cand_cnt[blockIdx.x] = cnt;
 }
 
-// One block: the lower digits, most significant first, over the candidates
-// only (the first kRestThreads * kRestRegKeys of them held in registers, any
-// further ones re-read each pass), until at most kRestThreads keys share the
-// prefix; those are then ranked directly, each thread counting the survivors
-// below and up to its own.  Integer counts only: the result does not depend
-// on the order of any addition.  Leaves the exact need-th smallest key in
-// `prefix` and the number of its ties still to be taken in `need`.
-__global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
-    const uint64_t* __restrict__ cand, const uint32_t* __restrict__ cand_cnt, int32_t n_seg,
-    int64_t n, SelState* __restrict__ st) {
+// One block's search for the exact n_draw-th smallest key: the lower digits,
+// most significant first, over the candidates only (the first kRestThreads *
+// kRestRegKeys of them held in registers, any further ones re-read each pass),
+// until at most kRestThreads keys share the prefix; those are then ranked
+// directly, each thread counting the survivors below and up to its own.
+// Integer counts only: the result does not depend on the order of any
+// addition.  Returns the key and the number of its ties to be taken.
+__device__ SelState select_rest(const uint64_t* __restrict__ cand,
+                                const uint32_t* __restrict__ cand_cnt, int32_t n_seg, int64_t n,
+                                const SelState& top) {
   __shared__ uint32_t h[256];
   __shared__ int64_t lds[kRestThreads / 64];
   __shared__ int64_t seg_start[kKeyBlocks + 1];
@@ -289,16 +344,21 @@ __global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
     return lo * per + (i - seg_start[lo]);
   };
   // positions first, then all the loads together (nc >= 1: the selected
-  // bucket holds the need-th key; indices past it re-read the last one)
-  int64_t at[kRestRegKeys];
-#pragma unroll
-  for (int u = 0; u < kRestRegKeys; ++u) {
-    const int64_t i = threadIdx.x + (int64_t)u * kRestThreads;
-    at[u] = cand_pos(i < nc ? i : nc - 1);
-  }
+  // bucket holds the need-th key; indices past it re-read the last one),
+  // in as many rounds of four as the candidates fill
   uint64_t reg[kRestRegKeys];
 #pragma unroll
-  for (int u = 0; u < kRestRegKeys; ++u) reg[u] = cand[at[u]];
+  for (int u0 = 0; u0 < kRestRegKeys; u0 += 4) {
+    if ((int64_t)u0 * kRestThreads >= nc) break;
+    int64_t at[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = threadIdx.x + (int64_t)(u0 + u) * kRestThreads;
+      at[u] = cand_pos(i < nc ? i : nc - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) reg[u0 + u] = cand[at[u]];
+  }
   // calls f(k) for every candidate k
   auto each_cand = [&](auto&& f) {
 #pragma unroll
@@ -308,8 +368,8 @@ __global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
          i += kRestThreads)
       f(cand[cand_pos(i)]);
   };
-  uint64_t prefix = st->prefix;
-  int64_t need = st->need;
+  uint64_t prefix = top.prefix;
+  int64_t need = top.need;
   int64_t n_match = nc;  // keys sharing the digits fixed so far
   int shift = 56;        // the prefix fixes the bits from `shift` up
   while (shift > 0 && n_match > kRestThreads) {
@@ -348,8 +408,9 @@ __global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
     __syncthreads();
     if (threadIdx.x < n_match) {
       const uint64_t mine = surv[threadIdx.x];
-      int64_t less = 0, leq = 0;
-      for (int64_t i = 0; i < n_match; ++i) {
+      int32_t less = 0, leq = 0;
+#pragma unroll 4
+      for (int32_t i = 0; i < (int32_t)n_match; ++i) {
         const uint64_t o = surv[i];
         less += o < mine;
         leq += o <= mine;
@@ -363,73 +424,41 @@ __global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
     prefix = s_prefix;
     need = s_need;
   }
-  if (threadIdx.x == 0) {
-    st->prefix = prefix;
-    st->need = need;
-  }
+  return SelState{prefix, need};
 }
 
-// Per slot, (key < K) in the low 32 bits and (key == K) in the high 32 bits:
-// one int64 whose block sums carry both counts.
-__device__ __forceinline__ int64_t sel_flags(uint64_t k, uint64_t K) {
-  return (k < K ? 1 : 0) + (k == K ? (int64_t(1) << 32) : 0);
-}
-
-__global__ void __launch_bounds__(kCountThreads) sel_count_kernel(
-    const uint64_t* __restrict__ keys, int64_t n, const SelState* __restrict__ st,
-    int64_t* __restrict__ counts) {
-  __shared__ int64_t lds[kCountThreads / 64];
-  const uint64_t K = st->prefix;
-  const int64_t s0 = (int64_t)blockIdx.x * kSlotsPerBlock + threadIdx.x * 4;
-  int64_t c = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (s0 + i < n) c += sel_flags(keys[s0 + i], K);
-  int64_t total;
-  block_exclusive_scan<kCountThreads>(c, &total, lds);
-  if (threadIdx.x == 0) counts[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(1024) sel_scan_kernel(const int64_t* __restrict__ counts,
-                                                        int64_t* __restrict__ offsets,
-                                                        int64_t nb) {
-  __shared__ int64_t lds[1024 / 64];
-  int64_t carry = 0;
-  for (int64_t base = 0; base < nb; base += 1024) {
-    const int64_t i = base + threadIdx.x;
-    const int64_t v = i < nb ? counts[i] : 0;
-    int64_t total;
-    const int64_t ex = block_exclusive_scan<1024>(v, &total, lds);
-    if (i < nb) offsets[i] = carry + ex;
-    carry += total;
-  }
-}
-
-// A slot with key < K goes to position (# keys < K before it) + min(# ties
-// before it, need); a tie is taken while fewer than `need` ties precede it.
-__global__ void __launch_bounds__(kCountThreads) sel_compact_kernel(
-    const uint64_t* __restrict__ keys, int64_t n, const SelState* __restrict__ st,
-    const int64_t* __restrict__ offsets, int32_t* __restrict__ sel) {
-  __shared__ int64_t lds[kCountThreads / 64];
-  const uint64_t K = st->prefix;
-  const int64_t need = st->need;
-  const int64_t s0 = (int64_t)blockIdx.x * kSlotsPerBlock + threadIdx.x * 4;
-  int64_t f[4], c = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[i] = s0 + i < n ? sel_flags(keys[s0 + i], K) : 0;
-    c += f[i];
-  }
-  int64_t total;
-  int64_t at = offsets[blockIdx.x] + block_exclusive_scan<kCountThreads>(c, &total, lds);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t less = at & 0xffffffffll, ties = at >> 32;
-    if (f[i] == 1)
-      sel[less + (ties < need ? ties : need)] = (int32_t)(s0 + i);
-    else if (f[i] != 0 && ties < need)
-      sel[less + ties] = (int32_t)(s0 + i);
-    at += f[i];
+// Marks the slots with a key below the n_draw-th smallest key K and those
+// equal to it (ties).  Every block finds K itself (select_rest: a few us,
+// where a launch of one block for it and the wait for its result cost 11);
+// the first one keeps the number of ties to be taken.  One granule per block
+// and round, 64 slots per wave.
+__global__ void __launch_bounds__(kRestThreads) select_rest_kernel(
+    const uint64_t* __restrict__ keys, int64_t n, const SelState* __restrict__ top,
+    const uint64_t* __restrict__ cand, const uint32_t* __restrict__ cand_cnt, int32_t n_seg,
+    int32_t nb, uint64_t* __restrict__ mark, uint64_t* __restrict__ tie,
+    int64_t* __restrict__ counts, int64_t* __restrict__ need) {
+  static_assert(kRestThreads == kGranule, "one slot per thread and round");
+  __shared__ int64_t part[kWords];
+  const SelState sel = select_rest(cand, cand_cnt, n_seg, n, *top);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *need = sel.need;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int32_t b = (int32_t)blockIdx.x; b < nb; b += (int32_t)gridDim.x) {
+    const int64_t s = (int64_t)b * kGranule + threadIdx.x;
+    const uint64_t k = s < n ? keys[s] : ~0ull;
+    const uint64_t m = __ballot(s < n && k < sel.prefix);
+    const uint64_t t = __ballot(s < n && k == sel.prefix);
+    if (lane == 0) {
+      mark[(int64_t)b * kWords + wave] = m;
+      tie[(int64_t)b * kWords + wave] = t;
+      part[wave] = (int64_t)__popcll(m) + ((int64_t)__popcll(t) << 32);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t sum = 0;
+      for (int w = 0; w < kWords; ++w) sum += part[w];
+      counts[b] = sum;
+    }
+    __syncthreads();
   }
 }
 
@@ -442,16 +471,15 @@ struct DrawParams {
   int64_t max_tokens, token_begin, l_max;
 };
 
-// Per-call constants of the draws: the positives listed by the count/scan
-// pass, the retained positives and the size of the retained set.
+// Per-call constants of the draws: the positives (slots with a rank), the
+// retained positives and the size of the retained set.
 struct DrawSet {
   int64_t n_pos, keep, n_set;
 };
 
-__device__ __forceinline__ DrawSet draw_set(const DrawParams& p,
-                                            const int64_t* __restrict__ meta) {
+__device__ __forceinline__ DrawSet draw_set(const DrawParams& p, const View& v) {
   DrawSet d;
-  d.n_pos = (p.mode == RB_POS_MIX || p.mode == RB_POS_RETAIN) ? meta[0] : 0;
+  d.n_pos = (p.mode == RB_POS_MIX || p.mode == RB_POS_RETAIN) ? v.n : 0;
   // retained set: the newest `keep` positives older than the fresh part, then
   // the fresh part [first_fresh, n_live)
   d.keep = d.n_pos < p.n_pos_keep ? d.n_pos : p.n_pos_keep;
@@ -461,93 +489,302 @@ __device__ __forceinline__ DrawSet draw_set(const DrawParams& p,
 
 // Slot of draw j: the Philox4x64-10 block with counter (j, step, 0, 0) picks
 // it (or the j-th selected slot without replacement).
+template <bool kRanks>
 __device__ __forceinline__ int64_t draw_slot(const DrawParams& p, const DrawSet& d,
-                                             const int32_t* __restrict__ pos_list, int64_t j) {
-  if (p.mode == RB_NO_REPLACE || p.mode == RB_UNUSED_FIRST) return pos_list[j];
+                                             const View& v, int64_t j) {
+  if constexpr (!kRanks)
+    return (int64_t)__umul64hi(philox4x64_10((uint64_t)j, p.step, 0, 0, p.seed, 0).x0,
+                               (uint64_t)p.n_live);
+  if (p.mode == RB_NO_REPLACE || p.mode == RB_UNUSED_FIRST) return rbp::ranks::slot_of(v, j);
   const Block4 b = philox4x64_10((uint64_t)j, p.step, 0, 0, p.seed, 0);
   if (p.mode == RB_UNIFORM) return (int64_t)__umul64hi(b.x0, (uint64_t)p.n_live);
+  int64_t k;  // rank of a positive
   if (p.mode == RB_POS_MIX) {
-    if (d.n_pos > 0 && (b.x1 >> 32) < p.p_q32) return pos_list[__umul64hi(b.x0, (uint64_t)d.n_pos)];
-    return (int64_t)__umul64hi(b.x0, (uint64_t)p.n_live);
+    if (d.n_pos == 0 || (b.x1 >> 32) >= p.p_q32)
+      return (int64_t)__umul64hi(b.x0, (uint64_t)p.n_live);
+    k = (int64_t)__umul64hi(b.x0, (uint64_t)d.n_pos);
+  } else {
+    if (d.n_set <= 0) return 0;
+    const int64_t i = (int64_t)__umul64hi(b.x0, (uint64_t)d.n_set);
+    if (i >= d.keep) return p.first_fresh + (i - d.keep);
+    k = d.n_pos - d.keep + i;
   }
-  if (d.n_set <= 0) return 0;
-  const int64_t i = (int64_t)__umul64hi(b.x0, (uint64_t)d.n_set);
-  return i < d.keep ? pos_list[d.n_pos - d.keep + i] : p.first_fresh + (i - d.keep);
+  return rbp::ranks::slot_of(v, k);
 }
 
-// Per-draw outputs of draw j; returns its contribution to the stream (full
-// length packed, min(length, l_max) padded).
-__device__ __forceinline__ int64_t draw_one(const DrawParams& p, const DrawSet& d,
-                                            const int32_t* __restrict__ pos_list,
-                                            const int32_t* __restrict__ length,
-                                            const float* __restrict__ advantage,
-                                            const int32_t* __restrict__ version, int64_t j,
-                                            int32_t* __restrict__ out_idx,
-                                            float* __restrict__ out_adv,
-                                            int32_t* __restrict__ out_len,
-                                            int32_t* __restrict__ out_age) {
-  const int64_t slot = draw_slot(p, d, pos_list, j);
-  const int64_t r = phys_row(slot, p.head, p.cap);
-  const int64_t len = length[r];
-  out_idx[j] = (int32_t)slot;
-  out_adv[j] = advantage[r];
-  out_len[j] = (int32_t)len;
-  out_age[j] = p.cur_version - version[r];
+// The record table as the draws read it, and the outputs they write.
+struct DrawTable {
+  const int32_t* length;
+  const float* advantage;
+  const int32_t* version;
+  const int64_t* arena_off;
+  const int32_t* arena_tokens;
+  const float* arena_old;
+  int32_t* out_idx;
+  float* out_adv;
+  int32_t *out_len, *out_age, *cu_seqlens;
+  int32_t* tokens;
+  float* old_logp;
+  int32_t* seq;
+  int64_t* n_tokens;
+};
+
+// Per-draw outputs of draw j of slot `slot`, row r, length len.
+__device__ __forceinline__ void write_draw(const DrawParams& p, const DrawTable& t, int64_t j,
+                                           int64_t slot, int64_t r, int64_t len) {
+  t.out_idx[j] = (int32_t)slot;
+  t.out_adv[j] = t.advantage[r];
+  t.out_len[j] = (int32_t)len;
+  t.out_age[j] = p.cur_version - t.version[r];
+}
+
+// Its contribution to the stream (full length packed, min(length, l_max)
+// padded).
+__device__ __forceinline__ int64_t stream_len(const DrawParams& p, int64_t len) {
   return p.layout == RB_LAYOUT_PACKED ? len : (len < p.l_max ? len : p.l_max);
+}
+
+template <bool kRanks>
+__device__ __forceinline__ int64_t draw_one(const DrawParams& p, const DrawSet& d,
+                                            const View& v, const DrawTable& t, int64_t j) {
+  const int64_t slot = draw_slot<kRanks>(p, d, v, j);
+  const int64_t r = phys_row(slot, p.head, p.cap);
+  const int64_t len = t.length[r];
+  write_draw(p, t, j, slot, r, len);
+  return stream_len(p, len);
+}
+
+__device__ __forceinline__ int64_t window_tokens(const DrawParams& p, int64_t sum) {
+  if (p.layout != RB_LAYOUT_PACKED) return sum;
+  const int64_t v = sum - p.token_begin;
+  return v < 0 ? 0 : (v > p.max_tokens ? p.max_tokens : v);
 }
 
 __device__ __forceinline__ void write_totals(const DrawParams& p, int64_t sum,
                                              int64_t* __restrict__ n_tokens,
                                              int64_t* __restrict__ stream_total) {
-  if (p.layout == RB_LAYOUT_PACKED) {
-    int64_t v = sum - p.token_begin;
-    v = v < 0 ? 0 : (v > p.max_tokens ? p.max_tokens : v);
-    *n_tokens = v;
-  } else {
-    *n_tokens = sum;
-  }
+  *n_tokens = window_tokens(p, sum);
   *stream_total = sum;
 }
 
+// ---- draw and gather in one launch ------------------------------------------
+//
+// A draw kernel and a gather kernel after it are two chains of dependent loads
+// (draw: record; gather: draw, arena offset, tokens) and two launches, about
+// 5 us each for the few draws of a training batch.  Here every block redoes the
+// draws it needs -- one Philox block and two loads per draw -- so nothing is
+// handed over.  16384 tokens of 24 uniform draws: 10.1 us in two launches, 8 in
+// one; see the launch rules for where redoing the draws stops paying.
+
+// Block b copies kFuseThreads * per window positions, from b of those on.
+// kRanks: every mode but the uniform one, which needs none of the ranks'
+// registers and LDS.
+template <bool kRanks>
+__global__ void __launch_bounds__(kFuseThreads) sample_packed_kernel(DrawParams p, Ranks ranks,
+                                                                     DrawTable t, int32_t per) {
+  __shared__ int64_t off_s[kRanks ? kLdsGranules : 1];
+  __shared__ int64_t lds[kFuseThreads / 64];
+  __shared__ int64_t src_s[kFuseDraws];     // arena offset of draw j
+  __shared__ int32_t cu_s[kFuseDraws + 1];  // its stream position
+  View v{};
+  if constexpr (kRanks) v = view_ranks<kFuseThreads>(ranks, off_s, lds);
+  const DrawSet d = draw_set(p, v);
+  constexpr int kPer = kFuseDraws / kFuseThreads;
+  const int64_t j0 = (int64_t)threadIdx.x * kPer;
+  int64_t len[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t j = j0 + k;
+    len[k] = 0;
+    if (j < p.n_draw) {
+      const int64_t slot = draw_slot<kRanks>(p, d, v, j);
+      const int64_t r = phys_row(slot, p.head, p.cap);
+      len[k] = t.length[r];
+      src_s[j] = t.arena_off[r];
+      if (blockIdx.x == 0) write_draw(p, t, j, slot, r, len[k]);
+    }
+    sum += len[k];
+  }
+  int64_t total;
+  int64_t at = block_exclusive_scan<kFuseThreads>(sum, &total, lds);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (j0 + k <= p.n_draw) {
+      cu_s[j0 + k] = (int32_t)at;
+      if (blockIdx.x == 0) t.cu_seqlens[j0 + k] = (int32_t)at;
+    }
+    at += len[k];
+  }
+  if (threadIdx.x == 0) {
+    if (p.n_draw == kFuseDraws) {  // no thread's j0 + k reaches it
+      cu_s[kFuseDraws] = (int32_t)total;
+      if (blockIdx.x == 0) t.cu_seqlens[kFuseDraws] = (int32_t)total;
+    }
+    if (blockIdx.x == 0) *t.n_tokens = window_tokens(p, total);
+  }
+  __syncthreads();
+  const int64_t w0 = (int64_t)blockIdx.x * (kFuseThreads * per) + threadIdx.x;
+  int32_t tk[kFusePositions], sq[kFusePositions];
+  float ol[kFusePositions];
+#pragma unroll
+  for (int k = 0; k < kFusePositions; ++k) {
+    const int64_t w = w0 + (int64_t)k * kFuseThreads, pos = p.token_begin + w;
+    tk[k] = 0;
+    ol[k] = 0.0f;
+    sq[k] = -1;
+    if (k >= per || w >= p.max_tokens || pos >= total) continue;
+    int32_t lo = 0, hi = (int32_t)p.n_draw;  // the draw that holds pos
+    while (hi - lo > 1) {
+      const int32_t m = (lo + hi) >> 1;
+      if (cu_s[m] <= pos) lo = m; else hi = m;
+    }
+    const int64_t src = src_s[lo] + (pos - cu_s[lo]);
+    tk[k] = t.arena_tokens[src];
+    ol[k] = t.arena_old[src];
+    sq[k] = lo;
+  }
+#pragma unroll
+  for (int k = 0; k < kFusePositions; ++k) {
+    const int64_t w = w0 + (int64_t)k * kFuseThreads;
+    if (k >= per || w >= p.max_tokens) continue;
+    t.tokens[w] = tk[k];
+    t.old_logp[w] = ol[k];
+    t.seq[w] = sq[k];
+  }
+}
+
+// Row j of [n_draw, l_max] from the record at `off` of length n (clamped to
+// l_max): positions past n hold token 0, log-prob 0, seq -1.  kVec: four
+// positions per thread with 16-byte stores (l_max % 4 == 0, rows 16-byte
+// aligned); the arena is read with 4-byte loads, its rows start anywhere.  A
+// thread has kGroups groups (or positions) in flight.
+template <bool kVec, int kGroups>
+__device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, int64_t off,
+                                         const DrawTable& t) {
+  int32_t* tok_row = t.tokens + j * l_max;
+  float* old_row = t.old_logp + j * l_max;
+  int32_t* seq_row = t.seq + j * l_max;
+  if constexpr (kVec) {
+    const int64_t step = (int64_t)blockDim.x * 4;
+    for (int64_t p0 = blockIdx.y * (step * kGroups) + threadIdx.x * 4; p0 < l_max;
+         p0 += gridDim.y * (step * kGroups)) {
+      int32_t tk[kGroups][4], sq[kGroups][4];
+      float ol[kGroups][4];
+#pragma unroll
+      for (int u = 0; u < kGroups; ++u)  // all loads in flight before the first store
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t p = p0 + u * step + i;
+          const bool in = p < n;
+          tk[u][i] = in ? t.arena_tokens[off + p] : 0;
+          ol[u][i] = in ? t.arena_old[off + p] : 0.0f;
+          sq[u][i] = in ? (int32_t)j : -1;
+        }
+#pragma unroll
+      for (int u = 0; u < kGroups; ++u) {
+        const int64_t p = p0 + u * step;
+        if (p >= l_max) continue;
+        *reinterpret_cast<int4*>(tok_row + p) = make_int4(tk[u][0], tk[u][1], tk[u][2], tk[u][3]);
+        *reinterpret_cast<float4*>(old_row + p) =
+            make_float4(ol[u][0], ol[u][1], ol[u][2], ol[u][3]);
+        *reinterpret_cast<int4*>(seq_row + p) = make_int4(sq[u][0], sq[u][1], sq[u][2], sq[u][3]);
+      }
+    }
+  } else {
+    const int64_t step = blockDim.x;
+    for (int64_t p0 = blockIdx.y * (step * kGroups) + threadIdx.x; p0 < l_max;
+         p0 += gridDim.y * (step * kGroups)) {
+      int32_t tk[kGroups];
+      float ol[kGroups];
+#pragma unroll
+      for (int u = 0; u < kGroups; ++u) {
+        const bool in = p0 + u * step < n;
+        tk[u] = in ? t.arena_tokens[off + p0 + u * step] : 0;
+        ol[u] = in ? t.arena_old[off + p0 + u * step] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < kGroups; ++u) {
+        const int64_t p = p0 + u * step;
+        if (p >= l_max) continue;
+        tok_row[p] = tk[u];
+        old_row[p] = ol[u];
+        seq_row[p] = p < n ? (int32_t)j : -1;
+      }
+    }
+  }
+}
+
+// Blocks (j, y): row j, which only its own draw decides.  One more column sums
+// the lengths of all draws.
+template <bool kRanks, bool kVec>
+__global__ void __launch_bounds__(kFuseThreads) sample_padded_kernel(DrawParams p, Ranks ranks,
+                                                                     DrawTable t) {
+  __shared__ int64_t off_s[kRanks ? kLdsGranules : 1];
+  __shared__ int64_t lds[kFuseThreads / 64];
+  if (blockIdx.x == 0 && blockIdx.y != 0) return;
+  View v{};
+  if constexpr (kRanks) v = view_ranks<kFuseThreads>(ranks, off_s, lds);
+  const DrawSet d = draw_set(p, v);
+  if (blockIdx.x == 0) {
+    int64_t sum = 0;
+    for (int64_t j = threadIdx.x; j < p.n_draw; j += kFuseThreads)
+      sum += stream_len(p, t.length[phys_row(draw_slot<kRanks>(p, d, v, j), p.head, p.cap)]);
+    int64_t total;
+    block_exclusive_scan<kFuseThreads>(sum, &total, lds);
+    if (threadIdx.x == 0) {
+      *t.n_tokens = total;
+      t.cu_seqlens[0] = 0;
+    }
+    return;
+  }
+  const int64_t j = (int64_t)blockIdx.x - 1;
+  const int64_t slot = draw_slot<kRanks>(p, d, v, j);
+  const int64_t r = phys_row(slot, p.head, p.cap);
+  const int64_t len = t.length[r], off = t.arena_off[r];
+  if (blockIdx.y == 0 && threadIdx.x == 0) {
+    write_draw(p, t, j, slot, r, len);
+    t.cu_seqlens[j + 1] = (int32_t)((j + 1) * p.l_max);
+  }
+  fill_row<kVec, kVec ? kRowVecs : kRowSingles>(j, p.l_max, stream_len(p, len), off, t);
+}
+
+// ---- draws, then the gather -------------------------------------------------
+
 // Up to kDrawThreads draws: one block, one draw per thread, block scan of the
 // lengths -> cu_seqlens, n_tokens.
-__global__ void __launch_bounds__(kDrawThreads) draw_kernel(
-    DrawParams p, const int64_t* __restrict__ meta, const int32_t* __restrict__ pos_list,
-    const int32_t* __restrict__ length, const float* __restrict__ advantage,
-    const int32_t* __restrict__ version, int32_t* __restrict__ out_idx,
-    float* __restrict__ out_adv, int32_t* __restrict__ out_len, int32_t* __restrict__ out_age,
-    int32_t* __restrict__ cu_seqlens, int64_t* __restrict__ n_tokens,
-    int64_t* __restrict__ stream_total) {
+template <bool kRanks>
+__global__ void __launch_bounds__(kDrawThreads) draw_kernel(DrawParams p, Ranks ranks, DrawTable t,
+                                                            int64_t* __restrict__ stream_total) {
+  __shared__ int64_t off_s[kRanks ? kLdsGranules : 1];
   __shared__ int64_t lds[kDrawThreads / 64];
-  const DrawSet d = draw_set(p, meta);
+  View rv{};
+  if constexpr (kRanks) rv = view_ranks<kDrawThreads>(ranks, off_s, lds);
+  const DrawSet d = draw_set(p, rv);
   const int64_t j = threadIdx.x;
-  const int64_t v = j < p.n_draw ? draw_one(p, d, pos_list, length, advantage, version, j,
-                                            out_idx, out_adv, out_len, out_age)
-                                 : 0;
+  const int64_t v = j < p.n_draw ? draw_one<kRanks>(p, d, rv, t, j) : 0;
   int64_t total;
   const int64_t ex = block_exclusive_scan<kDrawThreads>(v, &total, lds);
-  if (j == 0) cu_seqlens[0] = 0;
+  if (j == 0) t.cu_seqlens[0] = 0;
   if (j < p.n_draw)
-    cu_seqlens[j + 1] = (int32_t)(p.layout == RB_LAYOUT_PACKED ? ex + v : (j + 1) * p.l_max);
-  if (j == 0) write_totals(p, total, n_tokens, stream_total);
+    t.cu_seqlens[j + 1] = (int32_t)(p.layout == RB_LAYOUT_PACKED ? ex + v : (j + 1) * p.l_max);
+  if (j == 0) write_totals(p, total, t.n_tokens, stream_total);
 }
 
 // More draws: blocks of kRowThreads draws write the per-draw outputs and
 // their block sums; one block scans the sums; then each block writes its
 // cu_seqlens.  Many blocks keep the scattered record reads spread over the
 // chip.
-__global__ void __launch_bounds__(kRowThreads) draw_rows_kernel(
-    DrawParams p, const int64_t* __restrict__ meta, const int32_t* __restrict__ pos_list,
-    const int32_t* __restrict__ length, const float* __restrict__ advantage,
-    const int32_t* __restrict__ version, int32_t* __restrict__ out_idx,
-    float* __restrict__ out_adv, int32_t* __restrict__ out_len, int32_t* __restrict__ out_age,
-    int64_t* __restrict__ blk_sum) {
+template <bool kRanks>
+__global__ void __launch_bounds__(kRowThreads) draw_rows_kernel(DrawParams p, Ranks ranks,
+                                                                DrawTable t,
+                                                                int64_t* __restrict__ blk_sum) {
+  __shared__ int64_t off_s[kRanks ? kLdsGranules : 1];
   __shared__ int64_t lds[kRowThreads / 64];
-  const DrawSet d = draw_set(p, meta);
+  View rv{};
+  if constexpr (kRanks) rv = view_ranks<kRowThreads>(ranks, off_s, lds);
+  const DrawSet d = draw_set(p, rv);
   const int64_t j = (int64_t)blockIdx.x * kRowThreads + threadIdx.x;
-  const int64_t v = j < p.n_draw ? draw_one(p, d, pos_list, length, advantage, version, j,
-                                            out_idx, out_adv, out_len, out_age)
-                                 : 0;
+  const int64_t v = j < p.n_draw ? draw_one<kRanks>(p, d, rv, t, j) : 0;
   int64_t total;
   block_exclusive_scan<kRowThreads>(v, &total, lds);
   if (threadIdx.x == 0) blk_sum[blockIdx.x] = total;
@@ -621,77 +858,58 @@ __global__ void __launch_bounds__(256) gather_packed_kernel(
   }
 }
 
-// Padded rows: draw j fills row j of [n_draw, l_max] (positions past the
-// record's length: token 0, log-prob 0, seq -1).  kVec: four positions per
-// thread with 16-byte stores (l_max % 4 == 0, rows 16-byte aligned); the
-// arena is read with 4-byte loads, its rows start anywhere.
+// Padded rows of draws already made.
 template <bool kVec>
-__global__ void __launch_bounds__(256) gather_padded_kernel(
-    int64_t l_max, int64_t head, int64_t cap, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ len, const int64_t* __restrict__ arena_off,
-    const int32_t* __restrict__ arena_tokens, const float* __restrict__ arena_old,
-    int32_t* __restrict__ tokens, float* __restrict__ old_logp, int32_t* __restrict__ seq) {
+__global__ void __launch_bounds__(256) gather_padded_kernel(int64_t l_max, int64_t head,
+                                                            int64_t cap, DrawTable t) {
   const int64_t j = blockIdx.x;
-  const int64_t n = len[j] < l_max ? len[j] : l_max;
-  const int64_t off = arena_off[phys_row(idx[j], head, cap)];
-  int32_t* tok_row = tokens + j * l_max;
-  float* old_row = old_logp + j * l_max;
-  int32_t* seq_row = seq + j * l_max;
-  if constexpr (kVec) {
-    for (int64_t p = ((int64_t)blockIdx.y * blockDim.x + threadIdx.x) * 4; p < l_max;
-         p += (int64_t)gridDim.y * blockDim.x * 4) {
-      int4 tk;
-      float4 ol;
-      int4 sq;
-      int32_t* tkp = &tk.x;
-      float* olp = &ol.x;
-      int32_t* sqp = &sq.x;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool in = p + i < n;
-        tkp[i] = in ? arena_tokens[off + p + i] : 0;
-        olp[i] = in ? arena_old[off + p + i] : 0.0f;
-        sqp[i] = in ? (int32_t)j : -1;
-      }
-      *reinterpret_cast<int4*>(tok_row + p) = tk;
-      *reinterpret_cast<float4*>(old_row + p) = ol;
-      *reinterpret_cast<int4*>(seq_row + p) = sq;
-    }
-  } else {
-    for (int64_t p = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; p < l_max;
-         p += (int64_t)gridDim.y * blockDim.x) {
-      if (p < n) {
-        tok_row[p] = arena_tokens[off + p];
-        old_row[p] = arena_old[off + p];
-        seq_row[p] = (int32_t)j;
-      } else {
-        tok_row[p] = 0;
-        old_row[p] = 0.0f;
-        seq_row[p] = -1;
-      }
-    }
-  }
+  const int64_t n = t.out_len[j] < l_max ? t.out_len[j] : l_max;
+  fill_row<kVec, 1>(j, l_max, n, t.arena_off[phys_row(t.out_idx[j], head, cap)], t);
+}
+
+// Workspace of a table of `capacity` rows.  Its size is part of the contract of
+// rb_sample_gather_noalloc (which tables its static scratch holds), so it
+// keeps room for a 4-byte slot list and two 4-byte counts per granule: the
+// masks take the list's place.
+struct SampleWs {
+  uint64_t* mark;     // [2][nb * kWords]: marked slots, ties
+  int64_t* meta;      // total of the ranks, length of the stream, ties to take
+  uint64_t* keys;     // [capacity]
+  int64_t *counts, *offsets;  // [nb]
+  SelState* top;
+  uint32_t *top_hist, *cand_cnt;
+  uint64_t* cand;     // [capacity]
+  int64_t *blk_sum, *blk_off;
+  size_t bytes;
+};
+
+SampleWs carve_sample(void* base, int64_t capacity) {
+  const int64_t nb = rbp::ceil_div(capacity, kGranule);
+  rbp::WsCarver c(base);
+  SampleWs w;
+  c.take<int32_t>(nb);
+  c.take<int32_t>(nb);
+  // two sets of masks, 2 * nb * kWords * 8 <= capacity / 4 + 256 bytes: within
+  // 4 * capacity rounded up to 256
+  w.mark = reinterpret_cast<uint64_t*>(c.take<int32_t>(capacity));
+  w.meta = c.take<int64_t>(4);
+  w.keys = c.take<uint64_t>(capacity);
+  w.counts = c.take<int64_t>(nb);
+  w.offsets = c.take<int64_t>(nb);
+  w.top = c.take<SelState>(1);
+  w.top_hist = c.take<uint32_t>(kKeyBlocks * 256);
+  w.cand_cnt = c.take<uint32_t>(kKeyBlocks);
+  w.cand = c.take<uint64_t>(capacity);
+  w.blk_sum = c.take<int64_t>(kMaxRowBlocks);
+  w.blk_off = c.take<int64_t>(kMaxRowBlocks);
+  w.bytes = rbp::align_up(c.used, 256);
+  return w;
 }
 
 }  // namespace
 
 size_t rbp::sample_gather_ws(int64_t capacity) {
-  const int64_t nb = ceil_div(capacity < 1 ? 1 : capacity, kSlotsPerBlock);
-  WsCarver c(nullptr);
-  c.take<int32_t>(nb);
-  c.take<int32_t>(nb);
-  c.take<int32_t>(capacity < 1 ? 1 : capacity);
-  c.take<int64_t>(4);
-  c.take<uint64_t>(capacity < 1 ? 1 : capacity);
-  c.take<int64_t>(nb);
-  c.take<int64_t>(nb);
-  c.take<SelState>(1);
-  c.take<uint32_t>(kKeyBlocks * 256);
-  c.take<uint32_t>(kKeyBlocks);
-  c.take<uint64_t>(capacity < 1 ? 1 : capacity);
-  c.take<int64_t>(kMaxRowBlocks);
-  c.take<int64_t>(kMaxRowBlocks);
-  return align_up(c.used, 256);
+  return carve_sample(nullptr, capacity < 1 ? 1 : capacity).bytes;
 }
 
 namespace {
@@ -742,21 +960,7 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
               "rb_sample_gather: workspace needs %zu bytes, got %zu", need, ws_bytes);
 
   hipStream_t s = rbp::as_stream(stream);
-  const int64_t nb_cap = rbp::ceil_div(rec->capacity, kSlotsPerBlock);
-  rbp::WsCarver c(ws);
-  int32_t* counts = c.take<int32_t>(nb_cap);
-  int32_t* offsets = c.take<int32_t>(nb_cap);
-  int32_t* pos_list = c.take<int32_t>(rec->capacity);
-  int64_t* meta = c.take<int64_t>(4);
-  uint64_t* keys = c.take<uint64_t>(rec->capacity);
-  int64_t* sel_counts = c.take<int64_t>(nb_cap);
-  int64_t* sel_offsets = c.take<int64_t>(nb_cap);
-  SelState* sel_state = c.take<SelState>(1);
-  uint32_t* top_hist = c.take<uint32_t>(kKeyBlocks * 256);
-  uint32_t* cand_cnt = c.take<uint32_t>(kKeyBlocks);
-  uint64_t* cand = c.take<uint64_t>(rec->capacity);
-  int64_t* blk_sum = c.take<int64_t>(kMaxRowBlocks);
-  int64_t* blk_off = c.take<int64_t>(kMaxRowBlocks);
+  const SampleWs w = carve_sample(ws, rec->capacity);
 
   DrawParams p{};
   p.mode = cfg->mode;
@@ -776,69 +980,104 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
   p.token_begin = cfg->token_begin;
   p.l_max = cfg->l_max;
 
+  Ranks ranks{};
   if (no_replace) {
     const int64_t n = rec->n_live;
-    int64_t kb = rbp::ceil_div(n, 2048);
+    int64_t kb = rbp::ceil_div(n, kKeyThreads);
     if (kb > kKeyBlocks) kb = kKeyBlocks;
     hipLaunchKernelGGL(slot_key_kernel, dim3(kb), dim3(kKeyThreads), 0, s, cfg->seed, cfg->step,
                        n, rec->head, rec->capacity,
-                       cfg->mode == RB_UNUSED_FIRST ? rec->use_count : nullptr, keys, top_hist);
-    hipLaunchKernelGGL(select_top_kernel, dim3(1), dim3(kTopThreads), 0, s, top_hist,
-                       (int32_t)kb, cfg->n_draw, sel_state);
-    hipLaunchKernelGGL(select_cand_kernel, dim3(kb), dim3(kKeyThreads), 0, s, keys, n,
-                       sel_state, cand, cand_cnt);
-    hipLaunchKernelGGL(select_rest_kernel, dim3(1), dim3(kRestThreads), 0, s, cand, cand_cnt,
-                       (int32_t)kb, n, sel_state);
-    const int64_t nb = rbp::ceil_div(n, kSlotsPerBlock);
-    hipLaunchKernelGGL(sel_count_kernel, dim3(nb), dim3(kCountThreads), 0, s, keys, n, sel_state,
-                       sel_counts);
-    hipLaunchKernelGGL(sel_scan_kernel, dim3(1), dim3(1024), 0, s, sel_counts, sel_offsets, nb);
-    hipLaunchKernelGGL(sel_compact_kernel, dim3(nb), dim3(kCountThreads), 0, s, keys, n,
-                       sel_state, sel_offsets, pos_list);
+                       cfg->mode == RB_UNUSED_FIRST ? rec->use_count : nullptr, w.keys,
+                       w.top_hist);
+    hipLaunchKernelGGL(select_cand_kernel, dim3(kb), dim3(kKeyThreads), 0, s, w.keys, n,
+                       w.top_hist, cfg->n_draw, w.top, w.cand, w.cand_cnt);
+    ranks.nb = (int32_t)rbp::ceil_div(n, kGranule);
+    uint64_t* tie = w.mark + (int64_t)ranks.nb * kWords;
+    const unsigned blocks = ranks.nb < 256 ? ranks.nb : 256;
+    hipLaunchKernelGGL(select_rest_kernel, dim3(blocks), dim3(kRestThreads), 0, s, w.keys, n, w.top,
+                       w.cand, w.cand_cnt, (int32_t)kb, ranks.nb, w.mark, tie, w.counts,
+                       w.meta + 2);
+    ranks.tie = tie;
+    ranks.need = w.meta + 2;
   } else if (cfg->mode != RB_UNIFORM) {
     // positives over all live slots (mixture) or over the non-fresh ones (retention)
     const int64_t n_range = cfg->mode == RB_POS_MIX ? rec->n_live : p.first_fresh;
-    const int64_t nb = rbp::ceil_div(n_range > 0 ? n_range : 1, kSlotsPerBlock);
-    hipLaunchKernelGGL(pos_count_kernel, dim3(nb), dim3(kCountThreads), 0, s, rec->reward,
-                       rec->head, rec->capacity, n_range, counts);
-    hipLaunchKernelGGL(pos_scan_kernel, dim3(1), dim3(1024), 0, s, counts, offsets, nb, meta);
-    hipLaunchKernelGGL(pos_compact_kernel, dim3(nb), dim3(kCountThreads), 0, s, rec->reward,
-                       rec->head, rec->capacity, n_range, offsets, pos_list);
+    ranks.nb = (int32_t)rbp::ceil_div(n_range > 0 ? n_range : 1, kGranule);
+    hipLaunchKernelGGL(pos_mask_kernel, dim3(ranks.nb), dim3(kMaskThreads), 0, s, rec->reward,
+                       rec->head, rec->capacity, n_range, w.mark, w.counts);
+  }
+  ranks.mark = w.mark;
+  ranks.counts = w.counts;
+  if (ranks.nb > kLdsGranules) {
+    hipLaunchKernelGGL(rank_scan_kernel, dim3(1), dim3(1024), 0, s, w.counts, w.offsets,
+                       (int64_t)ranks.nb, w.meta);
+    ranks.offsets = w.offsets;
+    ranks.total = w.meta;
+  }
+  const DrawTable t{rec->length,     rec->advantage,      rec->version, rec->arena_off,
+                    rec->arena_tokens, rec->arena_old_logp, out->idx,     out->adv,
+                    out->len,        out->age,            out->cu_seqlens, out->tokens,
+                    out->old_logp,   out->seq_of_token,   out->n_tokens};
+  const bool packed = cfg->layout == RB_LAYOUT_PACKED;
+  const bool vec = cfg->l_max % 4 == 0 &&
+                   ((reinterpret_cast<uintptr_t>(out->tokens) |
+                     reinterpret_cast<uintptr_t>(out->old_logp) |
+                     reinterpret_cast<uintptr_t>(out->seq_of_token)) & 15) == 0;
+  // Draw and gather in one launch while every block can redo the draws it
+  // needs at little cost.  Padded, that is one draw (and one block sums all of
+  // them: up to kDrawThreads); packed, it is all of them: up to kFuseDraws, in
+  // windows of up to 2^18 draws x blocks (each one record read of 64 bytes).
+  const int64_t per = packed && cfg->max_tokens > 65536 ? kFusePositions : 1;
+  const int64_t blocks = packed ? rbp::ceil_div(cfg->max_tokens, kFuseThreads * per) : 0;
+  if (packed && cfg->n_draw <= kFuseDraws && blocks * cfg->n_draw <= (1 << 18)) {
+    hipLaunchKernelGGL(ranks.nb > 0 ? sample_packed_kernel<true> : sample_packed_kernel<false>,
+                       dim3((unsigned)blocks), dim3(kFuseThreads), 0, s, p,
+                       ranks, t, (int32_t)per);
+    RBP_CHECK_LAUNCH("rb_sample_gather");
+    return RBP_OK;
+  }
+  if (!packed && cfg->n_draw <= kDrawThreads) {
+    const auto kernel = ranks.nb > 0
+                            ? (vec ? sample_padded_kernel<true, true>
+                                   : sample_padded_kernel<true, false>)
+                            : (vec ? sample_padded_kernel<false, true>
+                                   : sample_padded_kernel<false, false>);
+    // blocks per row: as many as its passes, but no more in all than run at
+    // once (5 per compute unit): each redoes the draw, and a second round of
+    // them cost more than the longer rows (662 uniform draws of 2886 positions
+    // 27.9 us in 12 blocks each, 13.5 in one)
+    int64_t by = rbp::ceil_div(cfg->l_max, 256 * (vec ? 4 * kRowVecs : kRowSingles));
+    if (by > 1280 / cfg->n_draw) by = 1280 / cfg->n_draw;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cfg->n_draw + 1, (unsigned)by), dim3(kFuseThreads), 0, s, p,
+                       ranks, t);
+    RBP_CHECK_LAUNCH("rb_sample_gather");
+    return RBP_OK;
   }
   if (cfg->n_draw <= kDrawThreads) {
-    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, s, p, meta, pos_list,
-                       rec->length, rec->advantage, rec->version, out->idx, out->adv, out->len,
-                       out->age, out->cu_seqlens, out->n_tokens, meta + 1);
+    hipLaunchKernelGGL(ranks.nb > 0 ? draw_kernel<true> : draw_kernel<false>, dim3(1), dim3(kDrawThreads), 0, s, p, ranks, t, w.meta + 1);
   } else {
     const int64_t nb = rbp::ceil_div(cfg->n_draw, kRowThreads);
-    hipLaunchKernelGGL(draw_rows_kernel, dim3(nb), dim3(kRowThreads), 0, s, p, meta, pos_list,
-                       rec->length, rec->advantage, rec->version, out->idx, out->adv, out->len,
-                       out->age, blk_sum);
-    hipLaunchKernelGGL(draw_scan_kernel, dim3(1), dim3(1024), 0, s, p, blk_sum, blk_off, nb,
-                       out->n_tokens, meta + 1);
-    hipLaunchKernelGGL(draw_cu_kernel, dim3(nb), dim3(kRowThreads), 0, s, p, out->len, blk_off,
+    hipLaunchKernelGGL(ranks.nb > 0 ? draw_rows_kernel<true> : draw_rows_kernel<false>, dim3(nb),
+                       dim3(kRowThreads), 0, s, p, ranks, t, w.blk_sum);
+    hipLaunchKernelGGL(draw_scan_kernel, dim3(1), dim3(1024), 0, s, p, w.blk_sum, w.blk_off, nb,
+                       out->n_tokens, w.meta + 1);
+    hipLaunchKernelGGL(draw_cu_kernel, dim3(nb), dim3(kRowThreads), 0, s, p, out->len, w.blk_off,
                        out->cu_seqlens);
   }
-  if (cfg->layout == RB_LAYOUT_PACKED) {
+  if (packed) {
     // about 256 window positions per block
-    int64_t by = rbp::ceil_div(cfg->max_tokens, cfg->n_draw * 256);
-    if (by > 64) by = 64;
-    hipLaunchKernelGGL(gather_packed_kernel, dim3(cfg->n_draw, by), dim3(256), 0, s,
-                       rec->head, rec->capacity, cfg->token_begin, cfg->max_tokens, meta + 1,
+    int64_t gy = rbp::ceil_div(cfg->max_tokens, cfg->n_draw * 256);
+    if (gy > 64) gy = 64;
+    hipLaunchKernelGGL(gather_packed_kernel, dim3(cfg->n_draw, gy), dim3(256), 0, s,
+                       rec->head, rec->capacity, cfg->token_begin, cfg->max_tokens, w.meta + 1,
                        out->cu_seqlens, out->idx, rec->arena_off, rec->arena_tokens,
                        rec->arena_old_logp, out->tokens, out->old_logp, out->seq_of_token);
   } else {
-    const bool vec = cfg->l_max % 4 == 0 &&
-                     ((reinterpret_cast<uintptr_t>(out->tokens) |
-                       reinterpret_cast<uintptr_t>(out->old_logp) |
-                       reinterpret_cast<uintptr_t>(out->seq_of_token)) & 15) == 0;
     int64_t by = rbp::ceil_div(cfg->l_max, vec ? 1024 : 256);
     if (by > 64) by = 64;
     hipLaunchKernelGGL(vec ? gather_padded_kernel<true> : gather_padded_kernel<false>,
                        dim3(cfg->n_draw, by), dim3(256), 0, s, cfg->l_max, rec->head,
-                       rec->capacity, out->idx, out->len, rec->arena_off, rec->arena_tokens,
-                       rec->arena_old_logp, out->tokens, out->old_logp,
-                       out->seq_of_token);
+                       rec->capacity, t);
   }
   RBP_CHECK_LAUNCH("rb_sample_gather");
   return RBP_OK;
