@@ -13,13 +13,16 @@
 // result is bitwise reproducible.
 
 #include "group_advantage.h"
+#include "loss_terms.h"
 #include "rbp_internal.h"
 
 namespace {
 
 constexpr int kLossThreads = 256;
-constexpr int kLossMaxBlocks = 1024;
-constexpr int kNumSums = 5;  // -sum w*l, sum rho, n clipped, n valid, sum l
+constexpr int kLossMaxBlocks = rbp::loss::kMaxBlocks;
+using rbp::loss::kNumSums;
+using rbp::loss::token_terms;
+using rbp::loss::TokenTerms;
 
 constexpr int kAdvGroups = 256;  // groups per block, one thread each
 
@@ -51,31 +54,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
-}
-
-// Loss terms of one token (a masked token, s < 0, contributes nothing).
-struct TokenTerms {
-  float g, wterm, rho, cut, valid, term;
-};
-__device__ __forceinline__ TokenTerms token_terms(float lp, float olp, int32_t s,
-                                                  const float* __restrict__ adv,
-                                                  const int32_t* __restrict__ seq_len,
-                                                  float inv_nseq, float lo_b, float hi_b) {
-  TokenTerms r{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (s < 0) return r;
-  const float A = adv[s];
-  const float w = inv_nseq / (float)seq_len[s];
-  const float rho = expf(lp - olp);
-  const float clipped = fminf(fmaxf(rho, lo_b), hi_b);
-  const float term = fminf(rho * A, clipped * A);
-  const bool cut = (A > 0.0f && rho > hi_b) || (A < 0.0f && rho < lo_b);
-  r.g = cut ? 0.0f : -A * rho * w;
-  r.wterm = term * w;
-  r.rho = rho;
-  r.cut = cut ? 1.0f : 0.0f;
-  r.valid = 1.0f;
-  r.term = term;
-  return r;
 }
 
 // Four consecutive tokens per thread and iteration (16-byte loads and
@@ -132,21 +110,13 @@ __global__ void __launch_bounds__(kLossThreads) grpo_token_kernel(
   }
 }
 
-// Wave k sums the block partials of sum k: lane l takes blocks l, l + 64, ...
-// in order, then a fixed butterfly combines the lanes (bitwise reproducible).
+// Wave k sums the block partials of sum k.
 __global__ void __launch_bounds__(64 * kNumSums) grpo_finalize_kernel(
     const float* __restrict__ partials, int nblocks, float* __restrict__ loss_accum,
     float* __restrict__ stats) {
-  const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float v = 0.0f;
-  for (int b = lane; b < nblocks; b += 64) v += partials[b * kNumSums + k];
-  v = wave_sum(v);
-  if (lane == 0) {
-    if (k == 0)
-      loss_accum[0] += v;
-    else
-      stats[k - 1] += v;
-  }
+  const int k = threadIdx.x >> 6;
+  const float v = rbp::loss::sum_partials(partials, nblocks, k);
+  if ((threadIdx.x & 63) == 0) rbp::loss::add_sum(k, v, loss_accum, stats);
 }
 
 // ---- objective variants -------------------------------------------------

@@ -45,6 +45,7 @@
 // dz is rounded to bf16 once, as q, and c_t h_t once more.
 
 #include "logits_epilogue.h"
+#include "loss_terms.h"
 #include "rbp_internal.h"
 
 namespace {
@@ -272,7 +273,16 @@ __device__ __forceinline__ void merge_partial(float& m, float& s, float& e, floa
   }
 }
 
-// Step 2: kTok tokens per block of 16 waves, 1024 / kTok lanes per token
+// The loss pass where the merge does it (step 3): its inputs, dlogp and one row
+// of partial sums per block; partials null where a launch of its own does it.
+struct LossArgs {
+  const float *old_logp, *adv;
+  const int32_t* seq_len;
+  float inv_nseq, lo_b, hi_b;
+  float *dlogp, *partials;
+};
+
+// Steps 2 and 3: kTok tokens per block of 16 waves, 1024 / kTok lanes per token
 // (merge_tokens).  Lane group q merges the token's partials i = q, q + Q, ...
 // (coalesced: consecutive lanes read consecutive tokens), a wave's groups are
 // combined by shuffles and the 16 waves' results in a fixed order; the first
@@ -285,7 +295,7 @@ __global__ void __launch_bounds__(64 * kMergeWaves) fused_merge_kernel(
     int64_t ldp, int32_t n_half, const float* __restrict__ zy, const float* __restrict__ R,
     const int32_t* __restrict__ seq, int64_t Tn, float* __restrict__ logp,
     float* __restrict__ lse, float* __restrict__ ent, float* __restrict__ ref,
-    int32_t* __restrict__ listed, int32_t* __restrict__ n_listed) {
+    int32_t* __restrict__ listed, int32_t* __restrict__ n_listed, LossArgs loss) {
   __shared__ float sm[kMergeWaves][kTok], ss[kMergeWaves][kTok], se[kMergeWaves][kTok];
   constexpr int kGroups = 64 / kTok, Q = kMergeWaves * kGroups;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -323,66 +333,113 @@ __global__ void __launch_bounds__(64 * kMergeWaves) fused_merge_kernel(
     se[wave][c] = e;
   }
   __syncthreads();
-  if (threadIdx.x >= kTok || t >= Tn) return;
-  float M = -INFINITY, S = 0.0f, E = 0.0f;
+  if (wave != 0) return;
+  rbp::loss::TokenTerms terms{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (lane < kTok && t < Tn) {
+    float M = -INFINITY, S = 0.0f, E = 0.0f;
 #pragma unroll
-  for (int k = 0; k < kMergeWaves; ++k) merge_partial(M, S, E, sm[k][c], ss[k][c], se[k][c]);
-  const bool valid = seq == nullptr || seq[t] >= 0;
-  const float l = M + logf(S);
-  lse[t] = valid ? l : 0.0f;
-  logp[t] = valid ? zy[t] - l : 0.0f;
-  if (ent != nullptr) ent[t] = valid ? l - E / S : 0.0f;
-  const float r = R[t];
-  const bool keeps = (M - r <= kRefAbove) && (r - M <= kRefBelow);  // false for NaN
-  ref[t] = keeps ? r : M;
-  if (valid && !keeps) listed[atomicAdd(n_listed, 1)] = (int32_t)t;
-}
-
-// Step 4a: the listed tokens' columns re-referenced to M_t in place.  Block b
-// owns the 128 vocabulary rows of half tile b (one row per thread) and walks
-// the list; each q is multiplied by exp(R_t - M_t) where its half tile was
-// stored against R_t, else by exp(M_b - M_t).  Rows whose stored value
-// underflowed stay 0 (their p is below exp(-87) of the reference's).
-__global__ void __launch_bounds__(128) fixup_kernel(uint16_t* __restrict__ Qt, int64_t ldQ,
-                                                    const float* __restrict__ pM, int64_t ldp,
-                                                    const float* __restrict__ R,
-                                                    const float* __restrict__ ref,
-                                                    const int32_t* __restrict__ listed,
-                                                    const int32_t* __restrict__ n_listed,
-                                                    int64_t Tn, int32_t V) {
-  const int32_t half = (int32_t)blockIdx.x;
-  const int32_t v = half * 128 + (int32_t)threadIdx.x;
-  int64_t n = *n_listed;
-  if (n > Tn) n = Tn;
-  for (int64_t i = 0; i < n; ++i) {
-    const int64_t t = listed[i];
-    const float Mb = pM[(int64_t)half * ldp + t], r = R[t], M = ref[t];
-    const float x = stores_against_ref(Mb, r) ? fminf((r - M) * kLog2e, 126.0f)
-                                              : (Mb - M) * kLog2e;
-    const float fct = exp2_hw(x);
-    if (v < V) {
-      uint16_t* p = Qt + (int64_t)v * ldQ + t;
-      *p = __builtin_bit_cast(uint16_t, (__bf16)(bf16_to_f32(*p) * fct));
+    for (int k = 0; k < kMergeWaves; ++k) merge_partial(M, S, E, sm[k][c], ss[k][c], se[k][c]);
+    const int32_t sq = seq[t];
+    const bool valid = sq >= 0;
+    const float l = M + logf(S);
+    const float lp = valid ? zy[t] - l : 0.0f;
+    lse[t] = valid ? l : 0.0f;
+    logp[t] = lp;
+    if (ent != nullptr) ent[t] = valid ? l - E / S : 0.0f;
+    const float r = R[t];
+    const bool keeps = (M - r <= kRefAbove) && (r - M <= kRefBelow);  // false for NaN
+    ref[t] = keeps ? r : M;
+    if (valid && !keeps) listed[atomicAdd(n_listed, 1)] = (int32_t)t;
+    if (loss.partials != nullptr) {
+      terms = rbp::loss::token_terms(lp, loss.old_logp[t], sq, loss.adv, loss.seq_len,
+                                     loss.inv_nseq, loss.lo_b, loss.hi_b);
+      loss.dlogp[t] = terms.g;
     }
+  }
+  if (loss.partials == nullptr) return;
+  const float sums[rbp::loss::kNumSums] = {wave_sum(-terms.wterm), wave_sum(terms.rho),
+                                           wave_sum(terms.cut), wave_sum(terms.valid),
+                                           wave_sum(terms.term)};
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < rbp::loss::kNumSums; ++k)
+      loss.partials[(int64_t)blockIdx.x * rbp::loss::kNumSums + k] = sums[k];
   }
 }
 
-// Step 4b: one block per token t < T256.  c_t = -dlogp_t exp(ref_t - lse_t)
-// (0 for masked and padding tokens); H'_t = c_t h_t in bf16; the target
-// entry q_{t,y} = exp(lse_t - ref_t) expm1(logp_t), so that c_t q_{t,y} =
-// dlogp_t (1 - p_{t,y}).
+// Step 4, three kinds of blocks that do not wait for each other (as launches
+// of their own the small ones cost 4 to 5 us each):
+//   block 0: the loss pass's sums over its n_partials rows of partial sums;
+//   blocks 1 .. n_fix: the listed tokens' columns of the 256 vocabulary rows
+//     of one tile, re-referenced to M_t in place.  One row per thread walks the
+//     list; each q is multiplied by exp(R_t - M_t) where its half tile was
+//     stored against R_t, else by exp(M_b - M_t) (rows whose stored value
+//     underflowed stay 0: their p is below exp(-87) of the reference's), and
+//     the target's entry is written instead;
+//   the others: four tokens t < T256 each, a wave per token.  c_t = -dlogp_t
+//     exp(ref_t - lse_t) (0 for masked and padding tokens); H'_t = c_t h_t in
+//     bf16; and, for a token that is not listed, the target entry q_{t,y} =
+//     exp(lse_t - ref_t) expm1(logp_t), so that c_t q_{t,y} = dlogp_t (1 -
+//     p_{t,y}).
+constexpr int kScaleTokens = 4;
+
+struct fixup_kernel_args {
+  const float *R, *pM;
+  int64_t ldp;
+  const int32_t *listed, *n_listed;
+  int32_t n_fix;
+};
+struct LossSums {
+  const float* partials;
+  int n_partials;
+  float *loss_accum, *stats;
+};
+
 __global__ void __launch_bounds__(256) token_scale_kernel(
     const uint16_t* __restrict__ Hc, const int32_t* __restrict__ tokens,
     const int32_t* __restrict__ seq, const float* __restrict__ lse,
     const float* __restrict__ logp, const float* __restrict__ dlogp,
-    const float* __restrict__ ref, int64_t Tn, int32_t d, int32_t V, uint16_t* __restrict__ Hp,
-    float* __restrict__ cs, uint16_t* __restrict__ Qt, int64_t ldQ) {
-  const int64_t t = blockIdx.x;
-  const bool valid = t < Tn && (seq == nullptr || seq[t] >= 0);
+    const float* __restrict__ ref, int64_t Tn, int64_t T256, int32_t d, int32_t V,
+    uint16_t* __restrict__ Hp, float* __restrict__ cs, uint16_t* __restrict__ Qt, int64_t ldQ,
+    fixup_kernel_args fix, LossSums sums) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto target_q = [&](int64_t t) {
+    return __builtin_bit_cast(
+        uint16_t, (__bf16)(exp2_hw((lse[t] - ref[t]) * kLog2e) * expm1f(logp[t])));
+  };
+  if (blockIdx.x == 0) {
+    for (int k = wave; sums.n_partials > 0 && k < rbp::loss::kNumSums; k += 4) {
+      const float v = rbp::loss::sum_partials(sums.partials, sums.n_partials, k);
+      if (lane == 0) rbp::loss::add_sum(k, v, sums.loss_accum, sums.stats);
+    }
+    return;
+  }
+  if ((int32_t)blockIdx.x <= fix.n_fix) {
+    const int32_t v = ((int32_t)blockIdx.x - 1) * 256 + (int32_t)threadIdx.x;
+    const int64_t half = v >> 7;
+    int64_t n = *fix.n_listed;
+    if (n > Tn) n = Tn;
+    for (int64_t i = 0; i < n; ++i) {
+      const int64_t t = fix.listed[i];
+      const float Mb = fix.pM[half * fix.ldp + t], r = fix.R[t], M = ref[t];
+      const float x = stores_against_ref(Mb, r) ? fminf((r - M) * kLog2e, 126.0f)
+                                                : (Mb - M) * kLog2e;
+      const float fct = exp2_hw(x);
+      if (v < V) {
+        uint16_t* p = Qt + (int64_t)v * ldQ + t;
+        *p = tokens[t] == v ? target_q(t)
+                            : __builtin_bit_cast(uint16_t, (__bf16)(bf16_to_f32(*p) * fct));
+      }
+    }
+    return;
+  }
+  const int64_t t = ((int64_t)blockIdx.x - 1 - fix.n_fix) * kScaleTokens + wave;
+  if (t >= T256) return;
+  const bool valid = t < Tn && seq[t] >= 0;
   const float c = valid ? -dlogp[t] * exp2_hw((ref[t] - lse[t]) * kLog2e) : 0.0f;
   uint4* dst = reinterpret_cast<uint4*>(Hp + t * d);
   const uint4* src = reinterpret_cast<const uint4*>(Hc + t * d);
-  for (int32_t k = threadIdx.x; k < d / 8; k += 256) {
+  for (int32_t k = lane; k < d / 8; k += 64) {
     uint4 o = make_uint4(0u, 0u, 0u, 0u);
     if (t < Tn) {
       const uint4 h = src[k];
@@ -396,14 +453,11 @@ __global__ void __launch_bounds__(256) token_scale_kernel(
     }
     dst[k] = o;
   }
-  if (threadIdx.x == 0) {
+  if (lane == 0) {
     cs[t] = c;
-    if (valid) {
-      const int32_t y = tokens[t];
-      if (y >= 0 && y < V)
-        Qt[(int64_t)y * ldQ + t] = __builtin_bit_cast(
-            uint16_t, (__bf16)(exp2_hw((lse[t] - ref[t]) * kLog2e) * expm1f(logp[t])));
-    }
+    const int32_t y = valid ? tokens[t] : -1;
+    // a listed token's reference is not R_t (NaN included)
+    if (y >= 0 && y < V && ref[t] == fix.R[t]) Qt[(int64_t)y * ldQ + t] = target_q(t);
   }
 }
 
@@ -417,7 +471,7 @@ struct FusedWs {
   uint16_t* Qt;
   float *zy, *R, *ref, *cs;
   int32_t *listed, *n_listed;
-  void* loss;
+  float* loss;
   size_t loss_bytes;
   uint16_t* Hp;
   float *pM, *pS, *pE;
@@ -437,7 +491,7 @@ FusedWs carve_fused(void* base, int64_t Tc, int32_t d, int32_t V) {
   w.listed = c.take<int32_t>((size_t)Tc);
   w.n_listed = c.take<int32_t>(1);
   w.loss_bytes = rbp::loss_ws(Tc);
-  w.loss = c.take<uint8_t>(w.loss_bytes);
+  w.loss = c.take<float>(w.loss_bytes / sizeof(float));
   w.hp_at = rbp::align_up(c.used, 256);
   w.Hp = c.take<uint16_t>((size_t)Tc * (size_t)d);
   w.pm_at = rbp::align_up(c.used, 256);
@@ -541,30 +595,47 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
                        w.Qt, Tc, tiles_v, tiles_t);
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_LOGITS);
+    // the loss pass rides on the merge while its rows of partial sums fit
+    int n_partials = 0;
     merge_tokens(Tn, Vp / 128 > 2 * kMergeWaves, [&](auto tok) {
       constexpr int kTok = decltype(tok)::value;
-      hipLaunchKernelGGL(fused_merge_kernel<kTok>, dim3(rbp::ceil_div(Tn, kTok)),
-                         dim3(64 * kMergeWaves), 0, s, w.pM, w.pS, w.pE, Tc, (int32_t)(Vp / 128),
-                         w.zy, w.R, sq, Tn, logp + t0, lse + t0, entropy ? entropy + t0 : nullptr,
-                         w.ref, w.listed, w.n_listed);
+      const int64_t blocks = rbp::ceil_div(Tn, kTok);
+      if (blocks <= rbp::loss::kMaxBlocks) n_partials = (int)blocks;
+      const LossArgs loss{old_logp + t0,      adv,          seq_len,
+                          (float)(1.0 / (double)n_seq_total), 1.0f - eps_low, 1.0f + eps_high,
+                          dlogp + t0,         n_partials > 0 ? w.loss : nullptr};
+      hipLaunchKernelGGL(fused_merge_kernel<kTok>, dim3(blocks), dim3(64 * kMergeWaves), 0, s,
+                         w.pM, w.pS, w.pE, Tc, (int32_t)(Vp / 128), w.zy, w.R, sq, Tn, logp + t0,
+                         lse + t0, entropy ? entropy + t0 : nullptr, w.ref, w.listed,
+                         w.n_listed, loss);
     });
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_MERGE);
-    const int st = policy_loss_fwd_bwd(logp + t0, old_logp + t0, sq, adv, seq_len, Tn, B,
-                                       n_seq_total, eps_low, eps_high, loss_accum, dlogp + t0,
-                                       stats, w.loss, w.loss_bytes, stream);
-    if (st != RBP_OK) return st;
+    if (n_partials == 0) {
+      const int st = policy_loss_fwd_bwd(logp + t0, old_logp + t0, sq, adv, seq_len, Tn, B,
+                                         n_seq_total, eps_low, eps_high, loss_accum, dlogp + t0,
+                                         stats, w.loss, w.loss_bytes, stream);
+      if (st != RBP_OK) return st;
+    }
     RBP_FUSED_MARK(RBP_PHASE_LOSS);
-    hipLaunchKernelGGL(fixup_kernel, dim3((unsigned)(Vp / 128)), dim3(128), 0, s, w.Qt, Tc, w.pM,
-                       Tc, w.R, w.ref, w.listed, w.n_listed, Tn, V);
-    hipLaunchKernelGGL(token_scale_kernel, dim3((unsigned)T256), dim3(256), 0, s, Hc,
-                       tokens + t0, sq, lse + t0, logp + t0, dlogp + t0, w.ref, Tn, d, V, w.Hp,
-                       w.cs, w.Qt, Tc);
+    hipLaunchKernelGGL(token_scale_kernel,
+                       dim3((unsigned)(1 + tiles_v + rbp::ceil_div(T256, kScaleTokens))),
+                       dim3(256), 0, s, Hc, tokens + t0, sq, lse + t0, logp + t0, dlogp + t0,
+                       w.ref, Tn, T256, d, V, w.Hp, w.cs, w.Qt, Tc,
+                       fixup_kernel_args{w.R, w.pM, Tc, w.listed, w.n_listed, (int32_t)tiles_v},
+                       LossSums{w.loss, n_partials, loss_accum, stats});
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_SCALE);
     const int acc = (accumulate_dW || t0 > 0) ? 1 : 0;
-    rbp::launch_dweight(w.Hp, w.Qt, Tc, Tn, d, V, dW, acc, 0, tiles_v, s, w.pM,
-                        (int64_t)((ws_bytes - w.pm_at) / sizeof(float)));
+    const int64_t pm_floats = (int64_t)((ws_bytes - w.pm_at) / sizeof(float));
+    if (rbp::launch_both_products(w.Hp, W, w.Qt, Tc, Tn, d, V, dhidden + t0 * d, dW, acc, s, w.pM,
+                                  pm_floats, w.cs)) {
+      RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
+      RBP_FUSED_MARK(RBP_PHASE_DW);
+      RBP_FUSED_MARK(RBP_PHASE_DHIDDEN);
+      continue;
+    }
+    rbp::launch_dweight(w.Hp, w.Qt, Tc, Tn, d, V, dW, acc, 0, tiles_v, s, w.pM, pm_floats);
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     RBP_FUSED_MARK(RBP_PHASE_DW);
     rbp::launch_dhidden(W, w.Qt, Tc, Tn, d, V, dhidden + t0 * d, s,

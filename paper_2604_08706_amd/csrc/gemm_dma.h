@@ -347,8 +347,9 @@ struct SideLoad<G, kMNMajor> {
   }
 };
 
-// Persistent tile loop.  This workgroup takes the virtual blocks blockIdx.x,
-// blockIdx.x + gridDim.x, ... below n_vid; tile_of(vid) gives each one's Tile
+// Persistent tile loop.  This workgroup, number wg of n_wg (blockIdx.x of
+// gridDim.x in a launch of its own), takes the virtual blocks wg, wg + n_wg,
+// ... below n_vid; tile_of(vid) gives each one's Tile
 // (every tile of a launch has the same number of K steps, nk >= 1) and
 // epi(vid, acc) consumes its finished fp32 accumulators.  An epi that
 // returns bool may return false to keep the accumulators for the
@@ -380,11 +381,12 @@ struct SideLoad<G, kMNMajor> {
 // whenever it enters a new tile.
 template <class G, int kLA, int kLB, int kDeep, int kOut = kOutM, class TileFn, class EpiFn>
 __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, int32_t n_vid,
-                                            uint8_t* smem, TileFn&& tile_of, EpiFn&& epi) {
+                                            uint8_t* smem, TileFn&& tile_of, EpiFn&& epi,
+                                            int32_t wg, int32_t n_wg) {
   static_assert(kDeep == 1 || kDeep == 2, "deep operand: 1 = A, 2 = B");
   constexpr int nA = kDeep == 1 ? 3 : 2;
-  const int32_t stride = (int32_t)gridDim.x;
-  const int32_t vid0 = (int32_t)blockIdx.x;
+  const int32_t stride = n_wg;
+  const int32_t vid0 = wg;
   if (vid0 >= n_vid) return;
   constexpr int L = 32 / G::kWaves;
   SideLoad<G, kLA> la;
@@ -521,6 +523,13 @@ __device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, 
     }
   }
   wait_vmcnt<0>();
+}
+
+template <class G, int kLA, int kLB, int kDeep, int kOut = kOutM, class TileFn, class EpiFn>
+__device__ __forceinline__ void tile_stream(const Operand& A, const Operand& B, int32_t n_vid,
+                                            uint8_t* smem, TileFn&& tile_of, EpiFn&& epi) {
+  tile_stream<G, kLA, kLB, kDeep, kOut>(A, B, n_vid, smem, tile_of, epi, (int32_t)blockIdx.x,
+                                        (int32_t)gridDim.x);
 }
 
 // Workgroups for a persistent launch over n_tiles tiles on a device with

@@ -181,34 +181,47 @@ __device__ __forceinline__ void last_round_tile(int32_t i, int32_t r, int32_t ba
 // are carried from piece to piece of a tile; a tile's first share goes to dH
 // and the others to their slots of `part`, arrays laid out like dH that
 // part_add_dh_kernel adds in order.
-RBP_LOGITS_KERNEL void dhidden_pieces_kernel(const uint16_t* __restrict__ W,
-                                             const uint16_t* __restrict__ Gt, int64_t ldGt,
-                                             int64_t Tn, int32_t d, int32_t V,
-                                             const float* __restrict__ cs,
-                                             float* __restrict__ dH, int64_t tiles_m,
-                                             int64_t tiles_n, int32_t base, Pieces pc,
-                                             float* __restrict__ part, int64_t slot_floats) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
-  const int64_t T256 = (Tn + 255) / 256 * 256;
-  const Operand A{W, d, d, V};          // (m = hidden unit, k = vocab): W[v][m]
-  const Operand B{Gt, ldGt, T256, V};   // (n = token, k = vocab): Gt[v][t]
+struct DhArgs {
+  const uint16_t* W;
+  const uint16_t* Gt;
+  int64_t ldGt, Tn;
+  int32_t d, V;
+  const float* cs;
+  float* dH;
+  int64_t tiles_m, tiles_n;
+  int32_t base;
+  Pieces pc;
+  float* part;
+  int64_t slot_floats;
+};
+
+__device__ __forceinline__ void dhidden_pieces(const DhArgs& g, uint8_t* smem, int32_t wg,
+                                               int32_t n_wg) {
+  const int64_t T256 = (g.Tn + 255) / 256 * 256;
+  const Operand A{g.W, g.d, g.d, g.V};        // (m = hidden unit, k = vocab): W[v][m]
+  const Operand B{g.Gt, g.ldGt, T256, g.V};   // (n = token, k = vocab): Gt[v][t]
   auto tile_of = [&](int32_t vid) {
-    const Pieces::At a = pc.at(vid, (int32_t)gridDim.x);
+    const Pieces::At a = g.pc.at(vid, n_wg);
     int32_t tm, tn;
-    last_round_tile(a.tile, pc.r, base, tiles_m, tiles_n, tm, tn);
+    last_round_tile(a.tile, g.pc.r, g.base, g.tiles_m, g.tiles_n, tm, tn);
     // every piece spans `steps` steps; rows past V read as zero
-    const int32_t kb = a.piece * pc.steps * 64;
-    return Tile{tm * 256, tn * 256, kb, kb + pc.steps * 64};
+    const int32_t kb = a.piece * g.pc.steps * 64;
+    return Tile{tm * 256, tn * 256, kb, kb + g.pc.steps * 64};
   };
   auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) -> bool {
-    const Pieces::At a = pc.at(vid, (int32_t)gridDim.x);
+    const Pieces::At a = g.pc.at(vid, n_wg);
     if (!a.flush) return false;  // the tile's next piece follows on this workgroup
-    if (a.piece < pc.p)
-      store_dh(tile_of(vid), acc, Tn, d, cs, a.slot == 0 ? dH : part + (a.slot - 1) * slot_floats);
+    if (a.piece < g.pc.p)
+      store_dh(tile_of(vid), acc, g.Tn, g.d, g.cs,
+               a.slot == 0 ? g.dH : g.part + (a.slot - 1) * g.slot_floats);
     return true;
   };
-  tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, pc.q * (int32_t)gridDim.x, smem, tile_of,
-                                               epi);
+  tile_stream<GL, kMNMajor, kMNMajor, kDeepDh>(A, B, g.pc.q * n_wg, smem, tile_of, epi, wg, n_wg);
+}
+
+RBP_LOGITS_KERNEL void dhidden_pieces_kernel(DhArgs g) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
+  dhidden_pieces(g, smem, (int32_t)blockIdx.x, (int32_t)gridDim.x);
 }
 
 // dH += its tiles' slots of `part`, in slot order; one block per (tile, 4
@@ -310,20 +323,31 @@ __device__ __forceinline__ void dw_rows(const f32x16 (&acc)[GL::MI][GL::NI],
 // part_add_kernel adds afterwards -- the last, partly filled round of a
 // persistent launch done as one round of half-length tiles.  Columns of dz^T
 // past Tn are finite (the single pass) or zero, and meet zero rows of H.
-RBP_LOGITS_KERNEL void dweight_kernel(const uint16_t* __restrict__ Hc,
-                                      const uint16_t* __restrict__ Gt, int64_t ldGt, int64_t Tn,
-                                      int32_t d, int32_t V, float* __restrict__ dW, int accumulate,
-                                      int64_t tiles_m, int64_t tiles_n, int64_t tn_off,
-                                      int32_t vid_base, int32_t n_vid, int32_t split_steps,
-                                      float* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
+struct DwArgs {
+  const uint16_t* Hc;
+  const uint16_t* Gt;
+  int64_t ldGt, Tn;
+  int32_t d, V;
+  float* dW;
+  int32_t accumulate;
+  int64_t tiles_m, tiles_n, tn_off;
+  int32_t vid_base, n_vid, split_steps;
+  float* part;
+};
+
+__device__ __forceinline__ void dweight_tiles(const DwArgs& g, uint8_t* smem, int32_t wg,
+                                              int32_t n_wg) {
+  const int64_t Tn = g.Tn, tiles_m = g.tiles_m, tiles_n = g.tiles_n, tn_off = g.tn_off;
+  const int32_t d = g.d, V = g.V, accumulate = g.accumulate, split_steps = g.split_steps;
+  float* dW = g.dW;
+  float* part = g.part;
   const int64_t T8 = (Tn + 7) / 8 * 8;
-  const Operand A{Hc, d, d, Tn};        // (m = hidden unit, k = token): H[t][m]
-  const Operand B{Gt, ldGt, V, T8};     // (n = vocab, k = token): Gt[v][t]
+  const Operand A{g.Hc, d, d, Tn};        // (m = hidden unit, k = token): H[t][m]
+  const Operand B{g.Gt, g.ldGt, V, T8};   // (n = vocab, k = token): Gt[v][t]
   auto tile_of = [&](int32_t vid) {
     int32_t tm, tn;
     const int32_t half = split_steps > 0 ? (vid & 1) : 0;
-    const int32_t tv = vid_base + (split_steps > 0 ? vid >> 1 : vid);
+    const int32_t tv = g.vid_base + (split_steps > 0 ? vid >> 1 : vid);
     map_tile(tv, (int32_t)tiles_m, (int32_t)tiles_n, kGroupDw, tm, tn);
     const int32_t kb = half * split_steps * 64;
     return Tile{tm * 256, (tn + (int32_t)tn_off) * 256, kb,
@@ -365,7 +389,25 @@ RBP_LOGITS_KERNEL void dweight_kernel(const uint16_t* __restrict__ Hc,
         }
       }
   };
-  tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, n_vid, smem, tile_of, epi);
+  tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, g.n_vid, smem, tile_of, epi, wg, n_wg);
+}
+
+RBP_LOGITS_KERNEL void dweight_kernel(DwArgs g) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
+  dweight_tiles(g, smem, (int32_t)blockIdx.x, (int32_t)gridDim.x);
+}
+
+// Both products of a small batch in one launch: workgroups below n_dw take a
+// dW tile each, the others dhidden's pieces.  Neither needs the other's result
+// and neither fills the chip, so together they take as long as the longer one
+// (each is bound by the latency of its own chain of K steps and its stores).
+RBP_LOGITS_KERNEL void grad_both_kernel(DwArgs w, DhArgs h, int32_t n_dw) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
+  const int32_t b = (int32_t)blockIdx.x;
+  if (b < n_dw)
+    dweight_tiles(w, smem, b, n_dw);
+  else
+    dhidden_pieces(h, smem, b - n_dw, (int32_t)gridDim.x - n_dw);
 }
 
 // dW += part[i] over the tiles vid_base + i (i < n_tiles) of a split
@@ -403,6 +445,11 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(float* __restrict__ p, i
 }
 
 
+
+inline void launch_part_add(const DhArgs& g, hipStream_t s) {
+  hipLaunchKernelGGL(part_add_dh_kernel, dim3((unsigned)g.pc.r, 64), dim3(256), 0, s, g.dH, g.part,
+                     g.slot_floats, g.base, g.pc, g.tiles_m, g.tiles_n, g.d, g.Tn);
+}
 
 // Backward workspace carving: dz^T [Vp][T256] bf16, then scratch for partial
 // sums, [T256][d] fp32 at least.
@@ -446,14 +493,16 @@ void rbp::launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, i
   const bool split = tiles > grid && rem > 0 && 2 * rem <= grid && nk >= 8 &&
                      scratch != nullptr && rem * 65536 <= scratch_floats;
   const int64_t n_main = split ? tiles - rem : tiles;
-  hipLaunchKernelGGL(dweight_kernel, dim3(grid), dim3(GL::kThreads), 0, s, Hc, Gt, ldGt, Tn, d,
-                     V, dW, accumulate, tiles_d, tiles_n, tn_begin, 0, (int32_t)n_main, 0,
-                     (float*)nullptr);
+  DwArgs g{Hc,      Gt,       ldGt, Tn, d, V, dW, accumulate, tiles_d, tiles_n, tn_begin, 0,
+           (int32_t)n_main, 0,  nullptr};
+  hipLaunchKernelGGL(dweight_kernel, dim3(grid), dim3(GL::kThreads), 0, s, g);
   if (!split) return;
-  const int32_t half_steps = (int32_t)((nk + 1) / 2);
+  g.vid_base = (int32_t)n_main;
+  g.n_vid = (int32_t)(2 * rem);
+  g.split_steps = (int32_t)((nk + 1) / 2);
+  g.part = scratch;
   hipLaunchKernelGGL(dweight_kernel, dim3(rbp::gemm::stream_grid(2 * rem, device_cus())),
-                     dim3(GL::kThreads), 0, s, Hc, Gt, ldGt, Tn, d, V, dW, accumulate, tiles_d,
-                     tiles_n, tn_begin, (int32_t)n_main, (int32_t)(2 * rem), half_steps, scratch);
+                     dim3(GL::kThreads), 0, s, g);
   hipLaunchKernelGGL(part_add_kernel, dim3((unsigned)rem, 16), dim3(256), 0, s, dW, scratch,
                      (int32_t)n_main, tiles_d, tiles_n, tn_begin, d, V);
 }
@@ -473,12 +522,42 @@ void rbp::launch_dhidden(const uint16_t* W, const uint16_t* Gt, int64_t ldGt, in
                        dim3(GL::kThreads), 0, s, W, Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d,
                        tiles_t, (int32_t)n_main);
   if (pc.p > 1) {
+    const DhArgs g{W,       Gt,      ldGt,            Tn, d,       V,          cs, dhidden_c,
+                   tiles_d, tiles_t, (int32_t)n_main, pc, scratch, slot_floats};
     hipLaunchKernelGGL(dhidden_pieces_kernel, dim3((unsigned)pc.workgroups()),
-                       dim3(GL::kThreads), 0, s, W, Gt, ldGt, Tn, d, V, cs, dhidden_c, tiles_d,
-                       tiles_t, (int32_t)n_main, pc, scratch, slot_floats);
-    hipLaunchKernelGGL(part_add_dh_kernel, dim3((unsigned)r, 64), dim3(256), 0, s, dhidden_c,
-                       scratch, slot_floats, (int32_t)n_main, pc, tiles_d, tiles_t, d, Tn);
+                       dim3(GL::kThreads), 0, s, g);
+    launch_part_add(g, s);
   }
+}
+
+bool rbp::launch_both_products(const uint16_t* Hc, const uint16_t* W, const uint16_t* Gt,
+                               int64_t ldGt, int64_t Tn, int32_t d, int32_t V, float* dhidden_c,
+                               float* dW, int accumulate, hipStream_t s, float* scratch,
+                               int64_t scratch_floats, const float* cs) {
+  const int64_t tiles_d = rbp::ceil_div(d, 256), tiles_t = rbp::ceil_div(Tn, 256);
+  const int64_t tiles_v = rbp::ceil_div(V, 256);
+  const int64_t G = rbp::gemm::stream_grid(int64_t(1) << 30, device_cus());
+  // one dW tile per workgroup, the rest of a round for dhidden; whole groups
+  // of 8 keep a workgroup's number and its XCD together
+  const int64_t n_dw = (tiles_d * tiles_v + 7) / 8 * 8, r = tiles_d * tiles_t;
+  if (n_dw >= G || r > G - n_dw) return false;
+  const int64_t slot_floats = Tn * d, max_slots = scratch_floats / slot_floats;
+  const int64_t nk_v = rbp::ceil_div(V, 64), nk_t = rbp::ceil_div(Tn, 64);
+  const Pieces alone = plan_pieces(r, nk_v, G, max_slots);
+  const Pieces pc = plan_pieces(r, nk_v, G - n_dw, max_slots);
+  // In K steps (about 1 us): the two in turn, each with a launch and an
+  // epilogue of about 12, against the longer of the two.
+  const int64_t in_turn = nk_t + 12 + (int64_t)alone.q * alone.steps + 12;
+  const int64_t dw = nk_t + 12, dh = (int64_t)pc.q * pc.steps + 12;
+  if ((dw > dh ? dw : dh) >= in_turn) return false;
+  const DwArgs w{Hc,      Gt,      ldGt, Tn, d, V, dW, accumulate, tiles_d, tiles_v, 0, 0,
+                 (int32_t)(tiles_d * tiles_v), 0, nullptr};
+  const DhArgs h{W,       Gt,      ldGt, Tn, d,       V,          cs, dhidden_c,
+                 tiles_d, tiles_t, 0,    pc, scratch, slot_floats};
+  hipLaunchKernelGGL(grad_both_kernel, dim3((unsigned)(n_dw + pc.workgroups())),
+                     dim3(GL::kThreads), 0, s, w, h, (int32_t)n_dw);
+  if (pc.p > 1) launch_part_add(h, s);
+  return true;
 }
 
 size_t rbp::dhidden_extra(int64_t T256, int32_t d, int32_t V, size_t free_bytes, size_t base,
@@ -509,6 +588,9 @@ void rbp::launch_grad_products(const uint16_t* Hc, const uint16_t* W, const uint
     }
     return;
   }
+  if (launch_both_products(Hc, W, Gt, ldGt, Tn, d, V, dhidden_c, dW, accumulate, s, scratch,
+                           scratch_floats))
+    return;
   launch_dhidden(W, Gt, ldGt, Tn, d, V, dhidden_c, s, scratch, scratch_floats);
   // the scratch is free again once dhidden's sum has read it
   launch_dweight(Hc, Gt, ldGt, Tn, d, V, dW, accumulate, 0, round256(V) / 256, s, scratch,

@@ -59,6 +59,12 @@ void launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, int64_
 void launch_dhidden(const uint16_t* W, const uint16_t* Gt, int64_t ldGt, int64_t Tn, int32_t d,
                     int32_t V, float* dhidden_c, hipStream_t s, float* scratch,
                     int64_t scratch_floats, const float* cs = nullptr);
+// Both in one launch where neither fills the chip (small batches); false, and
+// nothing launched, where they had better run in turn.
+bool launch_both_products(const uint16_t* Hc, const uint16_t* W, const uint16_t* Gt, int64_t ldGt,
+                          int64_t Tn, int32_t d, int32_t V, float* dhidden_c, float* dW,
+                          int accumulate, hipStream_t s, float* scratch, int64_t scratch_floats,
+                          const float* cs = nullptr);
 
 // Workspace bytes to ask for beyond `base`, the least a chunk of T256 tokens
 // (a multiple of 256) runs with and whose last `free_bytes` are scratch by
