@@ -5,7 +5,7 @@ replay-buffer sample-and-gather, per-token policy log-probabilities from final
 hidden states and the LM head (bf16 MFMA with an online log-sum-exp), the
 clipped importance-weighted GRPO loss with group advantages, and the backward
 to the hidden states and the LM head.  All compute is in librbpolicy.so
-(hand-written HIP); this package is a thin ctypes binding over its C ABI
+(hand-written HIP); this package is a thin binding over its C ABI
 (include/rbpolicy.h) and uses torch only for device memory and streams.
 """
 

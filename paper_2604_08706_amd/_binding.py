@@ -1,9 +1,11 @@
-"""ctypes binding of librbpolicy.so (see include/rbpolicy.h).
+"""Binding of librbpolicy.so (see include/rbpolicy.h).
 
 Argument marshalling only: every entry point checks the torch tensors it is
 given (device, dtype, contiguity, size), passes raw device pointers and the
 current HIP stream to the C ABI, and raises ``RbpError`` on a nonzero status.
-All computation happens in the library's HIP kernels; there is no fallback.
+The checks and the call are native (csrc/marshal.cpp, the _marshal module); the
+structs, workspace sizes and status texts go through ctypes.  All computation
+happens in the library's HIP kernels; there is no fallback.
 """
 
 import ctypes
@@ -162,6 +164,24 @@ def lib():
     return _LIB
 
 
+_N = None
+
+
+def _native():
+    """The _marshal module (built beside the library).  Raises if missing."""
+    global _N
+    if _N is None:
+        lib()
+        try:
+            from . import _marshal
+        except ImportError as e:
+            raise ImportError("_marshal.so is missing or unusable: build it with "
+                              "`python -m paper_2604_08706_amd.build`") from e
+        _marshal.set_structs(RbRecords, RbSampleCfg, RbRing, RbpExec)
+        _N = _marshal
+    return _N
+
+
 def _check(fn, status):
     if status != RBP_OK:
         detail = lib().rbp_last_error().decode() or lib().rbp_status_string(status).decode()
@@ -186,18 +206,6 @@ def _opt(t, dtype, name, numel=None):
     return ctypes.c_void_p(0) if t is None else _dev(t, dtype, name, numel)
 
 
-def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
-
-
-def _ws(ws):
-    if ws is None:
-        return ctypes.c_void_p(0), 0
-    _dev(ws, ws.dtype, "ws")
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
-
-
 def rbp_workspace_bytes(op, n, d=0, V=0):
     return int(lib().rbp_workspace_bytes(op, n, d, V))
 
@@ -209,12 +217,9 @@ def workspace(op, n, d=0, V=0, device="cuda"):
 
 
 def rb_group_advantage(reward, group_off, adv, ddof=1, eps=1e-6, stream=None):
-    n_groups = group_off.numel() - 1
-    st = lib().rb_group_advantage(_dev(reward, torch.float32, "reward"),
-                                  _dev(group_off, torch.int32, "group_off"), n_groups,
-                                  ddof, eps, _dev(adv, torch.float32, "adv", reward.numel()),
-                                  _stream(stream))
-    _check("rb_group_advantage", st)
+    st = (_N or _native()).group_advantage(reward, group_off, adv, ddof, eps, stream)
+    if st:
+        _check("rb_group_advantage", st)
 
 
 def make_records(n_live, capacity, head, arena_off, length, reward, advantage, version,
@@ -241,14 +246,9 @@ def make_records(n_live, capacity, head, arena_off, length, reward, advantage, v
 
 def make_sample_cfg(mode, layout, seed, step, n_draw, p_pos_q32=0, n_fresh=0, n_pos_keep=0,
                     cur_version=0, max_tokens=0, token_begin=0, l_max=0):
-    cfg = RbSampleCfg()
-    cfg.mode, cfg.layout = int(mode), int(layout)
-    cfg.seed, cfg.step = int(seed), int(step)
-    cfg.n_draw, cfg.p_pos_q32 = int(n_draw), int(p_pos_q32)
-    cfg.n_fresh, cfg.n_pos_keep = int(n_fresh), int(n_pos_keep)
-    cfg.cur_version = int(cur_version)
-    cfg.max_tokens, cfg.token_begin, cfg.l_max = int(max_tokens), int(token_begin), int(l_max)
-    return cfg
+    return RbSampleCfg(int(mode), int(layout), int(seed), int(step), int(n_draw), int(p_pos_q32),
+                       int(n_fresh), int(n_pos_keep), int(cur_version), 0, int(max_tokens),
+                       int(token_begin), int(l_max))
 
 
 def alloc_batch(cfg, device="cuda"):
@@ -269,132 +269,64 @@ def alloc_batch(cfg, device="cuda"):
     }
 
 
-def _batch(cfg, out):
-    n = cfg.n_draw
-    width = cfg.max_tokens if cfg.layout == RB_LAYOUT_PACKED else n * cfg.l_max
-    b = RbBatch()
-    b.idx = _dev(out["idx"], torch.int32, "idx", n).value
-    b.adv = _dev(out["adv"], torch.float32, "adv", n).value
-    b.len = _dev(out["len"], torch.int32, "len", n).value
-    b.age = _dev(out["age"], torch.int32, "age", n).value
-    b.cu_seqlens = _dev(out["cu_seqlens"], torch.int32, "cu_seqlens", n + 1).value
-    b.tokens = _dev(out["tokens"], torch.int32, "tokens", width).value
-    b.old_logp = _dev(out["old_logp"], torch.float32, "old_logp", width).value
-    b.seq_of_token = _dev(out["seq_of_token"], torch.int32, "seq_of_token", width).value
-    b.n_tokens = _dev(out["n_tokens"], torch.int64, "n_tokens", 1).value
-    return b
-
-
 def rb_sample_gather(rec, cfg, out, ws, stream=None):
-    b = _batch(cfg, out)
-    wsp, wsb = _ws(ws)
-    st = lib().rb_sample_gather(ctypes.byref(rec), ctypes.byref(cfg), ctypes.byref(b), wsp,
-                                wsb, _stream(stream))
-    _check("rb_sample_gather", st)
+    st = (_N or _native()).sample_gather(rec, cfg, out, ws, stream)
+    if st:
+        _check("rb_sample_gather", st)
 
 
 def rb_sample_gather_noalloc(rec, cfg, out, stream=None):
     """rb_sample_gather with the library's static per-GPU scratch as its
     workspace (no workspace tensor; calls on one GPU must not overlap)."""
-    b = _batch(cfg, out)
-    st = lib().rb_sample_gather_noalloc(ctypes.byref(rec), ctypes.byref(cfg), ctypes.byref(b),
-                                        _stream(stream))
-    _check("rb_sample_gather_noalloc", st)
-
-
-def _bf16_bits(t, name, numel):
-    _dev(t, torch.bfloat16, name, numel)
-    return ctypes.c_void_p(t.data_ptr())
+    st = (_N or _native()).sample_gather_noalloc(rec, cfg, out, stream)
+    if st:
+        _check("rb_sample_gather_noalloc", st)
 
 
 def policy_logprob_fwd(hidden, W, tokens, seq_of_token, logp, lse, ws, stream=None):
-    T, d = hidden.shape
-    V = W.shape[0]
-    if W.shape[1] != d:
-        raise ValueError("hidden and W disagree on d")
-    wsp, wsb = _ws(ws)
-    st = lib().policy_logprob_fwd(_bf16_bits(hidden, "hidden", T * d), _bf16_bits(W, "W", V * d),
-                                  _dev(tokens, torch.int32, "tokens", T),
-                                  _opt(seq_of_token, torch.int32, "seq_of_token", T), T, d, V,
-                                  _dev(logp, torch.float32, "logp", T),
-                                  _dev(lse, torch.float32, "lse", T), wsp, wsb, _stream(stream))
-    _check("policy_logprob_fwd", st)
+    st = (_N or _native()).logprob_fwd(hidden, W, tokens, seq_of_token, logp, lse, ws, stream)
+    if st:
+        _check("policy_logprob_fwd", st)
 
 
 def policy_loss_fwd_bwd(logp, old_logp, seq_of_token, adv, seq_len, n_seq_total, loss_accum,
                         dlogp, stats, ws, eps_low=0.2, eps_high=0.2, stream=None):
-    T = logp.numel()
-    B = adv.numel()
-    wsp, wsb = _ws(ws)
-    st = lib().policy_loss_fwd_bwd(_dev(logp, torch.float32, "logp", T),
-                                   _dev(old_logp, torch.float32, "old_logp", T),
-                                   _dev(seq_of_token, torch.int32, "seq_of_token", T),
-                                   _dev(adv, torch.float32, "adv", B),
-                                   _dev(seq_len, torch.int32, "seq_len", B), T, B,
-                                   int(n_seq_total), eps_low, eps_high,
-                                   _dev(loss_accum, torch.float32, "loss_accum", 1),
-                                   _dev(dlogp, torch.float32, "dlogp", T),
-                                   _dev(stats, torch.float32, "stats", 4), wsp, wsb,
-                                   _stream(stream))
-    _check("policy_loss_fwd_bwd", st)
+    st = (_N or _native()).loss_fwd_bwd(logp, old_logp, seq_of_token, adv, seq_len,
+                                        int(n_seq_total), loss_accum, dlogp, stats, ws, eps_low,
+                                        eps_high, stream)
+    if st:
+        _check("policy_loss_fwd_bwd", st)
 
 
 def policy_loss_seq_fwd_bwd(logp, old_logp, cu_seqlens, adv, n_seq_total, loss_accum, dlogp,
                             stats, ws, eps_low=0.2, eps_high=0.2, stream=None):
-    T = logp.numel()
-    B = adv.numel()
-    wsp, wsb = _ws(ws)
-    st = lib().policy_loss_seq_fwd_bwd(_dev(logp, torch.float32, "logp", T),
-                                       _dev(old_logp, torch.float32, "old_logp", T),
-                                       _dev(cu_seqlens, torch.int32, "cu_seqlens", B + 1),
-                                       _dev(adv, torch.float32, "adv", B), T, B,
-                                       int(n_seq_total), eps_low, eps_high,
-                                       _dev(loss_accum, torch.float32, "loss_accum", 1),
-                                       _dev(dlogp, torch.float32, "dlogp", T),
-                                       _dev(stats, torch.float32, "stats", 4), wsp, wsb,
-                                       _stream(stream))
-    _check("policy_loss_seq_fwd_bwd", st)
+    st = (_N or _native()).loss_seq_fwd_bwd(logp, old_logp, cu_seqlens, adv, int(n_seq_total),
+                                            loss_accum, dlogp, stats, ws, eps_low, eps_high,
+                                            stream)
+    if st:
+        _check("policy_loss_seq_fwd_bwd", st)
 
 
 def rb_asymre_coef(reward, group_off, coef, delta_v=-0.1, stream=None):
-    n_groups = group_off.numel() - 1
-    st = lib().rb_asymre_coef(_dev(reward, torch.float32, "reward"),
-                              _dev(group_off, torch.int32, "group_off"), n_groups,
-                              float(delta_v), _dev(coef, torch.float32, "coef", reward.numel()),
-                              _stream(stream))
-    _check("rb_asymre_coef", st)
+    st = (_N or _native()).asymre_coef(reward, group_off, coef, float(delta_v), stream)
+    if st:
+        _check("rb_asymre_coef", st)
 
 
 def policy_asymre_fwd_bwd(logp, seq_of_token, coef, n_seq_total, loss_accum, dlogp, stats, ws,
                           stream=None):
-    T = logp.numel()
-    B = coef.numel()
-    wsp, wsb = _ws(ws)
-    st = lib().policy_asymre_fwd_bwd(_dev(logp, torch.float32, "logp", T),
-                                     _dev(seq_of_token, torch.int32, "seq_of_token", T),
-                                     _dev(coef, torch.float32, "coef", B), T, B,
-                                     int(n_seq_total),
-                                     _dev(loss_accum, torch.float32, "loss_accum", 1),
-                                     _dev(dlogp, torch.float32, "dlogp", T),
-                                     _dev(stats, torch.float32, "stats", 2), wsp, wsb,
-                                     _stream(stream))
-    _check("policy_asymre_fwd_bwd", st)
+    st = (_N or _native()).asymre_fwd_bwd(logp, seq_of_token, coef, int(n_seq_total), loss_accum,
+                                          dlogp, stats, ws, stream)
+    if st:
+        _check("policy_asymre_fwd_bwd", st)
 
 
 def policy_logprob_bwd(hidden, W, tokens, seq_of_token, lse, dlogp, dhidden, dW, ws,
                        accumulate_dW=False, stream=None):
-    T, d = hidden.shape
-    V = W.shape[0]
-    wsp, wsb = _ws(ws)
-    st = lib().policy_logprob_bwd(_bf16_bits(hidden, "hidden", T * d), _bf16_bits(W, "W", V * d),
-                                  _dev(tokens, torch.int32, "tokens", T),
-                                  _opt(seq_of_token, torch.int32, "seq_of_token", T),
-                                  _dev(lse, torch.float32, "lse", T),
-                                  _dev(dlogp, torch.float32, "dlogp", T), T, d, V,
-                                  _dev(dhidden, torch.float32, "dhidden", T * d),
-                                  _dev(dW, torch.float32, "dW", V * d),
-                                  1 if accumulate_dW else 0, wsp, wsb, _stream(stream))
-    _check("policy_logprob_bwd", st)
+    st = (_N or _native()).logprob_bwd(hidden, W, tokens, seq_of_token, lse, dlogp, dhidden, dW,
+                                       ws, 1 if accumulate_dW else 0, stream)
+    if st:
+        _check("policy_logprob_bwd", st)
 
 
 def _event_handle(ev, stream):
@@ -423,30 +355,12 @@ def policy_fused_fwd_bwd(hidden, W, tokens, seq_of_token, old_logp, adv, seq_len
                          accumulate_dW=False, eps_low=0.2, eps_high=0.2, exec=None,
                          stream=None):
     """exec: None or an RbpExec of phase events (make_exec)."""
-    T, d = hidden.shape
-    V = W.shape[0]
-    B = adv.numel()
-    wsp, wsb = _ws(ws)
-    st = lib().policy_fused_fwd_bwd(_bf16_bits(hidden, "hidden", T * d),
-                                    _bf16_bits(W, "W", V * d),
-                                    _dev(tokens, torch.int32, "tokens", T),
-                                    _dev(seq_of_token, torch.int32, "seq_of_token", T),
-                                    _dev(old_logp, torch.float32, "old_logp", T),
-                                    _dev(adv, torch.float32, "adv", B),
-                                    _dev(seq_len, torch.int32, "seq_len", B), T, d, V, B,
-                                    int(n_seq_total), eps_low, eps_high,
-                                    _dev(logp, torch.float32, "logp", T),
-                                    _dev(lse, torch.float32, "lse", T),
-                                    _opt(entropy, torch.float32, "entropy", T),
-                                    _dev(loss_accum, torch.float32, "loss_accum", 1),
-                                    _dev(dlogp, torch.float32, "dlogp", T),
-                                    _dev(stats, torch.float32, "stats", 4),
-                                    _dev(dhidden, torch.float32, "dhidden", T * d),
-                                    _dev(dW, torch.float32, "dW", V * d),
-                                    1 if accumulate_dW else 0, wsp, wsb,
-                                    None if exec is None else ctypes.byref(exec),
-                                    _stream(stream))
-    _check("policy_fused_fwd_bwd", st)
+    st = (_N or _native()).fused_fwd_bwd(hidden, W, tokens, seq_of_token, old_logp, adv, seq_len,
+                                         int(n_seq_total), logp, lse, entropy, loss_accum, dlogp,
+                                         stats, dhidden, dW, ws, 1 if accumulate_dW else 0,
+                                         eps_low, eps_high, exec, stream)
+    if st:
+        _check("policy_fused_fwd_bwd", st)
 
 
 def make_ring(capacity, slot_tokens, device="cuda", counters=True, replay_bins=0):
@@ -490,31 +404,20 @@ def ring_records(ring):
 
 def rb_push(ring, group_off, length, src_off, reward, version, tokens, old_logp, ddof=1,
             eps=1e-6, stream=None):
-    n_new = length.numel()
-    n_groups = group_off.numel() - 1
-    st = lib().rb_push(ctypes.byref(ring), n_new, n_groups,
-                       _dev(group_off, torch.int32, "group_off", n_groups + 1),
-                       _dev(length, torch.int32, "length", n_new),
-                       _dev(src_off, torch.int64, "src_off", n_new),
-                       _dev(reward, torch.float32, "reward", n_new), int(version),
-                       _dev(tokens, torch.int32, "tokens"),
-                       _dev(old_logp, torch.float32, "old_logp"), int(ddof), float(eps),
-                       _stream(stream))
-    _check("rb_push", st)
+    st = (_N or _native()).push(ring, group_off, length, src_off, reward, int(version), tokens,
+                                old_logp, int(ddof), float(eps), stream)
+    if st:
+        _check("rb_push", st)
 
 
 def rb_note_use(idx, head, capacity, step, use_count, last_step, since, ws, stream=None):
-    n = idx.numel()
-    wsp, wsb = _ws(ws)
-    st = lib().rb_note_use(_dev(idx, torch.int32, "idx", n), n, int(head), int(capacity),
-                           int(step), _dev(use_count, torch.int32, "use_count", capacity),
-                           _dev(last_step, torch.int64, "last_step", capacity),
-                           _opt(since, torch.int32, "since", n), wsp, wsb, _stream(stream))
-    _check("rb_note_use", st)
+    st = (_N or _native()).note_use(idx, int(head), int(capacity), int(step), use_count,
+                                    last_step, since, ws, stream)
+    if st:
+        _check("rb_note_use", st)
 
 
 def rb_hist_accumulate(values, hist, lo=0, stream=None):
-    n = values.numel()
-    st = lib().rb_hist_accumulate(_dev(values, torch.int32, "values", n), n, int(lo),
-                                  hist.numel(), _dev(hist, torch.int64, "hist"), _stream(stream))
-    _check("rb_hist_accumulate", st)
+    st = (_N or _native()).hist_accumulate(values, hist, int(lo), stream)
+    if st:
+        _check("rb_hist_accumulate", st)

@@ -1,9 +1,11 @@
-"""Build librbpolicy.so (HIP, gfx950 only) in-tree.
+"""Build librbpolicy.so (HIP, gfx950 only) and the binding's _marshal module in-tree.
 
     python -m paper_2604_08706_amd.build         # or: python paper_2604_08706_amd/build.py
 
 Every .hip file under csrc/ is compiled to an object with hipcc and the
-objects are linked into paper_2604_08706_amd/librbpolicy.so.  Compiling for
+objects are linked into paper_2604_08706_amd/librbpolicy.so.  csrc/marshal.cpp,
+host code against the torch and Python headers, is compiled with g++ and
+linked with the library into paper_2604_08706_amd/_marshal.so.  Compiling for
 gfx950 needs no GPU, so this runs on any machine with ROCm installed.
 """
 
@@ -11,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +22,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "librbpolicy.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 ARCH = "gfx950"
 FLAGS = [
@@ -49,19 +53,57 @@ def _compile(src, extra):
     return obj
 
 
+def _torch_root():
+    import importlib.util
+
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def _run(cmd, what):
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{what} failed:\n{r.stderr}")
+
+
+def _compile_marshal():
+    """Object of csrc/marshal.cpp."""
+    inc = os.path.join(_torch_root(), "include")
+    obj = os.path.join(OBJDIR, "marshal.cpp.o")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          f"-I{INCLUDE}", f"-I{sysconfig.get_paths()['include']}", "-isystem", inc, "-isystem",
+          os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem",
+          os.path.join(rocm, "include"), "-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj],
+         "g++ on marshal.cpp")
+    return obj
+
+
+def _link_marshal(obj):
+    """_marshal.so, next to the library it loads (torch's own are loaded by then)."""
+    tmp = MARSHAL + ".tmp"
+    _run(["g++", "-shared", obj, f"-L{PKG}", "-l:librbpolicy.so",
+          f"-L{os.path.join(_torch_root(), 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip",
+          "-lc10", "-Wl,-rpath,$ORIGIN", "-o", tmp], "linking _marshal.so")
+    os.replace(tmp, MARSHAL)
+
+
 def build(extra_flags=(), verbose=True):
-    """Compile every csrc/*.hip and link librbpolicy.so; returns its path."""
+    """Compile every csrc/*.hip and link librbpolicy.so (its path is returned),
+    then the _marshal module."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
-    workers = min(len(srcs), max(1, min(8, os.cpu_count() or 1)))
+    workers = min(len(srcs) + 1, max(1, min(8, os.cpu_count() or 1)))
     with ThreadPoolExecutor(workers) as ex:
+        marshal = ex.submit(_compile_marshal)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), srcs))
+        marshal_obj = marshal.result()
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     os.replace(tmp, LIB)
+    _link_marshal(marshal_obj)
     if verbose:
         print(f"built {LIB}")
     return LIB
