@@ -46,6 +46,7 @@
 
 #include "logits_epilogue.h"
 #include "loss_terms.h"
+#include "pieces.h"
 #include "rbp_internal.h"
 
 namespace {
@@ -510,7 +511,8 @@ size_t rbp::fused_ws(int64_t Tc, int32_t d, int32_t V) {
   const int32_t dd = d < 1 ? 1 : d, VV = V < 1 ? 1 : V;
   const FusedWs w = carve_fused(nullptr, T256, dd, VV);
   return w.bytes + dhidden_extra(T256, dd, VV, w.bytes - w.hp_at, w.bytes,
-                                 carve_fused(nullptr, T256 + 256, dd, VV).bytes);
+                                 carve_fused(nullptr, T256 + 256, dd, VV).bytes,
+                                 rbp::gemm::kMinSteps);
 }
 
 namespace {

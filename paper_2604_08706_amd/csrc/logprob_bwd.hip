@@ -262,25 +262,49 @@ __global__ void __launch_bounds__(256) part_add_dh_kernel(float* __restrict__ dH
 // for 1301 tokens, 1.66 ms this way, and 14.50 / 14.45 ms for 16384; without
 // accumulation into d = 1536, V = 151936, 4096 tokens 1.12 -> 0.96 ms.
 //
-// Rows go through a buffer resource over the tile: one offset per lane and
-// 32-column block, columns past d pointing beyond the range (loads read 0,
-// stores are dropped), and the row as the scalar offset -- or, in the last
-// vocabulary tile (kTail), inside the lane's offset, which the range check
-// then covers, so that rows past V are dropped too.
+// Rows go through a buffer resource over the tile, one offset per lane and
+// 32-column block; columns past d point beyond the range (loads read 0, stores
+// are dropped).  Inside the matrix the row is the scalar offset.  In a tile
+// that ends past the vocabulary or past d (kTail) it is part of the lane's
+// offset, which the range check covers, so that rows past V are dropped too,
+// and blocks of columns past d are left out (d = 64: 6 of 8).
 template <bool kTail>
 __device__ __forceinline__ void dw_rows(const f32x16 (&acc)[GL::MI][GL::NI],
                                         float* __restrict__ dW, const Tile& tile, int32_t d,
                                         int32_t V, int accumulate) {
-  const int64_t rows = kTail ? V - tile.n0 : 256;
+  const int64_t left = V - tile.n0, rows = left < 256 ? left : 256;
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
       uniform_ptr(dW + (int64_t)tile.n0 * d + tile.m0), 0,
       (int)(((rows - 1) * d + (d - tile.m0)) * 4), 0x00020000);
+  auto lane_offset = [&](int mi) {
+    const int m = GL::out_m(mi) + GL::lane_m();
+    return tile.m0 + m < d ? (uint32_t)(GL::lane_n() * d + m) * 4u : rbp::gemm::kOutOfRange;
+  };
+  if constexpr (kTail) {
+#pragma unroll
+    for (int mi = 0; mi < GL::MI; ++mi) {
+      if (tile.m0 + GL::out_m(mi) >= d) continue;
+      const uint32_t at = lane_offset(mi);
+#pragma unroll
+      for (int ni = 0; ni < GL::NI; ++ni) {
+        float o[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          o[r] = !accumulate ? 0.0f
+                             : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                   rsrc, at + GL::out_n(ni, r) * d * 4, 0, 0));
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mi][ni][r] + o[r]), rsrc,
+                                                at + GL::out_n(ni, r) * d * 4, 0, 0);
+        asm volatile("" ::: "memory");
+      }
+    }
+    return;
+  }
   uint32_t at[GL::MI];
 #pragma unroll
-  for (int mi = 0; mi < GL::MI; ++mi) {
-    const int m = GL::out_m(mi) + GL::lane_m();
-    at[mi] = tile.m0 + m < d ? (uint32_t)(GL::lane_n() * d + m) * 4u : rbp::gemm::kOutOfRange;
-  }
+  for (int mi = 0; mi < GL::MI; ++mi) at[mi] = lane_offset(mi);
 #pragma unroll
   for (int ni = 0; ni < GL::NI; ++ni)
 #pragma unroll
@@ -290,39 +314,24 @@ __device__ __forceinline__ void dw_rows(const f32x16 (&acc)[GL::MI][GL::NI],
       // time the same)
       float o[kDwRows][GL::MI];
 #pragma unroll
-      for (int k = 0; k < kDwRows; ++k) {
-        const int row = GL::out_n(ni, rb + k) * d * 4;
+      for (int k = 0; k < kDwRows; ++k)
 #pragma unroll
         for (int mi = 0; mi < GL::MI; ++mi)
           o[k][mi] = !accumulate ? 0.0f
                                  : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                                       rsrc, kTail ? at[mi] + row : at[mi], kTail ? 0 : row, 0));
-      }
+                                       rsrc, at[mi], GL::out_n(ni, rb + k) * d * 4, 0));
 #pragma unroll
-      for (int k = 0; k < kDwRows; ++k) {
-        const int row = GL::out_n(ni, rb + k) * d * 4;
+      for (int k = 0; k < kDwRows; ++k)
 #pragma unroll
         for (int mi = 0; mi < GL::MI; ++mi)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mi][ni][rb + k] + o[k][mi]),
-                                                rsrc, kTail ? at[mi] + row : at[mi],
-                                                kTail ? 0 : row, 0);
-      }
+                                                rsrc, at[mi], GL::out_n(ni, rb + k) * d * 4, 0);
       // keeps the next rows' loads below these stores (the compiler would
       // otherwise hoist them all)
       asm volatile("" ::: "memory");
     }
 }
 
-// Backward step 3: dW[v][m] (+)= sum_t H[t][m] dz[t][v], with A = H read
-// MN-major (m contiguous, k = token) and B = dz^T K-major (rows v, k = token).
-// The launch covers n_vid of the tiles of the vocabulary range [tn_off,
-// tn_off + tiles_n), from virtual tile vid_base on.  With split_steps > 0
-// each of them is done in two K halves of split_steps steps (virtual block
-// 2 i + h = half h of tile vid_base + i): half 0 updates dW, half 1 writes
-// its raw sums to part[i] (a 256 x 256 fp32 block, [v][m]), which
-// part_add_kernel adds afterwards -- the last, partly filled round of a
-// persistent launch done as one round of half-length tiles.  Columns of dz^T
-// past Tn are finite (the single pass) or zero, and meet zero rows of H.
 struct DwArgs {
   const uint16_t* Hc;
   const uint16_t* Gt;
@@ -368,7 +377,7 @@ __device__ __forceinline__ void dweight_tiles(const DwArgs& g, uint8_t* smem, in
       return;
     }
     if (d <= kMaxBufferD) {
-      if (tile.n0 + 256 <= V)
+      if (tile.n0 + 256 <= V && tile.m0 + 256 <= d)
         dw_rows<false>(acc, dW, tile, d, V, accumulate);
       else
         dw_rows<true>(acc, dW, tile, d, V, accumulate);
@@ -475,8 +484,9 @@ size_t rbp::logprob_bwd_ws(int64_t Tc, int32_t d, int32_t V) {
   const int64_t T256 = round256(Tc < 1 ? 1 : Tc);
   const int32_t dd = d < 1 ? 1 : d;
   const BwdWs w = carve_bwd(nullptr, T256, dd, V);
+  // pieces of 8 steps: heads of up to 1024 words ask for no more than ever
   return w.bytes + dhidden_extra(T256, dd, V, w.bytes - w.scratch_at, w.bytes,
-                                 carve_bwd(nullptr, T256 + 256, dd, V).bytes);
+                                 carve_bwd(nullptr, T256 + 256, dd, V).bytes, 8);
 }
 
 void rbp::launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, int64_t Tn,
@@ -561,14 +571,14 @@ bool rbp::launch_both_products(const uint16_t* Hc, const uint16_t* W, const uint
 }
 
 size_t rbp::dhidden_extra(int64_t T256, int32_t d, int32_t V, size_t free_bytes, size_t base,
-                          size_t next) {
+                          size_t next, int64_t min_steps) {
   // sized for the 256 compute units of an MI355X, 64 MiB of partial sums at
   // most (one 256 x 256 block per unit)
   constexpr int64_t kUnits = 256;
   const int64_t slot = T256 * (int64_t)d * 4;
   const int64_t tiles = rbp::ceil_div(d, 256) * (T256 / 256);
   const Pieces pc = plan_pieces(tiles % kUnits, rbp::ceil_div(V, 64), kUnits,
-                                (kUnits << 18) / slot);
+                                (kUnits << 18) / slot, min_steps);
   const size_t want = (size_t)(pc.slots() * slot);
   if (want <= free_bytes) return 0;
   const size_t extra = align_up(want - free_bytes, 256);

@@ -75,16 +75,18 @@ struct Pieces {
 // slots fit in the scratch (p = 1: not cut).  Cost in K steps (about 1 us
 // each): the q pieces a workgroup runs, a second epilogue for a helper, and
 // the slots' addition -- one more launch, 256 KB read per tile and slot at
-// about 4 TB/s, and a chain of loads.  A piece keeps at least 8 steps, which
-// cover the latency of its first loads.
-inline Pieces plan_pieces(int64_t r, int64_t nk, int64_t G, int64_t max_slots) {
+// about 4 TB/s, and a chain of loads.  A piece keeps at least min_steps steps:
+// with fewer than 4 its first loads' latency outweighs them.
+constexpr int64_t kMinSteps = 4;
+inline Pieces plan_pieces(int64_t r, int64_t nk, int64_t G, int64_t max_slots,
+                          int64_t min_steps = kMinSteps) {
   Pieces best{(int32_t)r, 1, 1, 1, 0, (int32_t)nk};
   if (r <= 0 || r >= G || max_slots < 1) return best;
   double best_cost = (double)nk;
   for (int64_t q = 1; q <= 8; ++q) {
     int64_t p = q * G / r;
-    if (p > nk / 8) p = nk / 8;
-    for (; p > q; p -= 1 + p / 4) {
+    if (p > nk / min_steps) p = nk / min_steps;
+    for (; p > q; p -= 1 + p / 8) {
       Pieces c{(int32_t)r, (int32_t)p, (int32_t)q, (int32_t)(p / q), (int32_t)(p % q), 0};
       while (c.p > q && c.slots() > max_slots) {
         --c.p;
@@ -93,8 +95,10 @@ inline Pieces plan_pieces(int64_t r, int64_t nk, int64_t G, int64_t max_slots) {
       }
       if (c.p <= q) break;
       p = c.p;
+      if (q > 1 && c.rem == 0) continue;  // p / q pieces of one, in more parts
       c.steps = (int32_t)((nk + p - 1) / p);
-      const double cost = (double)(q * c.steps) + (c.rem ? 4.0 : 0.0) + 5.0 +
+      const double cost = (double)(q * c.steps) + 0.25 * (double)(q - 1) +
+                          (c.rem ? 4.0 : 0.0) + 5.0 +
                           c.slots() * (0.3 + 0.065 * (double)r);
       if (cost < best_cost) {
         best_cost = cost;

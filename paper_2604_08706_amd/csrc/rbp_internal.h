@@ -71,8 +71,9 @@ bool launch_both_products(const uint16_t* Hc, const uint16_t* W, const uint16_t*
 // the time dhidden runs: what its cut of a partly filled round can use.
 // Always less than one more 256-token granule (`next` = the base of T256 +
 // 256 tokens), so the chunk that fits a workspace of this size stays T256.
+// min_steps: K steps of the shortest piece to plan for.
 size_t dhidden_extra(int64_t T256, int32_t d, int32_t V, size_t free_bytes, size_t base,
-                     size_t next);
+                     size_t next, int64_t min_steps);
 
 }  // namespace rbp
 
