@@ -332,6 +332,15 @@ __device__ __forceinline__ void dw_rows(const f32x16 (&acc)[GL::MI][GL::NI],
     }
 }
 
+// Backward step 3: dW[v][m] (+)= sum_t H[t][m] dz[t][v], with A = H read
+// MN-major (m contiguous, k = token) and B = dz^T K-major (rows v, k = token).
+// The launch covers the first n_vid of the tiles of the vocabulary range
+// [tn_off, tn_off + tiles_n), or (kPieces) the last round of them, blocks base
+// .. base + r - 1 of the launch over every tile, cut along the tokens (Pieces)
+// where it would leave compute units idle: a tile's first share updates dW, the
+// others write their raw sums to slots of `part` (slot k of tile i: a 256 x 256
+// fp32 block, [v][m]), which part_add_kernel adds afterwards.  Columns of dz^T
+// past Tn are finite (the single pass) or zero, and meet zero rows of H.
 struct DwArgs {
   const uint16_t* Hc;
   const uint16_t* Gt;
@@ -340,42 +349,42 @@ struct DwArgs {
   float* dW;
   int32_t accumulate;
   int64_t tiles_m, tiles_n, tn_off;
-  int32_t vid_base, n_vid, split_steps;
+  int32_t n_vid;       // whole tiles
+  int32_t base;        // kPieces
+  Pieces pc;
   float* part;
 };
 
+// Tile i of the r tiles of a last round, as dhidden's last_round_tile.
+__device__ __forceinline__ void last_dw_tile(int32_t i, const DwArgs& g, int32_t& tm,
+                                             int32_t& tn) {
+  map_tile(g.base + (int32_t)xcd_block((uint32_t)i, (uint32_t)g.pc.r), (int32_t)g.tiles_m,
+           (int32_t)g.tiles_n, kGroupDw, tm, tn);
+}
+
+template <bool kPieces>
 __device__ __forceinline__ void dweight_tiles(const DwArgs& g, uint8_t* smem, int32_t wg,
                                               int32_t n_wg) {
-  const int64_t Tn = g.Tn, tiles_m = g.tiles_m, tiles_n = g.tiles_n, tn_off = g.tn_off;
-  const int32_t d = g.d, V = g.V, accumulate = g.accumulate, split_steps = g.split_steps;
+  const int64_t Tn = g.Tn, tn_off = g.tn_off;
+  const int32_t d = g.d, V = g.V, accumulate = g.accumulate;
   float* dW = g.dW;
-  float* part = g.part;
   const int64_t T8 = (Tn + 7) / 8 * 8;
   const Operand A{g.Hc, d, d, Tn};        // (m = hidden unit, k = token): H[t][m]
   const Operand B{g.Gt, g.ldGt, V, T8};   // (n = vocab, k = token): Gt[v][t]
   auto tile_of = [&](int32_t vid) {
-    int32_t tm, tn;
-    const int32_t half = split_steps > 0 ? (vid & 1) : 0;
-    const int32_t tv = g.vid_base + (split_steps > 0 ? vid >> 1 : vid);
-    map_tile(tv, (int32_t)tiles_m, (int32_t)tiles_n, kGroupDw, tm, tn);
-    const int32_t kb = half * split_steps * 64;
-    return Tile{tm * 256, (tn + (int32_t)tn_off) * 256, kb,
-                split_steps > 0 ? kb + split_steps * 64 : (int32_t)Tn};
-  };
-  auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) {
-    const Tile tile = tile_of(vid);
-    if (split_steps > 0 && (vid & 1)) {
-      float* blk = part + (int64_t)(vid >> 1) * 65536;
-#pragma unroll
-      for (int ni = 0; ni < GL::NI; ++ni)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-#pragma unroll
-          for (int mi = 0; mi < GL::MI; ++mi)
-            blk[(GL::out_n(ni, r) + GL::lane_n()) * 256 + GL::out_m(mi) + GL::lane_m()] =
-                acc[mi][ni][r];
-      return;
+    int32_t tm, tn, kb = 0, ke = (int32_t)Tn;
+    if constexpr (kPieces) {
+      const Pieces::At a = g.pc.at(vid, n_wg);
+      last_dw_tile(a.tile, g, tm, tn);
+      kb = a.piece * g.pc.steps * 64;  // tokens past Tn read as zero
+      ke = kb + g.pc.steps * 64;
+    } else {
+      map_tile(vid, (int32_t)g.tiles_m, (int32_t)g.tiles_n, kGroupDw, tm, tn);
     }
+    return Tile{tm * 256, (tn + (int32_t)tn_off) * 256, kb, ke};
+  };
+  auto store = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) {
+    const Tile tile = tile_of(vid);
     if (d <= kMaxBufferD) {
       if (tile.n0 + 256 <= V && tile.m0 + 256 <= d)
         dw_rows<false>(acc, dW, tile, d, V, accumulate);
@@ -398,12 +407,38 @@ __device__ __forceinline__ void dweight_tiles(const DwArgs& g, uint8_t* smem, in
         }
       }
   };
-  tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, g.n_vid, smem, tile_of, epi, wg, n_wg);
+  if constexpr (kPieces) {
+    auto epi = [&](int32_t vid, f32x16 (&acc)[GL::MI][GL::NI]) -> bool {
+      const Pieces::At a = g.pc.at(vid, n_wg);
+      if (!a.flush) return false;  // the tile's next piece follows on this workgroup
+      if (a.piece >= g.pc.p) return true;
+      if (a.slot == 0) {
+        store(vid, acc);
+        return true;
+      }
+      float* blk = g.part + ((int64_t)(a.slot - 1) * g.pc.r + a.tile) * 65536;
+#pragma unroll
+      for (int ni = 0; ni < GL::NI; ++ni)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int mi = 0; mi < GL::MI; ++mi)
+            blk[(GL::out_n(ni, r) + GL::lane_n()) * 256 + GL::out_m(mi) + GL::lane_m()] =
+                acc[mi][ni][r];
+      return true;
+    };
+    tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, g.pc.q * n_wg, smem, tile_of, epi, wg,
+                                                       n_wg);
+  } else {
+    tile_stream<GL, kMNMajor, kKMajor, kDeepDw, kOutN>(A, B, g.n_vid, smem, tile_of, store, wg,
+                                                       n_wg);
+  }
 }
 
+template <bool kPieces>
 RBP_LOGITS_KERNEL void dweight_kernel(DwArgs g) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
-  dweight_tiles(g, smem, (int32_t)blockIdx.x, (int32_t)gridDim.x);
+  dweight_tiles<kPieces>(g, smem, (int32_t)blockIdx.x, (int32_t)gridDim.x);
 }
 
 // Both products of a small batch in one launch: workgroups below n_dw take a
@@ -414,38 +449,34 @@ RBP_LOGITS_KERNEL void grad_both_kernel(DwArgs w, DhArgs h, int32_t n_dw) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[kLdsBytes];
   const int32_t b = (int32_t)blockIdx.x;
   if (b < n_dw)
-    dweight_tiles(w, smem, b, n_dw);
+    dweight_tiles<false>(w, smem, b, n_dw);
   else
     dhidden_pieces(h, smem, b - n_dw, (int32_t)gridDim.x - n_dw);
 }
 
-// dW += part[i] over the tiles vid_base + i (i < n_tiles) of a split
-// dweight launch; one block per (tile, 16 vocabulary rows).
-__global__ void __launch_bounds__(256) part_add_kernel(float* __restrict__ dW,
-                                                       const float* __restrict__ part,
-                                                       int32_t vid_base, int64_t tiles_m,
-                                                       int64_t tiles_n, int64_t tn_off,
-                                                       int32_t d, int32_t V) {
+// dW += the slots of the tiles of a last round, in slot order; one block per
+// (tile, 4 vocabulary rows), 16 bytes per lane.
+__global__ void __launch_bounds__(256) part_add_kernel(DwArgs g) {
   const int32_t i = (int32_t)blockIdx.x;
   int32_t tm, tn;
-  map_tile(vid_base + i, (int32_t)tiles_m, (int32_t)tiles_n, kGroupDw, tm, tn);
-  const int32_t m0 = tm * 256, v0 = (tn + (int32_t)tn_off) * 256;
-  const int32_t vl = (int32_t)blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int32_t v = v0 + vl;
-  if (v >= V) return;
-  const float* src = part + (int64_t)i * 65536 + (int64_t)vl * 256;
-  for (int32_t ml = (threadIdx.x & 15) * 4; ml < 256; ml += 64) {
-    const int32_t m = m0 + ml;
-    if (m >= d) break;  // d % 8 == 0: a float4 never straddles the edge
-    float4* dst = reinterpret_cast<float4*>(dW + (int64_t)v * d + m);
-    const float4 p = *reinterpret_cast<const float4*>(src + ml);
-    float4 o = *dst;
+  last_dw_tile(i, g, tm, tn);
+  const int32_t vl = (int32_t)blockIdx.y * 4 + (threadIdx.x >> 6), ml = (threadIdx.x & 63) * 4;
+  const int64_t v = ((int64_t)tn + g.tn_off) * 256 + vl;
+  const int32_t m = tm * 256 + ml;
+  if (v >= g.V || m >= g.d) return;  // d % 8 == 0: a float4 never straddles the edge
+  float4* dst = reinterpret_cast<float4*>(g.dW + v * g.d + m);
+  float4 o = *dst;
+  const int32_t n = g.pc.slots_of(i);
+#pragma unroll 4
+  for (int32_t k = 0; k < n; ++k) {
+    const float4 p = *reinterpret_cast<const float4*>(
+        g.part + ((int64_t)k * g.pc.r + i) * 65536 + vl * 256 + ml);
     o.x += p.x;
     o.y += p.y;
     o.z += p.z;
     o.w += p.w;
-    *dst = o;
   }
+  *dst = o;
 }
 
 __global__ void __launch_bounds__(256) fill_zero_kernel(float* __restrict__ p, int64_t n) {
@@ -489,32 +520,42 @@ size_t rbp::logprob_bwd_ws(int64_t Tc, int32_t d, int32_t V) {
                                  carve_bwd(nullptr, T256 + 256, dd, V).bytes, 8);
 }
 
+namespace {
+
+// The cut of dW's last round, tiles % G of its tiles, along the tokens.  Only
+// where it fills at most three quarters of the chip: past that the pieces'
+// extra epilogues, each a read-modify-write of 512 KB, eat what the idle units
+// would give (and the busy ones run at a higher clock without them).
+Pieces plan_dweight(int64_t tiles, int64_t nk, int64_t G, const float* scratch,
+                    int64_t scratch_floats) {
+  const int64_t r = tiles % G;
+  const int64_t slots = scratch == nullptr || r == 0 || 4 * r > 3 * G
+                            ? 0
+                            : scratch_floats / (r * 65536);
+  return plan_pieces(r, nk, G, slots, 8);
+}
+
+}  // namespace
+
 void rbp::launch_dweight(const uint16_t* Hc, const uint16_t* Gt, int64_t ldGt, int64_t Tn,
                          int32_t d, int32_t V, float* dW, int accumulate, int64_t tn_begin,
                          int64_t tn_end, hipStream_t s, float* scratch, int64_t scratch_floats) {
   const int64_t tiles_d = rbp::ceil_div(d, 256), tiles_n = tn_end - tn_begin;
   if (tiles_n <= 0) return;
   const int64_t tiles = tiles_d * tiles_n;
-  const int64_t grid = rbp::gemm::stream_grid(tiles, device_cus());
-  // A last round filled to at most half: its tiles go to a second launch as
-  // two K halves each (one round of half the length), when the K range has
-  // at least 8 steps and the scratch holds one 256 x 256 block per tile.
-  const int64_t rem = tiles % grid, nk = rbp::ceil_div(Tn, 64);
-  const bool split = tiles > grid && rem > 0 && 2 * rem <= grid && nk >= 8 &&
-                     scratch != nullptr && rem * 65536 <= scratch_floats;
-  const int64_t n_main = split ? tiles - rem : tiles;
-  DwArgs g{Hc,      Gt,       ldGt, Tn, d, V, dW, accumulate, tiles_d, tiles_n, tn_begin, 0,
-           (int32_t)n_main, 0,  nullptr};
-  hipLaunchKernelGGL(dweight_kernel, dim3(grid), dim3(GL::kThreads), 0, s, g);
-  if (!split) return;
-  g.vid_base = (int32_t)n_main;
-  g.n_vid = (int32_t)(2 * rem);
-  g.split_steps = (int32_t)((nk + 1) / 2);
-  g.part = scratch;
-  hipLaunchKernelGGL(dweight_kernel, dim3(rbp::gemm::stream_grid(2 * rem, device_cus())),
-                     dim3(GL::kThreads), 0, s, g);
-  hipLaunchKernelGGL(part_add_kernel, dim3((unsigned)rem, 16), dim3(256), 0, s, dW, scratch,
-                     (int32_t)n_main, tiles_d, tiles_n, tn_begin, d, V);
+  const int64_t G = rbp::gemm::stream_grid(int64_t(1) << 30, device_cus());  // one round
+  const Pieces pc = plan_dweight(tiles, rbp::ceil_div(Tn, 64), G, scratch, scratch_floats);
+  const int64_t n_main = pc.p > 1 ? tiles - pc.r : tiles;
+  const DwArgs g{Hc,      Gt,       ldGt,            Tn, d,  V,      dW, accumulate, tiles_d,
+                 tiles_n, tn_begin, (int32_t)n_main, (int32_t)n_main, pc, scratch};
+  if (n_main > 0)
+    hipLaunchKernelGGL(dweight_kernel<false>, dim3(rbp::gemm::stream_grid(n_main, device_cus())),
+                       dim3(GL::kThreads), 0, s, g);
+  if (pc.p > 1) {
+    hipLaunchKernelGGL(dweight_kernel<true>, dim3((unsigned)pc.workgroups()),
+                       dim3(GL::kThreads), 0, s, g);
+    hipLaunchKernelGGL(part_add_kernel, dim3((unsigned)pc.r, 64), dim3(256), 0, s, g);
+  }
 }
 
 void rbp::launch_dhidden(const uint16_t* W, const uint16_t* Gt, int64_t ldGt, int64_t Tn,
@@ -557,11 +598,13 @@ bool rbp::launch_both_products(const uint16_t* Hc, const uint16_t* W, const uint
   const Pieces pc = plan_pieces(r, nk_v, G - n_dw, max_slots);
   // In K steps (about 1 us): the two in turn, each with a launch and an
   // epilogue of about 12, against the longer of the two.
-  const int64_t in_turn = nk_t + 12 + (int64_t)alone.q * alone.steps + 12;
+  const Pieces dw_alone = plan_dweight(tiles_d * tiles_v, nk_t, G, scratch, scratch_floats);
+  const int64_t in_turn = (int64_t)dw_alone.q * dw_alone.steps + 12 + (dw_alone.p > 1 ? 6 : 0) +
+                          (int64_t)alone.q * alone.steps + 12;
   const int64_t dw = nk_t + 12, dh = (int64_t)pc.q * pc.steps + 12;
   if ((dw > dh ? dw : dh) >= in_turn) return false;
-  const DwArgs w{Hc,      Gt,      ldGt, Tn, d, V, dW, accumulate, tiles_d, tiles_v, 0, 0,
-                 (int32_t)(tiles_d * tiles_v), 0, nullptr};
+  const DwArgs w{Hc,      Gt, ldGt, Tn, d, V, dW, accumulate, tiles_d,
+                 tiles_v, 0,  (int32_t)(tiles_d * tiles_v), 0, dw_alone, nullptr};
   const DhArgs h{W,       Gt,      ldGt, Tn, d,       V,          cs, dhidden_c,
                  tiles_d, tiles_t, 0,    pc, scratch, slot_floats};
   hipLaunchKernelGGL(grad_both_kernel, dim3((unsigned)(n_dw + pc.workgroups())),

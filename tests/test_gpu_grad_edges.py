@@ -3,7 +3,8 @@ dhidden's last round, against the fp64 oracle (1e-2 relative L2: dz is rounded
 to bf16 once, 2^-9 relative per term).
 
 dW: rows and columns past the vocabulary and the hidden size, one to three
-K steps, accumulated into values that are not zero.  dhidden: few tiles, so
+K steps, many tokens for few tiles (the last round cut along the tokens),
+accumulated into values that are not zero.  dhidden: few tiles, so
 that the last round is cut into many pieces when the workspace holds its
 partial sums, and into fewer with the least workspace of a chunk."""
 
@@ -35,6 +36,8 @@ def _least_workspace(rbp, T, d, V):
     (511, 1536, 9001, False), (700, 896, 40007, False),     # 12 tiles; 12 tiles, 20 pieces
     (1301, 1000, 12289, False), (1301, 1000, 12289, True),  # 24 tiles, both tails
     (4096, 1536, 4100, False),                              # 96 tiles: 8 pieces by threes
+    # dW's last round cut along the tokens: alone, with tails, after a whole round
+    (6000, 64, 300, False), (5000, 304, 1100, False), (1100, 264, 33500, False),
 ])
 def test_products_at_their_edges(T, d, V, least):
     rbp = require_gpu()
