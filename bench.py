@@ -44,22 +44,22 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # a product's launches in one step.  Only valid for the sources the counters
 # were read on (None until they are).
 TRAFFIC_SOURCES = ("fused.hip", "logprob_bwd.hip", "logits_epilogue.h", "gemm_core.h",
-                   "gemm_dma.h", "advantage_loss.hip")
+                   "gemm_dma.h", "pieces.h", "loss_terms.h", "advantage_loss.hip")
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (a 1 GiB copy reads 524300 KiB of
 # FETCH_SIZE and 1048576 KiB of WRITE_SIZE), per step:
 #   logits  = target_ref_kernel + logits_store_kernel
-#   dW      = dweight_kernel (main launch + last-round launch) + part_add_kernel
-#   dhidden = dhidden_kernel (main launch + last-round launch) + part_add_dh_kernel
+#   dW      = dweight_kernel (whole rounds + last round in pieces) + part_add_kernel
+#   dhidden = dhidden_kernel + dhidden_pieces_kernel + part_add_dh_kernel
 TRAFFIC = {
-    "sources_sha256": "2825da243df2c1621cbac27110d208ee401acf8a4a769cfa1f4deb269e77941d",
-    "bytes": {"logits": 34395098112, "dW": 42019896320, "dhidden": 40238567424},
+    "sources_sha256": "1d20e93973c6df005489d33d122411b9b140616030c35ea385e4e74c0c916c35",
+    "bytes": {"logits": 35892458496, "dW": 42035679232, "dhidden": 40054835200},
 }
 
 # the three products of the single pass, by the phase that times them
 PRODUCTS = {
     "logits": "logits_store_kernel (forward product; stores q = exp(z - R_t) as bf16)",
     "dW": "dweight_kernel (dW product)",
-    "dhidden": "dhidden_kernel (dhidden product: main launch + last-round K halves)",
+    "dhidden": "dhidden_kernel (dhidden product: whole rounds + last round in K pieces)",
 }
 
 
@@ -677,7 +677,7 @@ def main():
     frac = tok_s * 6 * dV / PEAK_BF16
     ph = f["phase_ms"]
     # the three products; the dW and dhidden phases each hold a main launch,
-    # a launch of the last round's K halves and the small kernel that adds them
+    # a launch of the last round's K pieces and the small kernel that adds them
     products = {k: ph[k] for k in PRODUCTS}
     dom = max(products, key=products.get)
     dom_ms = products[dom]

@@ -357,8 +357,10 @@ int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
  * library keeps nothing between calls): phase_event[k], a hipEvent_t or
  * NULL, is recorded on `stream` when phase k of a chunk is done
  * (RBP_PHASE_*), for timing the phases without a profiler; with several
- * chunks a later record replaces an earlier one.  Leave them NULL under
- * graph capture.
+ * chunks a later record replaces an earlier one.  Phases whose work shares a
+ * launch (the loss with the merge; dW and dhidden of a small batch) are done
+ * together: their events follow each other.  Leave them NULL under graph
+ * capture.
  */
 enum {
   RBP_PHASE_START = 0,    /* before the chunk's first kernel                    */

@@ -31,15 +31,17 @@
 //      tile was stored against its own maximum); the others -- a ratio below
 //      about e^-20 or above about e^40, or an invalid behaviour log-prob --
 //      are listed and take M_t as their reference instead;
-//   3. the loss pass writes dlogp (policy_loss_fwd_bwd);
-//   4. the listed tokens' columns of Q^T are re-referenced to M_t in place;
+//   3. the clipped loss writes dlogp and its sums, by the merge's blocks (beyond
+//      65536 tokens per chunk by policy_loss_fwd_bwd's own launches);
+//   4. in one launch: the loss's sums over the blocks; the listed tokens' columns of Q^T are re-referenced to M_t in place;
 //      then per token c_t = -dlogp_t exp(ref_t - lse_t), so that
 //      dz_{t,v} = c_t q_{t,v} off the target, and the target entry becomes
 //      q_{t,y} = dz_{t,y} / c_t = exp(lse_t - ref_t) (p_{t,y} - 1); and
 //      H' = c (.) H, row t of the hidden states scaled by c_t, in bf16;
 //   5. dW (+)= Q H' (sum over tokens of q_t (c_t h_t)^T) and
 //      dh_t = c_t (Q^T W)_t, the products of the 4-call backward with the
-//      per-token scale folded into an operand and into an epilogue.
+//      per-token scale folded into an operand and into an epilogue (both in
+//      one launch where neither fills the chip).
 // Unlike policy_logprob_fwd this keeps a T x V array (2 V bytes per token, in
 // the workspace): exp(z - R_t), the backward's dz up to one factor per token.
 // dz is rounded to bf16 once, as q, and c_t h_t once more.

@@ -12,8 +12,10 @@
 //   2. dH[t][m] = sum_v W[v][m] dz^T[v][t]: W and dz^T read MN-major;
 //   3. dW[v][m] (+)= sum_t H[t][m] dz^T[v][t]: H read MN-major, dz^T K-major.
 // Every product runs on the persistent direct-load stream of gemm_dma.h (one
-// 256 x 256 workgroup per CU), reading W and H in place.  No floating-point
-// atomics are used, so results are bitwise reproducible.
+// 256 x 256 workgroup per CU), reading W and H in place.  The last round of
+// dH's and dW's tiles is cut along K where it would leave compute units idle
+// (pieces.h), and where neither product fills the chip both share one launch.
+// No floating-point atomics are used, so results are bitwise reproducible.
 
 #include "logits_epilogue.h"
 #include "pieces.h"
