@@ -71,11 +71,14 @@ __global__ void __launch_bounds__(kPushThreads) push_kernel(
   } lds;
   int32_t b = (int32_t)blockIdx.x;
   if (b < group_blocks) {
-    if (blockIdx.y == 0)
-      rbp::block_advantages(reward, group_off, b * kPushThreads, n_groups, ddof, eps, lds.r,
-                            [&](int32_t k, float a) {
-                              ring.advantage[ring_row(ring.base, k, ring.cap)] = a;
-                            });
+    if (blockIdx.y != 0) return;
+    int32_t lo, n;
+    auto out = [&](int32_t k, float a) {
+      ring.advantage[ring_row(ring.base, k, ring.cap)] = a;
+    };
+    rbp::block_advantages<kPushThreads>(reward, group_off, b * kPushThreads, n_groups, ddof, eps,
+                                        lds.r, lo, n, out,
+                                        [&](int32_t k, float a) { out(lo + k, a); });
     return;
   }
   b -= group_blocks;

@@ -72,3 +72,22 @@ def test_hot_kernels_do_not_spill(src, kernel):
     for vgprs, scratch in _kernels(src, kernel):
         assert scratch == 0, f"{kernel} spills {scratch} bytes per lane"
         assert vgprs <= 256
+
+
+def test_group_advantage_paths_are_apart():
+    """rb_group_advantage has a path through LDS and a direct one.  Each member
+    of a group is written in two places (all rewards equal, or not), so the
+    kernel needs three LDS stores -- the rewards' stage and those two -- and
+    three global ones: the copy out of the stage and the direct path's two.
+    More means that a loop over a group's records tests for the path and
+    carries both of its stores."""
+    with tempfile.TemporaryDirectory() as tmp:
+        asm = os.path.join(tmp, "k.s")
+        r = subprocess.run([b.hipcc(), *b.FLAGS, "--cuda-device-only", "-S",
+                            os.path.join(b.CSRC, "advantage_loss.hip"), "-o", asm],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        text = open(asm).read()
+    body = re.search(r"^_ZN\S*group_advantage_kernel\S*:.*?^\.Lfunc_end", text, re.S | re.M)
+    stores = [len(re.findall(op, body.group(0))) for op in ("ds_write", "global_store")]
+    assert stores == [3, 3]
