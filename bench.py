@@ -567,7 +567,9 @@ def spread(xs):
             "max": round(float(np.max(xs)), 3)}
 
 
-PHASES = ("logits", "merge", "loss", "scale", "dW", "dhidden")  # the RBP_PHASE_* order
+# the RBP_PHASE_* order; the loss ends with the launch that forms the scales, so
+# its phase holds both and "scale" next to nothing (up to 65536 tokens per chunk)
+PHASES = ("logits", "merge", "loss", "scale", "dW", "dhidden")
 
 
 def fused_leg(rbp, wl, S, out, first_step, steps, warmup, ws_tokens=None, entropy=True):

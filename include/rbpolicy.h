@@ -357,16 +357,16 @@ int policy_logprob_bwd(const uint16_t* hidden, const uint16_t* W,
  * library keeps nothing between calls): phase_event[k], a hipEvent_t or
  * NULL, is recorded on `stream` when phase k of a chunk is done
  * (RBP_PHASE_*), for timing the phases without a profiler; with several
- * chunks a later record replaces an earlier one.  Phases whose work shares a
- * launch (the loss with the merge; dW and dhidden of a small batch) are done
- * together: their events follow each other.  Leave them NULL under graph
- * capture.
+ * chunks a later record replaces an earlier one.  An event stands for everything
+ * its phase writes.  Phases that share a launch (the loss's last sums with the
+ * scales; dW and dhidden of a small batch) are done together: their events
+ * follow each other.  Leave them NULL under graph capture.
  */
 enum {
   RBP_PHASE_START = 0,    /* before the chunk's first kernel                    */
   RBP_PHASE_LOGITS = 1,   /* target logits and the logit tile pass done         */
   RBP_PHASE_MERGE = 2,    /* lse, logp and entropy done                         */
-  RBP_PHASE_LOSS = 3,     /* loss pass done (dlogp)                             */
+  RBP_PHASE_LOSS = 3,     /* dlogp, loss_accum and stats done                   */
   RBP_PHASE_SCALE = 4,    /* per-token scales, scaled hidden states done        */
   RBP_PHASE_DW = 5,       /* dW done                                            */
   RBP_PHASE_DHIDDEN = 6,  /* dhidden done                                       */

@@ -620,8 +620,8 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
                                          n_seq_total, eps_low, eps_high, loss_accum, dlogp + t0,
                                          stats, w.loss, w.loss_bytes, stream);
       if (st != RBP_OK) return st;
+      RBP_FUSED_MARK(RBP_PHASE_LOSS);
     }
-    RBP_FUSED_MARK(RBP_PHASE_LOSS);
     hipLaunchKernelGGL(token_scale_kernel,
                        dim3((unsigned)(1 + tiles_v + rbp::ceil_div(T256, kScaleTokens))),
                        dim3(256), 0, s, Hc, tokens + t0, sq, lse + t0, logp + t0, dlogp + t0,
@@ -629,6 +629,8 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
                        fixup_kernel_args{w.R, w.pM, Tc, w.listed, w.n_listed, (int32_t)tiles_v},
                        LossSums{w.loss, n_partials, loss_accum, stats});
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
+    // dlogp is the merge's, but loss_accum and stats are complete only now
+    if (n_partials > 0) RBP_FUSED_MARK(RBP_PHASE_LOSS);
     RBP_FUSED_MARK(RBP_PHASE_SCALE);
     const int acc = (accumulate_dW || t0 > 0) ? 1 : 0;
     const int64_t pm_floats = (int64_t)((ws_bytes - w.pm_at) / sizeof(float));

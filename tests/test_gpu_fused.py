@@ -435,3 +435,31 @@ def test_fused_infinite_behaviour_logprobs():
     assert np.all(to_np(out["dlogp"])[pick] == 0)
     with np.errstate(over="ignore", invalid="ignore"):
         _check(out, h64, W64, y, seq, lens, want_logp, want_lse, old, adv, n_seq)
+
+
+def test_loss_event_comes_after_the_loss_sums():
+    """RBP_PHASE_LOSS stands for dlogp, loss_accum and stats: the launch that
+    adds the sums over the blocks also forms the scales (about 80 us for 49152
+    tokens of d = 2048), so its time lies between the MERGE and LOSS events
+    and next to nothing between LOSS and SCALE."""
+    rbp = require_gpu()
+    T, d, V = 49152, 2048, 300
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    hidden = (torch.randn((T, d), generator=g, device="cuda") * 0.1).bfloat16()
+    W = torch.randn((V, d), generator=g, device="cuda").bfloat16()
+    tokens = torch.randint(0, V, (T,), generator=g, dtype=torch.int32, device="cuda")
+    seq = torch.zeros(T, dtype=torch.int32, device="cuda")
+    old = torch.full((T,), -6.0, device="cuda")
+    args = (rbp, hidden, W, tokens, seq, old, torch.ones(1, device="cuda"),
+            torch.full((1,), T, dtype=torch.int32, device="cuda"), 1)
+    evs = [torch.cuda.Event(enable_timing=True) for _ in range(rbp.RBP_NUM_PHASES)]
+    ex = rbp.make_exec(evs)
+    loss_ms, scale_ms = [], []
+    for _ in range(4):
+        out = _run(*args, ex=ex)
+        loss_ms.append(evs[rbp.RBP_PHASE_MERGE].elapsed_time(evs[rbp.RBP_PHASE_LOSS]))
+        scale_ms.append(evs[rbp.RBP_PHASE_LOSS].elapsed_time(evs[rbp.RBP_PHASE_SCALE]))
+    print(f"[fused] merge -> loss {min(loss_ms)} ms, loss -> scale {min(scale_ms)} ms", flush=True)
+    assert min(scale_ms) < 0.5 * min(loss_ms)
+    assert to_np(out["stats"])[2] == T
