@@ -18,6 +18,7 @@
 // arithmetic of rb_group_advantage).
 
 #include "group_advantage.h"
+#include "launch_rules.h"
 #include "rbp_internal.h"
 
 namespace {
@@ -28,9 +29,9 @@ __device__ __forceinline__ int64_t ring_row(int64_t base, int64_t i, int64_t cap
 }
 
 constexpr int kHistMaxBins = 4096;
-constexpr int kPushThreads = 256;
-constexpr int kPushLoads = 8;  // tokens a thread has in flight
-constexpr int kPushTokens = kPushLoads * kPushThreads;
+using rbp::rules::kPushLoads;
+using rbp::rules::kPushThreads;
+using rbp::rules::kPushTokens;
 
 struct PushRing {
   int64_t base, cap, slot_tokens;  // base: the first new record's row
@@ -304,10 +305,7 @@ extern "C" int rb_push(rb_ring* ring, int32_t n_new, int32_t n_groups, const int
                     ring->replay_hist,
                     ring->replay_bins,
                     cap - ring->n_live};
-  // rows of the grid for long records, while there are too few records for
-  // two blocks per compute unit
-  int64_t by = rbp::ceil_div(ring->slot_tokens, kPushTokens);
-  if (by > 512 / n_new) by = 512 / n_new < 1 ? 1 : 512 / n_new;
+  const int64_t by = rbp::rules::push_rows(n_new, ring->slot_tokens);
   // a launch holds 2^32 threads, 2^24 blocks: at most 2^21 blocks of records
   // beside the (at most 2^23) blocks of groups and of fields, which lie below
   // 2^24 together unless both counts are near 2^31
