@@ -29,5 +29,36 @@ inline int64_t push_rows(int64_t n_new, int64_t slot_tokens) {
   return rows < passes ? rows : passes;
 }
 
+// ---- rb_sample_gather, packed -------------------------------------------------
+
+constexpr int kFuseDraws = 512;     // draws that a block can redo, one per thread
+constexpr int kPackedSmall = 512;   // threads of a block in windows of up to 2^17 positions
+constexpr int kPackedLarge = 1024;  // and beyond: half as many blocks redo the draws
+
+struct PackedRoute {
+  int threads, positions;  // of the one launch's blocks and of a thread
+  int64_t blocks;          // 0: the draws first, then the gather, in launches of their own
+};
+
+// Draw and gather in one launch, every block redoing all the draws, pays while
+// the blocks run at once -- one per compute unit where slots are found by rank
+// (the granules' offsets and masks in LDS and registers), two otherwise -- and
+// the records that they read over and over stay few.  Two positions per thread
+// halve the blocks once more.  Device times, one launch against two: 524288
+// positions of 64 uniform draws 5.3 us against 6.6, of 512 7.4 / 8.0 (8.4 with
+// one position per thread); 10^6 of 64 6.6 / 7.9; mix draws from 32768 records:
+// 262144 positions of 512 draws 12.4 / 13.7, 2000000 of 24 in 977 blocks 41 / 15.5.
+inline PackedRoute packed_route(int64_t n_draw, int64_t max_tokens, bool ranks) {
+  const PackedRoute none{0, 0, 0};
+  if (n_draw > kFuseDraws) return none;
+  const auto blocks_of = [&](int64_t per) { return max_tokens / per + (max_tokens % per != 0); };
+  if (max_tokens <= 256 * kPackedSmall) return {kPackedSmall, 1, blocks_of(kPackedSmall)};
+  const int64_t at_once = ranks ? 256 : 512, one = blocks_of(kPackedLarge),
+                two = blocks_of(2 * kPackedLarge);
+  if (one <= at_once && one * n_draw <= 3 << 16) return {kPackedLarge, 1, one};
+  if (two <= at_once && two * n_draw <= 1 << 17) return {kPackedLarge, 2, two};
+  return none;
+}
+
 }  // namespace rules
 }  // namespace rbp

@@ -33,6 +33,7 @@
 #include <atomic>
 #include <mutex>
 
+#include "launch_rules.h"
 #include "ranks.h"
 #include "rbp_internal.h"
 
@@ -44,9 +45,8 @@ using rbp::ranks::View;
 
 constexpr int kMaskThreads = 256;
 constexpr int kLdsGranules = 2048;     // granules whose offsets a block scans itself
-constexpr int kFuseThreads = 256;      // sample_packed / sample_padded
-constexpr int kFuseDraws = 512;        // draws that sample_packed redoes in every block
-constexpr int kFusePositions = 4;      // window positions per thread, at most
+constexpr int kFuseThreads = 256;      // sample_padded
+using rbp::rules::kFuseDraws;          // draws that sample_packed redoes in every block
 constexpr int kRowVecs = 4;            // 16-byte groups of a padded row per thread
 constexpr int kRowSingles = 8;         // or positions, where rows are not aligned to them
 constexpr int kDrawThreads = 1024;  // single-block draw pass, up to this many draws
@@ -573,66 +573,59 @@ __device__ __forceinline__ void write_totals(const DrawParams& p, int64_t sum,
 // (draw: record; gather: draw, arena offset, tokens) and two launches, about
 // 5 us each for the few draws of a training batch.  Here every block redoes the
 // draws it needs -- one Philox block and two loads per draw -- so nothing is
-// handed over.  16384 tokens of 24 uniform draws: 10.1 us in two launches, 8 in
-// one; see the launch rules for where redoing the draws stops paying.
+// handed over; see launch_rules.h for where redoing the draws stops paying.
 
-// Block b copies kFuseThreads * per window positions, from b of those on.
+// Block b copies kThreads * kPos window positions, from b of those on; a thread
+// makes one draw and copies kPos positions.  (Two draws and four positions a
+// thread, in blocks of 256, are as many chains of loads one after another:
+// 16384 positions of 512 mix draws from 32768 records took 13.0 us, now 10.8;
+// 358400 of 512 uniform draws 9.2, the two launches 7.7.)
 // kRanks: every mode but the uniform one, which needs none of the ranks'
 // registers and LDS.
-template <bool kRanks>
-__global__ void __launch_bounds__(kFuseThreads) sample_packed_kernel(DrawParams p, Ranks ranks,
-                                                                     DrawTable t, int32_t per) {
+template <bool kRanks, int kThreads, int kPos>
+__global__ void __launch_bounds__(kThreads) sample_packed_kernel(DrawParams p, Ranks ranks,
+                                                                 DrawTable t) {
+  static_assert(kThreads >= kFuseDraws, "one draw per thread");
   __shared__ int64_t off_s[kRanks ? kLdsGranules : 1];
-  __shared__ int64_t lds[kFuseThreads / 64];
+  __shared__ int64_t lds[kThreads / 64];
   __shared__ int64_t src_s[kFuseDraws];     // arena offset of draw j
   __shared__ int32_t cu_s[kFuseDraws + 1];  // its stream position
   View v{};
-  if constexpr (kRanks) v = view_ranks<kFuseThreads>(ranks, off_s, lds);
+  if constexpr (kRanks) v = view_ranks<kThreads>(ranks, off_s, lds);
   const DrawSet d = draw_set(p, v);
-  constexpr int kPer = kFuseDraws / kFuseThreads;
-  const int64_t j0 = (int64_t)threadIdx.x * kPer;
-  int64_t len[kPer], sum = 0;
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int64_t j = j0 + k;
-    len[k] = 0;
-    if (j < p.n_draw) {
-      const int64_t slot = draw_slot<kRanks>(p, d, v, j);
-      const int64_t r = phys_row(slot, p.head, p.cap);
-      len[k] = t.length[r];
-      src_s[j] = t.arena_off[r];
-      if (blockIdx.x == 0) write_draw(p, t, j, slot, r, len[k]);
-    }
-    sum += len[k];
+  const int64_t j = threadIdx.x;
+  int64_t len = 0;
+  if (j < p.n_draw) {
+    const int64_t slot = draw_slot<kRanks>(p, d, v, j);
+    const int64_t r = phys_row(slot, p.head, p.cap);
+    len = t.length[r];
+    src_s[j] = t.arena_off[r];
+    if (blockIdx.x == 0) write_draw(p, t, j, slot, r, len);
   }
   int64_t total;
-  int64_t at = block_exclusive_scan<kFuseThreads>(sum, &total, lds);
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    if (j0 + k <= p.n_draw) {
-      cu_s[j0 + k] = (int32_t)at;
-      if (blockIdx.x == 0) t.cu_seqlens[j0 + k] = (int32_t)at;
-    }
-    at += len[k];
+  const int64_t at = block_exclusive_scan<kThreads>(len, &total, lds);
+  if (j < p.n_draw) {
+    cu_s[j] = (int32_t)at;
+    if (blockIdx.x == 0) t.cu_seqlens[j] = (int32_t)at;
   }
-  if (threadIdx.x == 0) {
-    if (p.n_draw == kFuseDraws) {  // no thread's j0 + k reaches it
-      cu_s[kFuseDraws] = (int32_t)total;
-      if (blockIdx.x == 0) t.cu_seqlens[kFuseDraws] = (int32_t)total;
+  if (j == 0) {
+    cu_s[p.n_draw] = (int32_t)total;
+    if (blockIdx.x == 0) {
+      t.cu_seqlens[p.n_draw] = (int32_t)total;
+      *t.n_tokens = window_tokens(p, total);
     }
-    if (blockIdx.x == 0) *t.n_tokens = window_tokens(p, total);
   }
   __syncthreads();
-  const int64_t w0 = (int64_t)blockIdx.x * (kFuseThreads * per) + threadIdx.x;
-  int32_t tk[kFusePositions], sq[kFusePositions];
-  float ol[kFusePositions];
+  const int64_t w0 = (int64_t)blockIdx.x * (kThreads * kPos) + threadIdx.x;
+  int32_t tk[kPos], sq[kPos];
+  float ol[kPos];
 #pragma unroll
-  for (int k = 0; k < kFusePositions; ++k) {
-    const int64_t w = w0 + (int64_t)k * kFuseThreads, pos = p.token_begin + w;
+  for (int k = 0; k < kPos; ++k) {  // all loads in flight before the first store
+    const int64_t w = w0 + k * kThreads, pos = p.token_begin + w;
     tk[k] = 0;
     ol[k] = 0.0f;
     sq[k] = -1;
-    if (k >= per || w >= p.max_tokens || pos >= total) continue;
+    if (w >= p.max_tokens || pos >= total) continue;
     int32_t lo = 0, hi = (int32_t)p.n_draw;  // the draw that holds pos
     while (hi - lo > 1) {
       const int32_t m = (lo + hi) >> 1;
@@ -644,9 +637,9 @@ __global__ void __launch_bounds__(kFuseThreads) sample_packed_kernel(DrawParams 
     sq[k] = lo;
   }
 #pragma unroll
-  for (int k = 0; k < kFusePositions; ++k) {
-    const int64_t w = w0 + (int64_t)k * kFuseThreads;
-    if (k >= per || w >= p.max_tokens) continue;
+  for (int k = 0; k < kPos; ++k) {
+    const int64_t w = w0 + k * kThreads;
+    if (w >= p.max_tokens) continue;
     t.tokens[w] = tk[k];
     t.old_logp[w] = ol[k];
     t.seq[w] = sq[k];
@@ -1025,14 +1018,20 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
                      reinterpret_cast<uintptr_t>(out->seq_of_token)) & 15) == 0;
   // Draw and gather in one launch while every block can redo the draws it
   // needs at little cost.  Padded, that is one draw (and one block sums all of
-  // them: up to kDrawThreads); packed, it is all of them: up to kFuseDraws, in
-  // windows of up to 2^18 draws x blocks (each one record read of 64 bytes).
-  const int64_t per = packed && cfg->max_tokens > 65536 ? kFusePositions : 1;
-  const int64_t blocks = packed ? rbp::ceil_div(cfg->max_tokens, kFuseThreads * per) : 0;
-  if (packed && cfg->n_draw <= kFuseDraws && blocks * cfg->n_draw <= (1 << 18)) {
-    hipLaunchKernelGGL(ranks.nb > 0 ? sample_packed_kernel<true> : sample_packed_kernel<false>,
-                       dim3((unsigned)blocks), dim3(kFuseThreads), 0, s, p,
-                       ranks, t, (int32_t)per);
+  // them: up to kDrawThreads); packed, it is all of them (packed_route).
+  const auto route = packed ? rbp::rules::packed_route(cfg->n_draw, cfg->max_tokens, ranks.nb > 0)
+                            : rbp::rules::PackedRoute{0, 0, 0};
+  if (route.blocks > 0) {
+    constexpr int kS = rbp::rules::kPackedSmall, kL = rbp::rules::kPackedLarge;
+    const bool rk = ranks.nb > 0;
+    const auto kernel =
+        route.threads == kS
+            ? (rk ? sample_packed_kernel<true, kS, 1> : sample_packed_kernel<false, kS, 1>)
+            : (route.positions == 1
+                   ? (rk ? sample_packed_kernel<true, kL, 1> : sample_packed_kernel<false, kL, 1>)
+                   : (rk ? sample_packed_kernel<true, kL, 2> : sample_packed_kernel<false, kL, 2>));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)route.blocks), dim3(route.threads), 0, s, p, ranks,
+                       t);
     RBP_CHECK_LAUNCH("rb_sample_gather");
     return RBP_OK;
   }

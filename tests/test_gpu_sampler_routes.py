@@ -1,8 +1,8 @@
 """rb_sample_gather at the lines between its launch routes, bit-exact against
-the oracle's rules: draws redone by every block or made once (512, 1024), one
-or four window positions per thread (65536), windows in which redoing the draws
-stops (2^18 draws x blocks), tables whose offsets every block scans or one
-launch does (2048 granules of 1024 slots), a ring head inside the table, padded
+the oracle's rules: draws redone by every block or made once (512, 1024),
+blocks of 512 or 1024 threads (2^17 window positions), one or two positions per
+thread (2^18 with ranks, 2^19 without, draws x blocks), windows in which redoing
+the draws stops, tables whose offsets every block scans or one launch does (2048 granules of 1024 slots), a ring head inside the table, padded
 rows with and without 16-byte groups."""
 
 import numpy as np
@@ -70,6 +70,11 @@ SMALL, LARGE = (5000, 6000, 4321), (2048 * 1024 + 777, 2048 * 1024 + 1000, 2_000
     (SMALL, "unused", "packed", 300, 300 * 1024, 0), (SMALL, "uniform", "packed", 512, 524289, 0),
     (SMALL, "uniform", "packed", 20, 1000, 100000), (SMALL, "unused", "packed", 1024, 3000, 0),
     (SMALL, "distinct", "packed", 5000, 9000, 200), (SMALL, "mix", "packed", 1025, 9000, 200),
+    (SMALL, "uniform", "packed", 512, 131072, 7), (SMALL, "unused", "packed", 511, 131073, 0),
+    (SMALL, "mix", "packed", 60, 262144, 0), (SMALL, "distinct", "packed", 300, 262145, 3),
+    (SMALL, "retain", "packed", 512, 524289, 0), (SMALL, "uniform", "packed", 375, 524288, 0),
+    (SMALL, "uniform", "packed", 255, 524289, 1), (SMALL, "uniform", "packed", 512, 393217, 0),
+    (SMALL, "uniform", "packed", 2, 1048576, 0), (SMALL, "uniform", "packed", 2, 1048577, 0),
     (SMALL, "uniform", "padded", 1024, 24, 0), (SMALL, "mix", "padded", 1025, 24, 0),
     (SMALL, "retain", "padded", 300, 17, 0), (SMALL, "unused", "padded", 1024, 8, 0),
     (SMALL, "distinct", "padded", 1500, 9, 0), (SMALL, "mix", "padded", 3, 9000, 0),

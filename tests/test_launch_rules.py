@@ -49,3 +49,37 @@ def test_push_splits_long_records_whatever_their_number(tmp_path):
     16 blocks share a record): one long record among many short ones is not
     left to a single block."""
     _run(tmp_path, PUSH)
+
+
+PACKED = r"""
+#include <cstdio>
+#include "launch_rules.h"
+using namespace rbp::rules;
+int main() {
+  for (int64_t w = 1; w < ((int64_t)1 << 40); w += 1 + w / 7)
+    for (int64_t edge : {w, (int64_t)1 << 17, ((int64_t)1 << 17) + 1, (int64_t)1 << 18,
+                         ((int64_t)1 << 18) + 1, (int64_t)1 << 19, ((int64_t)1 << 19) + 1,
+                         (int64_t)1 << 20, ((int64_t)1 << 20) + 1})
+      for (int64_t n : {1, 2, 255, 256, 257, 511, 512, 513, 1 << 20})
+        for (bool ranks : {false, true}) {
+          const PackedRoute r = packed_route(n, edge, ranks);
+          if (r.blocks == 0) continue;
+          const int64_t per = (int64_t)r.threads * r.positions;
+          const bool covers = r.blocks * per >= edge && (r.blocks - 1) * per < edge;
+          const bool known = (r.threads == 512 && r.positions == 1) ||
+                             (r.threads == 1024 && (r.positions == 1 || r.positions == 2));
+          // one draw per thread; a block per compute unit with ranks, two without
+          if (!covers || !known || n > r.threads || n > kFuseDraws ||
+              r.blocks > (ranks ? 256 : 512) || r.blocks * n > 3 << 16)
+            return printf("n=%ld w=%ld ranks=%d\n", (long)n, (long)edge, ranks), 1;
+        }
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_packed_draws_are_redone_by_blocks_that_run_at_once(tmp_path):
+    """Where every block of a packed gather redoes the draws, a thread makes one
+    of them, the blocks cover the window once and all run at the same time."""
+    _run(tmp_path, PACKED)
