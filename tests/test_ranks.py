@@ -76,3 +76,25 @@ def test_rank_is_the_position_in_slot_order(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
+
+
+def test_masks_of_ties_are_read_only_where_there_are_some(tmp_path):
+    """The same walk with the masks of ties overwritten in every granule but the
+    last whose count says that it has none: a draw in such a granule must not
+    read them."""
+    program = PROGRAM.replace("        const int64_t needs[]", """\
+        std::vector<ulonglong2> kept(t);
+        const uint64_t* want = reinterpret_cast<const uint64_t*>(kept.data());
+        for (int g = 0; g + 1 < nb; ++g)
+          if (off[g] >> 32 == off[g + 1] >> 32)
+            for (int w = 0; w < kWords; ++w) tie[g * kWords + w] = ~0ull;
+        const int64_t needs[]""", 1)
+    program = program.replace("v.tie && (tie[s / 64]", "v.tie && (want[s / 64]", 1)
+    assert program.count("want") == 2
+    src, exe = tmp_path / "ranks.hip", tmp_path / "ranks"
+    src.write_text(program)
+    r = subprocess.run([b.hipcc(), *b.FLAGS, str(src), "-o", str(exe)], capture_output=True,
+                       text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
