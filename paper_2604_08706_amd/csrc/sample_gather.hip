@@ -49,7 +49,7 @@ constexpr int kFuseThreads = 256;      // sample_padded
 using rbp::rules::kFuseDraws;          // draws that sample_packed redoes in every block
 constexpr int kRowVecs = 4;            // 16-byte groups of a padded row per thread
 constexpr int kRowSingles = 8;         // or positions, where rows are not aligned to them
-constexpr int kDrawThreads = 1024;  // single-block draw pass, up to this many draws
+using rbp::rules::kDrawThreads;     // single-block draw pass, up to this many draws
 constexpr int kRowThreads = 256;    // draws per block beyond that
 constexpr int kMaxRowBlocks = (1 << 20) / kRowThreads;
 
@@ -1017,8 +1017,8 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
                      reinterpret_cast<uintptr_t>(out->old_logp) |
                      reinterpret_cast<uintptr_t>(out->seq_of_token)) & 15) == 0;
   // Draw and gather in one launch while every block can redo the draws it
-  // needs at little cost.  Padded, that is one draw (and one block sums all of
-  // them: up to kDrawThreads); packed, it is all of them (packed_route).
+  // needs at little cost.  Padded, that is one draw, and one block sums all of
+  // them (padded_one_launch); packed, it is all of them (packed_route).
   const auto route = packed ? rbp::rules::packed_route(cfg->n_draw, cfg->max_tokens, ranks.nb > 0)
                             : rbp::rules::PackedRoute{0, 0, 0};
   if (route.blocks > 0) {
@@ -1035,7 +1035,7 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
     RBP_CHECK_LAUNCH("rb_sample_gather");
     return RBP_OK;
   }
-  if (!packed && cfg->n_draw <= kDrawThreads) {
+  if (!packed && rbp::rules::padded_one_launch(cfg->n_draw, cfg->l_max, ranks.nb)) {
     const auto kernel = ranks.nb > 0
                             ? (vec ? sample_padded_kernel<true, true>
                                    : sample_padded_kernel<true, false>)

@@ -60,7 +60,8 @@ def _slots(t, mode, seed, step, k, p_q32, n_fresh, n_keep):
                                       n_keep))
 
 
-SMALL, LARGE = (5000, 6000, 4321), (2048 * 1024 + 777, 2048 * 1024 + 1000, 2_000_000)
+SMALL, MEDIUM = (5000, 6000, 4321), (70_000, 71_000, 60_000)
+LARGE = (2048 * 1024 + 777, 2048 * 1024 + 1000, 2_000_000)
 
 
 @pytest.mark.parametrize("size,mode,layout,k,width,begin", [
@@ -79,6 +80,9 @@ SMALL, LARGE = (5000, 6000, 4321), (2048 * 1024 + 777, 2048 * 1024 + 1000, 2_000
     (SMALL, "retain", "padded", 300, 17, 0), (SMALL, "unused", "padded", 1024, 8, 0),
     (SMALL, "distinct", "padded", 1500, 9, 0), (SMALL, "mix", "padded", 3, 9000, 0),
     (LARGE, "mix", "packed", 400, 4000, 0), (LARGE, "retain", "padded", 200, 24, 0),
+    (MEDIUM, "mix", "padded", 768, 24, 0), (MEDIUM, "retain", "padded", 769, 24, 0),
+    (MEDIUM, "unused", "padded", 1000, 23, 0), (MEDIUM, "mix", "padded", 1024, 200, 0),
+    (LARGE, "mix", "padded", 512, 24, 0), (LARGE, "mix", "padded", 513, 24, 0),
     (LARGE, "unused", "packed", 700, 5000, 0), (LARGE, "distinct", "padded", 2000, 24, 0),
 ])
 def test_routes(size, mode, layout, k, width, begin):

@@ -83,3 +83,33 @@ def test_packed_draws_are_redone_by_blocks_that_run_at_once(tmp_path):
     """Where every block of a packed gather redoes the draws, a thread makes one
     of them, the blocks cover the window once and all run at the same time."""
     _run(tmp_path, PACKED)
+
+
+PADDED = r"""
+#include <cstdio>
+#include "launch_rules.h"
+using namespace rbp::rules;
+int main() {
+  for (int64_t n : {1, 512, 513, 600, 768, 769, 1000, 1024, 1025, 1 << 20})
+    for (int64_t l : {1, 100, 400, 1000, 2000, 8192, 1 << 20}) {
+      bool before = true;
+      for (int64_t nb : {0, 1, 32, 65, 255, 256, 293, 977, 2048, 2930, 1 << 21}) {
+        const bool one = padded_one_launch(n, l, nb);
+        // one block sums the lengths of all draws; larger tables never go back
+        // to one launch; where two were measured faster, two are taken
+        if ((one && n > kDrawThreads) || (n <= 512 && !one) || (one && !before) ||
+            (one && nb >= 977 && n >= 600 && l <= 1000) || (one && nb >= 65 && n > 768 && l <= 100))
+          return printf("n=%ld l=%ld nb=%ld\n", (long)n, (long)l, (long)nb), 1;
+        before = one;
+      }
+    }
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_padded_draws_by_rank_from_large_tables_are_made_once(tmp_path):
+    """A padded gather of more than 512 draws by rank makes the draws in a
+    launch of their own once the table is large against its rows."""
+    _run(tmp_path, PADDED)
