@@ -71,6 +71,15 @@ struct Pieces {
   int64_t workgroups() const { return (int64_t)r * u + ((int64_t)r * rem + q - 1) / q; }
 };
 
+// The largest number of pieces up to p that needs at most max_slots (>= 1)
+// slots: p / q - 1, and one more for a left-over piece, two for several.
+inline int64_t fitting_pieces(int64_t p, int64_t q, int64_t max_slots) {
+  const int64_t all = (max_slots + 1) * q;  // no piece left over
+  if (p >= all) return all;
+  const int64_t one = max_slots * q + 1;    // one
+  return p < one ? p : one;                 // any below
+}
+
 // The cut of r tiles of nk K steps for G workgroups when at most max_slots
 // slots fit in the scratch (p = 1: not cut).  Cost in K steps (about 1 us
 // each): the q pieces a workgroup runs, a second epilogue for a helper, and
@@ -87,14 +96,9 @@ inline Pieces plan_pieces(int64_t r, int64_t nk, int64_t G, int64_t max_slots,
     int64_t p = q * G / r;
     if (p > nk / min_steps) p = nk / min_steps;
     for (; p > q; p -= 1 + p / 8) {
+      p = fitting_pieces(p, q, max_slots);
+      if (p <= q) break;
       Pieces c{(int32_t)r, (int32_t)p, (int32_t)q, (int32_t)(p / q), (int32_t)(p % q), 0};
-      while (c.p > q && c.slots() > max_slots) {
-        --c.p;
-        c.u = c.p / c.q;
-        c.rem = c.p % c.q;
-      }
-      if (c.p <= q) break;
-      p = c.p;
       if (q > 1 && c.rem == 0) continue;  // p / q pieces of one, in more parts
       c.steps = (int32_t)((nk + p - 1) / p);
       const double cost = (double)(q * c.steps) + 0.25 * (double)(q - 1) +

@@ -104,3 +104,43 @@ def test_workspace_of_a_chunk_holds_that_chunk_and_no_more():
                 for n in range(256, 256 * 70, 256):
                     got = lib.rbp_workspace_bytes(op, n, d, V)
                     assert token * n + fixed <= got < token * (n + 256) + fixed, (op, d, V, n)
+
+
+PLANS = r"""
+#include <cstdio>
+#include "pieces.h"
+using namespace rbp::gemm;
+static int64_t walked(int64_t p, int64_t q, int64_t max_slots) {  // one piece less at a time
+  for (;; --p) {
+    const Pieces c{1, (int32_t)p, (int32_t)q, (int32_t)(p / q), (int32_t)(p % q), 0};
+    if (p <= q || c.slots() <= max_slots) return p;
+  }
+}
+int main() {
+  for (int64_t q = 1; q <= 8; ++q)
+    for (int64_t p = q + 1; p <= 600; ++p)
+      for (int64_t m = 1; m <= 80; ++m)
+        if (fitting_pieces(p, q, m) != walked(p, q, m))
+          return printf("p=%ld q=%ld max_slots=%ld\n", (long)p, (long)q, (long)m), 1;
+  // a plan's time does not grow with the pieces that the scratch has no room for
+  for (int i = 0; i < 100; ++i) {
+    const Pieces c = plan_pieces(1, (int64_t)1 << 30, (int64_t)1 << 26, 1 + i % 3);
+    if (c.p < 2 || c.slots() > 1 + i % 3) return printf("plan p=%d\n", c.p), 1;
+  }
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_plans_step_to_the_pieces_that_fit_the_scratch(tmp_path):
+    """The most pieces that the scratch has slots for are formed directly, equal
+    to a walk down from all of them: one tile on 2^26 units is planned in
+    microseconds (a walk would take about a second per plan)."""
+    src, exe = tmp_path / "plans.hip", tmp_path / "plans"
+    src.write_text(PLANS)
+    r = subprocess.run([b.hipcc(), *b.FLAGS, str(src), "-o", str(exe)], capture_output=True,
+                       text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=20)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
