@@ -108,10 +108,12 @@ Workspace workspace(PyObject* o) {
   return {p, (size_t)THPVariable_Unpack(o).nbytes()};
 }
 
+// An integer of any size, cut to its low 64 bits as ctypes cuts it (a policy
+// version may be a hash).
 int64_t integer(PyObject* o) {
-  const long long v = PyLong_AsLongLong(o);
-  if (v == -1 && PyErr_Occurred()) throw Raised{};
-  return v;
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (v == (unsigned long long)-1 && PyErr_Occurred()) throw Raised{};
+  return (int64_t)v;
 }
 float real(PyObject* o) {
   const double v = PyFloat_AsDouble(o);
@@ -119,12 +121,13 @@ float real(PyObject* o) {
   return (float)v;
 }
 
-// The current stream, or the given one (an object with `cuda_stream`).
+// The current stream, or the given one: an object with `cuda_stream`, which is
+// an address or None (the null stream).
 void* stream(PyObject* o) {
   if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
   PyObject* s = PyObject_GetAttrString(o, "cuda_stream");
   if (s == nullptr) throw Raised{};
-  void* p = PyLong_AsVoidPtr(s);
+  void* p = s == Py_None ? nullptr : PyLong_AsVoidPtr(s);
   Py_DECREF(s);
   if (p == nullptr && PyErr_Occurred()) throw Raised{};
   return p;

@@ -77,6 +77,33 @@ def test_wrong_dtype_layout_and_size_are_refused(name):
 
 
 @pytest.mark.gpu
+def test_wide_integers_and_null_streams_are_taken_as_ctypes_takes_them():
+    """An integer keeps its low bits, and a stream whose handle is None is the
+    null stream: both were accepted while the calls went through ctypes."""
+    dev = "cuda"
+    ring = rbp.make_ring(4, 2)
+    off, one = _t(2, torch.int32, dev), torch.ones(2, dtype=torch.int32, device=dev)
+    off[1] = 2
+    for version in ((1 << 63) + 5, (1 << 64) + 7, -(1 << 63) - 1, -3):
+        rbp.rb_push(ring, off, one, _t(2, torch.int64, dev), _t(2, device=dev), version, one,
+                    _t(2, device=dev))
+        row = (ring.head + ring.n_live - 1) % 4
+        want = ((version + (1 << 31)) % (1 << 32)) - (1 << 31)
+        assert ring.t["version"][row].item() == want
+
+    class Null:
+        cuda_stream = None
+
+    values, hist = torch.full((5,), -1, dtype=torch.int32, device=dev), _t(3, torch.int64, dev)
+    torch.cuda.synchronize()
+    rbp.rb_hist_accumulate(values, hist, lo=(1 << 64) - 1, stream=Null())
+    torch.cuda.synchronize()
+    assert hist.tolist() == [5, 0, 0]
+    with pytest.raises(TypeError):
+        rbp.rb_hist_accumulate(values, hist, stream=type("S", (), {"cuda_stream": 1.5})())
+
+
+@pytest.mark.gpu
 def test_the_given_stream_is_used():
     s = torch.cuda.Stream()
     v = torch.full((1000,), 3, dtype=torch.int32, device="cuda")
