@@ -5,8 +5,9 @@
 Every .hip file under csrc/ is compiled to an object with hipcc and the
 objects are linked into paper_2604_08706_amd/librbpolicy.so.  csrc/marshal.cpp,
 host code against the torch and Python headers, is compiled with g++ and
-linked with the library into paper_2604_08706_amd/_marshal.so.  Compiling for
-gfx950 needs no GPU, so this runs on any machine with ROCm installed.
+linked with the library into paper_2604_08706_amd/_marshal.so; without torch
+only the library, which a C program links, is built.  Compiling for gfx950 needs
+no GPU, so this runs on any machine with ROCm installed.
 """
 
 import os
@@ -54,9 +55,11 @@ def _compile(src, extra):
 
 
 def _torch_root():
+    """Folder of the installed torch, None without one."""
     import importlib.util
 
-    return os.path.dirname(importlib.util.find_spec("torch").origin)
+    spec = importlib.util.find_spec("torch")
+    return None if spec is None else os.path.dirname(spec.origin)
 
 
 def _run(cmd, what):
@@ -89,21 +92,26 @@ def _link_marshal(obj):
 
 def build(extra_flags=(), verbose=True):
     """Compile every csrc/*.hip and link librbpolicy.so (its path is returned),
-    then the _marshal module."""
+    then, where torch is installed, the _marshal module."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
     workers = min(len(srcs) + 1, max(1, min(8, os.cpu_count() or 1)))
+    python = _torch_root() is not None
     with ThreadPoolExecutor(workers) as ex:
-        marshal = ex.submit(_compile_marshal)
+        marshal = ex.submit(_compile_marshal) if python else None
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), srcs))
-        marshal_obj = marshal.result()
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     os.replace(tmp, LIB)
-    _link_marshal(marshal_obj)
+    # the library needs neither torch nor g++: it is in place whatever follows
+    if python:
+        _link_marshal(marshal.result())
+    else:
+        sys.stderr.write("torch is not installed: _marshal.so, which only the Python binding "
+                         "needs, is not built\n")
     if verbose:
         print(f"built {LIB}")
     return LIB
