@@ -386,7 +386,7 @@ __global__ void __launch_bounds__(64 * kMergeWaves) fused_merge_kernel(
 //     p_{t,y}).
 constexpr int kScaleTokens = 4;
 
-struct fixup_kernel_args {
+struct FixupArgs {
   const float *R, *pM;
   int64_t ldp;
   const int32_t *listed, *n_listed;
@@ -404,7 +404,7 @@ __global__ void __launch_bounds__(256) token_scale_kernel(
     const float* __restrict__ logp, const float* __restrict__ dlogp,
     const float* __restrict__ ref, int64_t Tn, int64_t T256, int32_t d, int32_t V,
     uint16_t* __restrict__ Hp, float* __restrict__ cs, uint16_t* __restrict__ Qt, int64_t ldQ,
-    fixup_kernel_args fix, LossSums sums) {
+    FixupArgs fix, LossSums sums) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   auto target_q = [&](int64_t t) {
     return __builtin_bit_cast(
@@ -626,7 +626,7 @@ extern "C" int policy_fused_fwd_bwd(const uint16_t* hidden, const uint16_t* W,
                        dim3((unsigned)(1 + tiles_v + rbp::ceil_div(T256, kScaleTokens))),
                        dim3(256), 0, s, Hc, tokens + t0, sq, lse + t0, logp + t0, dlogp + t0,
                        w.ref, Tn, T256, d, V, w.Hp, w.cs, w.Qt, Tc,
-                       fixup_kernel_args{w.R, w.pM, Tc, w.listed, w.n_listed, (int32_t)tiles_v},
+                       FixupArgs{w.R, w.pM, Tc, w.listed, w.n_listed, (int32_t)tiles_v},
                        LossSums{w.loss, n_partials, loss_accum, stats});
     RBP_CHECK_LAUNCH("policy_fused_fwd_bwd");
     // dlogp is the merge's, but loss_accum and stats are complete only now

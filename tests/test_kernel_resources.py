@@ -48,10 +48,12 @@ def _resources(src):
     return out
 
 
-def _kernels(src, fragment):
-    """Every instance (template instantiations included) of a kernel."""
-    hits = [v for k, v in _resources(src).items() if fragment in k]
-    assert hits, (src, fragment, list(_resources(src)))
+def _kernels(src, kernel):
+    """Every instance (template instantiations included) of a kernel: the
+    function of that name, not one whose mangled arguments contain it."""
+    own = re.compile(rf"_ZN12_GLOBAL__N_1{len(kernel)}{kernel}[IE]")
+    hits = [v for k, v in _resources(src).items() if own.match(k)]
+    assert hits, (src, kernel, list(_resources(src)))
     return hits
 
 
@@ -63,10 +65,21 @@ def _kernels(src, fragment):
     ("logprob_bwd.hip", "dweight_kernel"),
     ("fused.hip", "logits_store_kernel"),
     ("fused.hip", "fused_merge_kernel"),
-    ("fused.hip", "fixup_kernel"),
+    ("logprob_bwd.hip", "grad_both_kernel"),
+    ("logprob_bwd.hip", "part_add_kernel"),
+    ("logprob_bwd.hip", "part_add_dh_kernel"),
+    ("logprob_fwd.hip", "lse_merge_kernel"),
     ("fused.hip", "token_scale_kernel"),
     ("sample_gather.hip", "select_rest_kernel"),
     ("sample_gather.hip", "draw_kernel"),
+    ("sample_gather.hip", "draw_rows_kernel"),
+    ("sample_gather.hip", "sample_packed_kernel"),
+    ("sample_gather.hip", "sample_padded_kernel"),
+    ("sample_gather.hip", "gather_padded_kernel"),
+    ("buffer_ops.hip", "push_kernel"),
+    ("buffer_ops.hip", "use_small_kernel"),
+    ("advantage_loss.hip", "group_advantage_kernel"),
+    ("advantage_loss.hip", "grpo_token_kernel"),
 ])
 def test_hot_kernels_do_not_spill(src, kernel):
     for vgprs, scratch in _kernels(src, kernel):
