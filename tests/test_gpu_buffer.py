@@ -317,8 +317,8 @@ def test_push_of_a_full_capacity_evicts_exactly_the_live_records():
 
 
 def test_push_long_records_and_note_use_at_full_capacity():
-    # records of up to 9000 tokens into 8192-token rows: the copy splits each
-    # row over 16 blocks that loop over it, and records past the row are cut
+    # records of up to 9000 tokens into 8192-token rows: four blocks take a pass
+    # of each row, and records past the row are cut
     rbp = require_gpu()
     cap, slot = 48, 8192
     ring = rbp.make_ring(cap, slot)

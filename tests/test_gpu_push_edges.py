@@ -93,3 +93,30 @@ def test_push_one_long_record_among_many():
         lens[300] = 2049
         c.push(lens, [8] * 75)
     c.compare()
+
+
+def test_push_of_many_records_and_groups_into_a_wrapped_ring():
+    """More than 256 groups (two blocks of them) and 1030 records (five blocks of
+    fields), the evicted ones starting inside a block; rows of two passes.  Use
+    counts of 0 to 5 and more reach the histogram from several blocks."""
+    rbp = require_gpu()
+    c = _Check(rbp, 1500, 2300, seed=5)
+    c.push(c.rng.integers(1, 2400, 900), [9] * 100)
+    c.use(2500)
+    # 1500 - 900 = 600: records 600 .. 1029 evict, from inside the block 512 .. 767
+    c.push(c.rng.integers(1, 2400, 1030), [3] * 340 + [1] * 9 + [1])
+    c.compare()
+    c.use(3000)
+    c.push(c.rng.integers(1, 100, 1500), [5] * 257 + [215])  # every row, wrapping
+    c.compare()
+
+
+def test_push_of_groups_past_the_stage():
+    """256 groups of 18 hold 4608 records, more than a block stages in LDS, so
+    their rewards are read directly; the block of the last groups stages its own."""
+    rbp = require_gpu()
+    c = _Check(rbp, 6000, 8, seed=6)
+    for sizes in ([18] * 256 + [7] * 30, [16] * 256 + [17] * 3, [4097], [1] * 300):
+        c.push(c.rng.integers(1, 9, sum(sizes)), sizes)
+        c.use(4000)
+    c.compare()
