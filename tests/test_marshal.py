@@ -118,7 +118,12 @@ def test_the_given_stream_is_used():
     early = s.query()  # the current stream has nothing to wait for
     s.synchronize()
     assert not early and hist[3].item() == 1000
+    # the current stream, when none is given: nothing of it reaches the default
+    # stream, which reads the counts while `s` is still busy
     with torch.cuda.stream(s):
+        torch.cuda._sleep(50_000_000)
         rbp.rb_hist_accumulate(v, hist)
+    before = hist[3].item()
+    early = s.query()
     s.synchronize()
-    assert hist[3].item() == 2000
+    assert not early and before == 1000 and hist[3].item() == 2000
