@@ -118,12 +118,14 @@ def test_the_given_stream_is_used():
     early = s.query()  # the current stream has nothing to wait for
     s.synchronize()
     assert not early and hist[3].item() == 1000
-    # the current stream, when none is given: nothing of it reaches the default
-    # stream, which reads the counts while `s` is still busy
-    with torch.cuda.stream(s):
-        torch.cuda._sleep(50_000_000)
+    # the current stream, when none is given: captured there, so nothing runs
+    # before the replay (a launch on any other stream would not be captured)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
         rbp.rb_hist_accumulate(v, hist)
-    before = hist[3].item()
-    early = s.query()
-    s.synchronize()
-    assert not early and before == 1000 and hist[3].item() == 2000
+    torch.cuda.synchronize()
+    assert hist[3].item() == 1000
+    for n in (2, 3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert hist[3].item() == 1000 * n
