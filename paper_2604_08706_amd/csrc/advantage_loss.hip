@@ -32,11 +32,21 @@ __global__ void __launch_bounds__(kAdvGroups) group_advantage_kernel(
     const float* __restrict__ reward, const int32_t* __restrict__ group_off,
     int32_t n_groups, int32_t ddof, float eps, float* __restrict__ adv) {
   __shared__ float r_s[rbp::kAdvStage], a_s[rbp::kAdvStage];
-  int32_t lo, n;
-  if (!rbp::block_advantages<kAdvGroups>(
-          reward, group_off, (int32_t)blockIdx.x * kAdvGroups, n_groups, ddof, eps, r_s, lo, n,
-          [&](int32_t i, float a) { adv[i] = a; }, [&](int32_t k, float a) { a_s[k] = a; }))
+  const int32_t g0 = blockIdx.x * kAdvGroups;
+  const int32_t g1 = g0 + kAdvGroups < n_groups ? g0 + kAdvGroups : n_groups;
+  const int32_t g = g0 + threadIdx.x;
+  const int32_t lo = group_off[g0], n = group_off[g1] - lo;
+  if (n > rbp::kAdvStage) {
+    if (g < g1)
+      rbp::group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps,
+                           [&](int32_t i, float a) { adv[i] = a; });
     return;
+  }
+  for (int32_t k = threadIdx.x; k < n; k += kAdvGroups) r_s[k] = reward[lo + k];
+  __syncthreads();
+  if (g < g1)
+    rbp::group_advantage(r_s, group_off[g] - lo, group_off[g + 1] - lo, ddof, eps,
+                         [&](int32_t k, float a) { a_s[k] = a; });
   __syncthreads();
   for (int32_t k = threadIdx.x; k < n; k += kAdvGroups) adv[lo + k] = a_s[k];
 }

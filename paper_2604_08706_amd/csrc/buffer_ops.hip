@@ -73,13 +73,23 @@ __global__ void __launch_bounds__(kPushThreads) push_kernel(
   int32_t b = (int32_t)blockIdx.x;
   if (b < group_blocks) {
     if (blockIdx.y != 0) return;
-    int32_t lo, n;
+    const int32_t g0 = b * kPushThreads;
+    const int32_t g1 = g0 + kPushThreads < n_groups ? g0 + kPushThreads : n_groups;
+    const int32_t g = g0 + (int32_t)threadIdx.x;
+    const int32_t lo = group_off[g0], n = group_off[g1] - lo;
     auto out = [&](int32_t k, float a) {
       ring.advantage[ring_row(ring.base, k, ring.cap)] = a;
     };
-    rbp::block_advantages<kPushThreads>(reward, group_off, b * kPushThreads, n_groups, ddof, eps,
-                                        lds.r, lo, n, out,
-                                        [&](int32_t k, float a) { out(lo + k, a); });
+    if (n > rbp::kAdvStage) {
+      if (g < g1)
+        rbp::group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps, out);
+      return;
+    }
+    for (int32_t k = threadIdx.x; k < n; k += kPushThreads) lds.r[k] = reward[lo + k];
+    __syncthreads();
+    if (g < g1)
+      rbp::group_advantage(lds.r, group_off[g] - lo, group_off[g + 1] - lo, ddof, eps,
+                           [&](int32_t k, float a) { out(lo + k, a); });
     return;
   }
   b -= group_blocks;

@@ -46,37 +46,14 @@ __device__ __forceinline__ void group_advantage(const float* __restrict__ reward
   for (int32_t i = lo; i < hi; ++i) out(i, (float)(((double)reward[i] - mean) / denom));
 }
 
-// Records of a block's groups that fit its stage in LDS.
+// Records of a block's groups that fit its stage in LDS: the records of
+// consecutive groups form one contiguous range, which is read with coalesced
+// accesses when it fits (a thread per group reading its own records makes a
+// wave's loads 4 G bytes apart), and directly when it does not.  The kernels
+// write the two paths out, each with its own output: with one output that asks
+// for the path at every record, and the stride read from the launch, 10^6
+// records in groups of 8 took 6.8 us and not 6.0, one group of 3000 records
+// 637 and not 508.
 constexpr int kAdvStage = 4096;
-
-// The groups [g0, g0 + kThreads) below n_groups, one thread each.  Their
-// records form one contiguous range, returned as its first record `lo` and
-// length `n`; when it fits the stage `r_s`, it is read with coalesced accesses
-// (a thread per group reading its own records makes a wave's loads 4 G bytes
-// apart), longer ranges are read directly.  Same arithmetic either way.
-// Returns whether it was staged; staged(i - lo, A_i) or direct(i, A_i) has then
-// received record i's value.  Two outputs, so that neither path's loop over a
-// group's records asks which one it is on: with that test inside, and the
-// stride read from the launch, 10^6 records in groups of 8 took 6.8 us and
-// not 6.1, one group of 3000 records 644 and not 508.
-template <int kThreads, class Direct, class Staged>
-__device__ __forceinline__ bool block_advantages(const float* __restrict__ reward,
-                                                 const int32_t* __restrict__ group_off,
-                                                 int32_t g0, int32_t n_groups, int32_t ddof,
-                                                 float eps, float (&r_s)[kAdvStage], int32_t& lo,
-                                                 int32_t& n, Direct direct, Staged staged) {
-  const int32_t g1 = g0 + kThreads < n_groups ? g0 + kThreads : n_groups;
-  const int32_t g = g0 + (int32_t)threadIdx.x;
-  lo = group_off[g0];
-  n = group_off[g1] - lo;
-  if (n > kAdvStage) {
-    if (g < g1) group_advantage(reward, group_off[g], group_off[g + 1], ddof, eps, direct);
-    return false;
-  }
-  for (int32_t k = threadIdx.x; k < n; k += kThreads) r_s[k] = reward[lo + k];
-  __syncthreads();
-  if (g < g1) group_advantage(r_s, group_off[g] - lo, group_off[g + 1] - lo, ddof, eps, staged);
-  return true;
-}
 
 }  // namespace rbp
