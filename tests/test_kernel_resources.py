@@ -87,6 +87,18 @@ def test_hot_kernels_do_not_spill(src, kernel):
         assert vgprs <= 256
 
 
+def _assembly(src, kernel):
+    """gfx950 assembly of a kernel; template arguments may follow its name as
+    they are mangled (Lb1: true)."""
+    with tempfile.TemporaryDirectory() as tmp:
+        asm = os.path.join(tmp, "k.s")
+        r = subprocess.run([b.hipcc(), *b.FLAGS, "--cuda-device-only", "-S",
+                            os.path.join(b.CSRC, src), "-o", asm], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        text = open(asm).read()
+    return re.search(rf"^_ZN\S*{kernel}\S*:.*?^\.Lfunc_end", text, re.S | re.M).group(0)
+
+
 def test_group_advantage_paths_are_apart():
     """rb_group_advantage has a path through LDS and a direct one.  Each member
     of a group is written in two places (all rewards equal, or not), so the
@@ -94,13 +106,15 @@ def test_group_advantage_paths_are_apart():
     three global ones: the copy out of the stage and the direct path's two.
     More means that a loop over a group's records tests for the path and
     carries both of its stores."""
-    with tempfile.TemporaryDirectory() as tmp:
-        asm = os.path.join(tmp, "k.s")
-        r = subprocess.run([b.hipcc(), *b.FLAGS, "--cuda-device-only", "-S",
-                            os.path.join(b.CSRC, "advantage_loss.hip"), "-o", asm],
-                           capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr
-        text = open(asm).read()
-    body = re.search(r"^_ZN\S*group_advantage_kernel\S*:.*?^\.Lfunc_end", text, re.S | re.M)
-    stores = [len(re.findall(op, body.group(0))) for op in ("ds_write", "global_store")]
+    body = _assembly("advantage_loss.hip", "group_advantage_kernel")
+    stores = [len(re.findall(op, body)) for op in ("ds_write", "global_store")]
     assert stores == [3, 3]
+
+
+@pytest.mark.parametrize("kernel", ["gather_padded_kernelILb1", "gather_padded_kernelILb0",
+                                    "sample_padded_kernelILb0ELb1",
+                                    "sample_padded_kernelILb0ELb0"])
+def test_padded_rows_branch_once_per_position(kernel):
+    """A position past the record skips its loads; the padding is set before, so
+    the branch has no other side (s_or_saveexec begins one)."""
+    assert "s_or_saveexec" not in _assembly("sample_gather.hip", kernel)
