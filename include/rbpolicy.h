@@ -43,8 +43,11 @@
  *     on the host before anything is enqueued; on an error nothing is enqueued,
  *     except RBP_EHIP, which reports a failed launch (outputs then undefined).
  *     rbp_last_error() gives a thread-local description of the last failure.
- *   - Results are bitwise reproducible for identical inputs (no floating-point
- *     atomics; every reduction runs in a fixed order).
+ *   - Results are bitwise reproducible for identical inputs and workspace sizes
+ *     (no floating-point atomics; every reduction runs in a fixed order).  The
+ *     gradients of policy_logprob_bwd and policy_fused_fwd_bwd are summed in an
+ *     order that the workspace's size decides: its chunks, and the partial sums
+ *     that fit beyond them.
  *   - No exception crosses this interface.  The library holds no mutable global
  *     state except the thread-local error text.
  */

@@ -31,11 +31,12 @@
 //      tile was stored against its own maximum); the others -- a ratio below
 //      about e^-20 or above about e^40, or an invalid behaviour log-prob --
 //      are listed and take M_t as their reference instead;
-//   3. the clipped loss writes dlogp and its sums, by the merge's blocks (beyond
-//      65536 tokens per chunk by policy_loss_fwd_bwd's own launches);
-//   4. in one launch: the loss's sums over the blocks; the listed tokens' columns of Q^T are re-referenced to M_t in place;
-//      then per token c_t = -dlogp_t exp(ref_t - lse_t), so that
-//      dz_{t,v} = c_t q_{t,v} off the target, and the target entry becomes
+//   3. the clipped loss writes dlogp and its sums per block, in the merge's blocks
+//      (beyond 65536 tokens per chunk in policy_loss_fwd_bwd's own launches);
+//   4. in one launch: the loss's sums over the blocks; the listed tokens' columns
+//      of Q^T are re-referenced to M_t in place; and per token
+//      c_t = -dlogp_t exp(ref_t - lse_t), so that dz_{t,v} = c_t q_{t,v} off the
+//      target, and the target entry becomes
 //      q_{t,y} = dz_{t,y} / c_t = exp(lse_t - ref_t) (p_{t,y} - 1); and
 //      H' = c (.) H, row t of the hidden states scaled by c_t, in bf16;
 //   5. dW (+)= Q H' (sum over tokens of q_t (c_t h_t)^T) and

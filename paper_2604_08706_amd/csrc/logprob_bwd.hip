@@ -178,8 +178,8 @@ __device__ __forceinline__ void last_round_tile(int32_t i, int32_t r, int32_t ba
 }
 
 // The last round of a dhidden launch: its r tiles (blocks base .. base + r - 1
-// of the launch over every tile), fewer than there are compute units, cut along the vocabulary
-// so that every unit has work (Pieces, below).  A workgroup's accumulators
+// of the launch over every tile), fewer than there are compute units, cut along
+// the vocabulary so that every unit has work (pieces.h).  A workgroup's accumulators
 // are carried from piece to piece of a tile; a tile's first share goes to dH
 // and the others to their slots of `part`, arrays laid out like dH that
 // part_add_dh_kernel adds in order.
@@ -517,7 +517,13 @@ size_t rbp::logprob_bwd_ws(int64_t Tc, int32_t d, int32_t V) {
   const int64_t T256 = round256(Tc < 1 ? 1 : Tc);
   const int32_t dd = d < 1 ? 1 : d;
   const BwdWs w = carve_bwd(nullptr, T256, dd, V);
-  // pieces of 8 steps: heads of up to 1024 words ask for no more than ever
+  // Planned with pieces of 8 steps, where a launch cuts down to 4 (and the single
+  // pass asks for 4), for the sake of the size alone: heads of up to 1024 words
+  // then ask for exactly dz^T and one dhidden, which callers may have counted
+  // on.  It costs them time, not results: 256 tokens of d = 64, V = 1000 take
+  // 29.8 us so and 25.7 with 575 KB more, which a caller may give; d = 128,
+  // V = 2048 33.1 with the 256 KB asked for, 30.0 with 1.1 MB, 41.9 with none.
+  // From d = 512 on both plans ask for the most a chunk may.
   return w.bytes + dhidden_extra(T256, dd, V, w.bytes - w.scratch_at, w.bytes,
                                  carve_bwd(nullptr, T256 + 256, dd, V).bytes, 8);
 }

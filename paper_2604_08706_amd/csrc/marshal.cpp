@@ -4,7 +4,9 @@
 //
 // Checked from Python and passed through ctypes, an argument cost about 1 us
 // and a call 2 to 3 more: 15 us for the loss, 30 for the single pass, more than
-// the GPU works on a small batch.  Here a whole call costs about 1 us.
+// the GPU works on a small batch.  Here the checks cost a fraction of that: a
+// call with one launch takes 2.9 us in all (a histogram) to 3.2 (a push, a
+// draw), the loss with its two launches 5.6.
 //
 // The GIL is released around the library call, whose launches may block on a
 // full queue.  No C++ exception leaves a function: torch's become Python ones.

@@ -17,7 +17,7 @@
 //       again one bit per slot with the numbers per granule;
 //   the k-th marked slot (slot = FIFO position, 0 = oldest) is then found by
 //   rank (ranks.h): no list of slots is written or read back.
-//   up to 1024 draws, as far as it pays (launch rules below), one launch:
+//   up to 1024 draws, as far as it pays (launch_rules.h), one launch:
 //   sample_packed / sample_padded : every block draws what it copies --
 //       Philox4x64-10 block -> slot -> record -- and, packed, scans all the
 //       lengths; the first block writes the per-draw outputs;
@@ -1068,13 +1068,14 @@ int sample_gather(const rb_records* rec, const rb_sample_cfg* cfg, const rb_batc
     // 27.9 us in 12 blocks each, 13.5 in one)
     int64_t by = rbp::ceil_div(cfg->l_max, 256 * (vec ? 4 * kRowVecs : kRowSingles));
     if (by > 1280 / cfg->n_draw) by = 1280 / cfg->n_draw;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)cfg->n_draw + 1, (unsigned)by), dim3(kFuseThreads), 0, s, p,
-                       ranks, t);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cfg->n_draw + 1, (unsigned)by),
+                       dim3(kFuseThreads), 0, s, p, ranks, t);
     RBP_CHECK_LAUNCH("rb_sample_gather");
     return RBP_OK;
   }
   if (cfg->n_draw <= kDrawThreads) {
-    hipLaunchKernelGGL(ranks.nb > 0 ? draw_kernel<true> : draw_kernel<false>, dim3(1), dim3(kDrawThreads), 0, s, p, ranks, t, w.meta + 1);
+    hipLaunchKernelGGL(ranks.nb > 0 ? draw_kernel<true> : draw_kernel<false>, dim3(1),
+                       dim3(kDrawThreads), 0, s, p, ranks, t, w.meta + 1);
   } else {
     const int64_t nb = rbp::ceil_div(cfg->n_draw, kRowThreads);
     hipLaunchKernelGGL(ranks.nb > 0 ? draw_rows_kernel<true> : draw_rows_kernel<false>, dim3(nb),
