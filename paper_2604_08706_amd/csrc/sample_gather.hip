@@ -653,8 +653,11 @@ __global__ void __launch_bounds__(kThreads) sample_packed_kernel(DrawParams p, R
 // thread has kGroups groups (or positions) in flight.  The padding is set first
 // and the loads are under one condition: as selects, which become two branches
 // each, with the stride read from the launch, 4096 rows of 512 took 18.8 us
-// and not 18.5, 100 rows of 16383 9.5 and not 7.5.
-template <bool kVec, int kGroups>
+// and not 18.5, 100 rows of 16383 9.5 and not 7.5.  kSelect: behind a draw by
+// rank it is the other way round, and the draws there are many and narrow: 1000
+// rows of 1047 15.9 us as selects and 16.6 under one condition, 1024 rows of 400
+// 15.5 and 15.9 (only wide ragged rows lose: 256 of 8191 16.1 and 15.1).
+template <bool kVec, int kGroups, bool kSelect>
 __device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, int64_t off,
                                          const int32_t* __restrict__ arena_tokens,
                                          const float* __restrict__ arena_old,
@@ -665,7 +668,7 @@ __device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, in
   float* old_row = old_logp + j * l_max;
   int32_t* seq_row = seq + j * l_max;
   if constexpr (kVec) {
-    constexpr int64_t step = kFuseThreads * 4;
+    const int64_t step = (kSelect ? (int64_t)blockDim.x : kFuseThreads) * 4;
     for (int64_t p0 = blockIdx.y * (step * kGroups) + threadIdx.x * 4; p0 < l_max;
          p0 += gridDim.y * (step * kGroups)) {
       int32_t tk[kGroups][4], sq[kGroups][4];
@@ -675,13 +678,19 @@ __device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, in
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int64_t p = p0 + u * step + i;
-          tk[u][i] = 0;
-          ol[u][i] = 0.0f;
-          sq[u][i] = -1;
-          if (p < n) {
-            tk[u][i] = arena_tokens[off + p];
-            ol[u][i] = arena_old[off + p];
-            sq[u][i] = (int32_t)j;
+          if constexpr (kSelect) {
+            tk[u][i] = p < n ? arena_tokens[off + p] : 0;
+            ol[u][i] = p < n ? arena_old[off + p] : 0.0f;
+            sq[u][i] = p < n ? (int32_t)j : -1;
+          } else {
+            tk[u][i] = 0;
+            ol[u][i] = 0.0f;
+            sq[u][i] = -1;
+            if (p < n) {
+              tk[u][i] = arena_tokens[off + p];
+              ol[u][i] = arena_old[off + p];
+              sq[u][i] = (int32_t)j;
+            }
           }
         }
 #pragma unroll
@@ -695,7 +704,7 @@ __device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, in
       }
     }
   } else {
-    constexpr int64_t step = kFuseThreads;
+    const int64_t step = kSelect ? (int64_t)blockDim.x : kFuseThreads;
     for (int64_t p0 = blockIdx.y * (step * kGroups) + threadIdx.x; p0 < l_max;
          p0 += gridDim.y * (step * kGroups)) {
       int32_t tk[kGroups];
@@ -703,11 +712,16 @@ __device__ __forceinline__ void fill_row(int64_t j, int64_t l_max, int64_t n, in
 #pragma unroll
       for (int u = 0; u < kGroups; ++u) {
         const int64_t p = p0 + u * step;
-        tk[u] = 0;
-        ol[u] = 0.0f;
-        if (p < n) {
-          tk[u] = arena_tokens[off + p];
-          ol[u] = arena_old[off + p];
+        if constexpr (kSelect) {
+          tk[u] = p < n ? arena_tokens[off + p] : 0;
+          ol[u] = p < n ? arena_old[off + p] : 0.0f;
+        } else {
+          tk[u] = 0;
+          ol[u] = 0.0f;
+          if (p < n) {
+            tk[u] = arena_tokens[off + p];
+            ol[u] = arena_old[off + p];
+          }
         }
       }
 #pragma unroll
@@ -753,9 +767,9 @@ __global__ void __launch_bounds__(kFuseThreads) sample_padded_kernel(DrawParams 
     write_draw(p, t, j, slot, r, len);
     t.cu_seqlens[j + 1] = (int32_t)((j + 1) * p.l_max);
   }
-  fill_row<kVec, kVec ? kRowVecs : kRowSingles>(j, p.l_max, stream_len(p, len), off,
-                                                t.arena_tokens, t.arena_old, t.tokens, t.old_logp,
-                                                t.seq);
+  fill_row<kVec, kVec ? kRowVecs : kRowSingles, kRanks>(j, p.l_max, stream_len(p, len), off,
+                                                        t.arena_tokens, t.arena_old, t.tokens,
+                                                        t.old_logp, t.seq);
 }
 
 // ---- draws, then the gather -------------------------------------------------
@@ -877,8 +891,8 @@ __global__ void __launch_bounds__(kFuseThreads) gather_padded_kernel(
     int32_t* __restrict__ tokens, float* __restrict__ old_logp, int32_t* __restrict__ seq) {
   const int64_t j = blockIdx.x;
   const int64_t n = len[j] < l_max ? len[j] : l_max;
-  fill_row<kVec, 1>(j, l_max, n, arena_off[phys_row(idx[j], head, cap)], arena_tokens, arena_old,
-                    tokens, old_logp, seq);
+  fill_row<kVec, 1, false>(j, l_max, n, arena_off[phys_row(idx[j], head, cap)], arena_tokens,
+                           arena_old, tokens, old_logp, seq);
 }
 
 // Workspace of a table of `capacity` rows.  Its size is part of the contract of
